@@ -126,20 +126,19 @@ rtm_status rtm_plan_workspace_bytes(const rtm_plan *plan, size_t *bytes);
 double rtm_cfl_bound(int32_t ndim);
 const char *rtm_status_str(rtm_status s);
 /* Tuning hooks, process wide: stencil kernel of the sweeps.  -1 automatic
- * (LDS-tiled 64 x 16 for F32 3D grids, else one thread per cell), 0 one
- * thread per cell, 1..13 LDS-tiled z-marching variants (3D; x-width x y-rows):
- * 1: 64x16, 2: 64x32, 3: 64x16 with 512 threads, 4: 64x16 with 128 threads,
- * 5: 32x32, 6: 128x8, 7: as 1 and 8: as 2 with non-temporal streaming loads
- * and stores, 9: 64x32 with 512 threads, 10: 64x32 with 1024 threads,
- * 11: as 3 (all three non-temporal), 12: as 7 and 13: as 9 with the x/y halo
- * of a plane loaded four planes ahead, with the column fronts.  Every choice
- * gives bitwise-identical levels.  Batched shots run the 64x16 variants 3,
- * 11, 7 or 12 (8..10 select 7, 13 selects 12, the others 1).
+ * (3D grids: LDS-tiled, the shape chosen from the grid's size; small and 2D
+ * grids: one thread per cell), 0 one thread per cell, 1..13 LDS-tiled
+ * z-marching variants (3D; x-width x y-rows, rows halved for F64): 1: 64x16,
+ * 2: 64x32, 3: 64x32 with two rows per thread, 4: 64x8, 5: 32x32, 6: 128x8,
+ * 7..12: as 1..6 with non-temporal streaming loads and stores, 13: 32x16.
+ * Every choice gives bitwise-identical levels.  Batched shots run 64x16 tiles,
+ * non-temporal for 7..12.
  * rtm_set_stencil_blocks: the tiled acoustic kernels split z into the fewest
- * chunks (of at least 16 planes) that give a launch this many workgroups of
- * 256 threads' worth (default 2048; a 512 thread shape aims at half as
- * many); a batch's tile table (made by rtm_batch_create) aims at twice as
- * many.  The TTI kernels have their own targets (rtm_set_tti_blocks). */
+ * chunks (of at least 4 planes) that give a launch this many workgroups of
+ * 256 threads' worth (default 2048, which leaves the split of the automatic
+ * variant to its own rule); a batch's tile table (made by rtm_batch_create)
+ * aims at twice as many.  The TTI kernels have their own targets
+ * (rtm_set_tti_blocks). */
 void rtm_set_stencil_variant(int variant);
 void rtm_set_stencil_blocks(int32_t blocks);
 /* Tuning hook, process wide: with on != 0 (default) the tiled stencil of the

@@ -32,7 +32,7 @@ using namespace rtm;
 // ---------------------------------------------------------------------------
 static thread_local std::string g_last_error;
 static int g_stencil_variant = -1;  // -1 auto, else kStencilSimple / a tiled variant id
-static int g_stencil_blocks = 2048; // tiled stencil: split z until this many workgroups
+static int g_stencil_blocks = kAutoBlocks;  // tiled stencil: split z until this many workgroups
 // tiled TTI kernels' z-split targets (forward, transpose).  At 300 x 400 x 400
 // the forward step (700 tiles, three workgroups per CU) is fastest with 4
 // chunks (650 us; 1 chunk 684-691 us), the transpose (350 tiles, one
@@ -217,7 +217,7 @@ extern "C" void rtm_set_tti_blocks(int32_t forward, int32_t transpose) {
 }
 
 extern "C" void rtm_set_stencil_blocks(int32_t blocks) {
-  g_stencil_blocks = blocks > 0 ? blocks : 2048;
+  g_stencil_blocks = blocks > 0 ? blocks : kAutoBlocks;
 }
 
 extern "C" void rtm_profile_enable(int32_t stride) {
@@ -510,9 +510,7 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
     return ring + (int64_t)slot * P->ld;
   };
   const int ndim = d.ndim;
-  int variant = kStencilSimple;
-  if (ndim == 3 && sizeof(T) == 4) variant = kStencilTiled;
-  if (g_stencil_variant >= 0) variant = g_stencil_variant;
+  const int variant = g_stencil_variant;
   StepArgs<T> a = step_args<T>(P, static_cast<const T *>(io.m));
   const int nb = io.n_begin, ne = io.n_end < 0 ? d.nt : io.n_end;
   if (io.state_in) {
@@ -1217,9 +1215,7 @@ static rtm_status exact_impl(const rtm_plan *P, const void *mv, const double *sr
   const T *q = static_cast<const T *>(qv);
   T *resid = static_cast<T *>(residv);
   T *grad = static_cast<T *>(gradv);
-  int variant = kStencilSimple;
-  if (ndim == 3 && sizeof(T) == 4) variant = kStencilTiled;
-  if (g_stencil_variant >= 0) variant = g_stencil_variant;
+  const int variant = g_stencil_variant;
   StepArgs<T> a = step_args<T>(P, m);
 
   // 1. forward sweep, traces, checkpoints (u^{jc}, u^{jc-1}) before step jc
@@ -1253,7 +1249,7 @@ static rtm_status exact_impl(const rtm_plan *P, const void *mv, const double *sr
   const T inv_dt2 = (T)(1.0 / (d.dt * d.dt));
   // fuse the u_tt store and the correlation into the stencil when a tiled
   // kernel serves the grid (3D F32); else separate passes
-  const bool fused = g_exact_fused && ndim == 3 && sizeof(T) == 4 && variant >= kStencilTiled;
+  const bool fused = g_exact_fused && ndim == 3 && sizeof(T) == 4 && variant != kStencilSimple;
   for (int j = ncp - 1; j >= 0; --j) {
     const int n_lo = j * c, n_hi = std::min(nt, (j + 1) * c);
     HIP_TRY(launch_copy<T>(lvF(n_lo), CP + (int64_t)(2 * j) * ld, N, st));
@@ -1430,6 +1426,8 @@ struct rtm_batch {
   size_t tab_off = 0, tab_bytes = 0, total = 0;
   std::vector<int4> tile_host;
   int32_t nsrc_total = 0, nrec_total = 0;
+  bool ragged = false;  // a row length that is no multiple of four
+  bool stream = false;  // the levels of one step exceed the memory-side cache
   // cached graph of the last fwi_gradient_batched launch sequence
   hipGraphExec_t gexec = nullptr;
   uint64_t gkey = 0;
@@ -1485,10 +1483,12 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
     b->nrec_total += shots[i].nrec;
   }
   // tile table: 64 x 16 column tiles of every shot, z split until the launch
-  // has >= 2 x rtm_set_stencil_blocks workgroups (default 4096; each chunk >=
-  // 16 planes): the windows are shallow (128-256 planes) and the extra waves
-  // in flight outweigh the chunks' warm-up planes (measured: 1024 -> 4096
-  // workgroups, 115 -> 121 Gcell-updates/s).  Fixed when the batch is created.
+  // has >= 2 x rtm_set_stencil_blocks workgroups (default 4096): the windows
+  // are shallow (128-256 planes) and the extra waves in flight outweigh the
+  // chunks' warm-up planes.  Chunks of at least 16 planes where the shots'
+  // levels stream from HBM, of 4 where they stay in the memory-side cache
+  // (the warm-up planes then cost less than idle CUs).  Fixed when the batch
+  // is created.
   int nzc = 1;
   auto count = [&](int z) {
     int64_t t = 0;
@@ -1497,7 +1497,13 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
   };
   int minz = INT32_MAX;
   for (auto *p : b->P) minz = std::min<int>(minz, (int)p->d.nz);
-  while (count(nzc) < 2 * (int64_t)g_stencil_blocks && minz / (nzc * 2) >= 16) nzc *= 2;
+  int64_t cells = 0;
+  for (auto *p : b->P) {
+    cells += p->N;
+    b->ragged |= p->d.nx % 4 != 0;
+  }
+  b->stream = 16 * cells > (int64_t)640000000;
+  while (count(nzc) < 2 * (int64_t)g_stencil_blocks && minz / (nzc * 2) >= (b->stream ? 16 : 4)) nzc *= 2;
   for (int i = 0; i < nshots; ++i) {
     const rtm_desc &d = b->P[i]->d;
     const int ntx = (int)((d.nx + 63) / 64), nty = (int)((d.ny + 15) / 16);
@@ -1669,7 +1675,7 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   }
   int s0 = 0;
   for (int s = 0; s < nt; ++s) {
-    HIP_TRY(launch_stencil_batched<float>(shots, tiles, ntiles, s, variant, st,
+    HIP_TRY(launch_stencil_batched<float>(shots, tiles, ntiles, s, variant, b->ragged, st,
                                           g_stencil_alternate ? (s & 1) : 0));
     HIP_TRY(launch_inject_batched<float>(shots, iof, src_t, s, s, st));
     HIP_TRY(launch_sample_batched<float>(shots, iof, rec_t, s, s, st));
@@ -1693,7 +1699,7 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   }
   s0 = 0;
   for (int s = 0; s < nt; ++s) {
-    HIP_TRY(launch_stencil_batched<float>(shots, tiles, ntiles, s, variant, st,
+    HIP_TRY(launch_stencil_batched<float>(shots, tiles, ntiles, s, variant, b->ragged, st,
                                           g_stencil_alternate ? (s & 1) : 0));
     HIP_TRY(launch_inject_batched<float>(shots, ioa, rec_t, s, nt - 1 - s, st));
     if (s + 1 - s0 == k || s == nt - 1) {
@@ -1787,7 +1793,7 @@ extern "C" rtm_status fwi_gradient_batched(rtm_batch *b, const rtm_shot_io *io, 
   rtm_status s = stage_batch_points(b, b->src, io, false, host, &snp, &snc, &key);
   if (s) return s;
   if ((s = stage_batch_points(b, b->rec, io, true, host, &rnp, &rnc, &key))) return s;
-  int variant = g_stencil_variant >= kStencilTiled ? g_stencil_variant : 7;
+  int variant = g_stencil_variant >= kStencilTiled ? g_stencil_variant : b->stream ? 7 : 1;
   key = (key ^ (uint64_t)variant) * 1099511628211ull;
   key = (key ^ (uint64_t)(g_stencil_alternate + 64)) * 1099511628211ull;
   HIP_TRY(hipMemcpyAsync(w + b->tab_off, host.data(), b->tab_bytes, hipMemcpyHostToDevice, st));

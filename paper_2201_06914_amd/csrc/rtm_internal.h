@@ -113,6 +113,8 @@ struct ProbeArgs {
 };
 
 // launchers (stream-ordered; return the launch status)
+// variant -1: chosen from the grid, and so are its z chunks if target_blocks
+// is kAutoBlocks
 // rev != 0: the tiled kernels march each z-chunk downwards (same results)
 template <typename T>
 hipError_t launch_stencil(int ndim, const StepArgs<T> &a, int variant, int target_blocks,
@@ -144,7 +146,7 @@ hipError_t launch_offset_gathers(const T *U, const T *V, int nfield, int64_t fst
 // table, then injection / sampling of level s+1 for time index n
 template <typename T>
 hipError_t launch_stencil_batched(const ShotStep<T> *shots, const int4 *tiles, int ntiles, int s,
-                                  int variant, hipStream_t st, int rev = 0);
+                                  int variant, bool ragged, hipStream_t st, int rev = 0);
 template <typename T>
 hipError_t launch_inject_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
                                  const BatchPoints<T> &pt, int s, int n, hipStream_t st);
@@ -233,12 +235,13 @@ hipError_t launch_dot(const T *a, const T *b, int64_t n, double *partials, doubl
 
 constexpr int kReduceBlocks = 1024;  // partial sums of the two-pass reductions
 
-// Stencil variants: 0 = one thread per cell (any ndim, any dtype),
-// 1 = LDS-tiled z-marching (3D).  Both share the per-cell arithmetic, so they
-// give bitwise-identical levels.
+// Stencil variants: 0 = one thread per cell (any ndim, any dtype), 1 .. 13 =
+// LDS-tiled z-marching (3D).  All share the per-cell arithmetic, so they give
+// bitwise-identical levels.
 constexpr int kStencilSimple = 0;
 constexpr int kStencilTiled = 1;     // first LDS-tiled variant
 constexpr int kStencilVariants = 13;  // last variant id
+constexpr int kAutoBlocks = 2048;     // the default z-split target
 
 // XCD-aware block order: hardware workgroup ids go round-robin over the 8
 // XCDs (id b to XCD b mod 8); XCD x receives ids x, x + 8, ... and this maps

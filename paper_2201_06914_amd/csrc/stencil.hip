@@ -6,27 +6,34 @@
 // Two kernels share one per-cell arithmetic (cell_lap / cell_update), so their
 // results are bitwise identical:
 //   k_stencil_simple  one thread per cell, neighbours from global memory
-//                     (2D grids, FP64 3D, reference for the tiled kernel)
-//   k_stencil3d_tiled 3D: a TX x TY column tile per workgroup marches down a
-//                     z-chunk; the current plane (with a 4-cell x/y halo)
-//                     sits in LDS, double buffered, and the z neighbours in a
-//                     9-deep register queue per column.  Loads of plane z+1
-//                     are issued before plane z is computed.
+//                     (2D and small grids, reference for the tiled kernel)
+//   k_stencil3d_tiled 3D: a TX x TY column tile per workgroup marches through
+//                     a z-chunk; the planes z .. z+4 (with a 4-cell x/y halo)
+//                     sit in a ring of LDS planes, and the z neighbours in a
+//                     9-deep register queue per column.  Every access is a
+//                     16-byte vector of consecutive x cells.
 #include <algorithm>
+#include <type_traits>
 
 #include "step_common.h"
 
 namespace rtm {
 
+// The fused multiply-adds of the step are spelled out: left to the compiler,
+// which product of a sum is contracted depends on the code around it, and the
+// kernels that share this arithmetic would differ in the last bit.
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) {
+  return __builtin_fma(a, b, c);
+}
+
 // c1 (p1 + m1) + c2 (p2 + m2) + c3 (p3 + m3) + c4 (p4 + m4), fixed order
 template <typename T>
 __device__ __forceinline__ T axis_sum(const StepArgs<T> &a, T p1, T m1, T p2, T m2, T p3,
                                       T m3, T p4, T m4) {
-  T s = a.c1 * (p1 + m1);
-  s += a.c2 * (p2 + m2);
-  s += a.c3 * (p3 + m3);
-  s += a.c4 * (p4 + m4);
-  return s;
+  T s = fma_t(a.c1, p1 + m1, a.c2 * (p2 + m2));
+  s = fma_t(a.c3, p3 + m3, s);
+  return fma_t(a.c4, p4 + m4, s);
 }
 
 // n / d; for FP32 a hardware reciprocal refined by one Newton step and one
@@ -47,7 +54,8 @@ __device__ __forceinline__ float quot<float>(float n, float d) {
 
 template <typename T>
 __device__ __forceinline__ T cell_update(const StepArgs<T> &a, T u, T up, T m, T lap, T damp) {
-  return quot(T(2) * m * u - (m - damp) * up + a.dt2 * lap, m + damp);
+  const T v = fma_t(u, T(2) * m, -((m - damp) * up));
+  return quot(fma_t(a.dt2, lap, v), m + damp);
 }
 
 // ---------------------------------------------------------------------------
@@ -55,12 +63,12 @@ __device__ __forceinline__ T cell_update(const StepArgs<T> &a, T u, T up, T m, T
 // ---------------------------------------------------------------------------
 template <typename T, int NDIM>
 __global__ __launch_bounds__(256) void k_stencil_simple(StepArgs<T> a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.N) return;
-  const int x = (int)(i % a.nx);
-  const int64_t zy = i / a.nx;
-  const int y = (int)(zy % a.ny);
-  const int z = (int)(zy / a.ny);
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;  // N < 2^31
+  if (i >= (uint32_t)a.N) return;
+  const uint32_t zy = i / (uint32_t)a.nx;
+  const int x = (int)(i - zy * (uint32_t)a.nx);
+  const int z = (int)(zy / (uint32_t)a.ny);
+  const int y = (int)(zy - (uint32_t)z * (uint32_t)a.ny);
   const T *u = a.cur;
   auto U = [&](int zz, int yy, int xx) -> T {
     return (zz >= 0 && zz < a.nz && yy >= 0 && yy < a.ny && xx >= 0 && xx < a.nx)
@@ -76,262 +84,351 @@ __global__ __launch_bounds__(256) void k_stencil_simple(StepArgs<T> a) {
   if constexpr (NDIM == 3) {
     const T ly = axis_sum(a, U(z, y + 1, x), U(z, y - 1, x), U(z, y + 2, x), U(z, y - 2, x),
                           U(z, y + 3, x), U(z, y - 3, x), U(z, y + 4, x), U(z, y - 4, x));
-    lap = ((a.cc * c + lz) + ly) + lx;
+    lap = (fma_t(a.cc, c, lz) + ly) + lx;
   } else {
-    lap = (a.cc * c + lz) + lx;
+    lap = fma_t(a.cc, c, lz) + lx;
   }
   a.next[i] = cell_update(a, c, a.prev[i], a.m[i], lap, sponge_a(a, z, y, x));
 }
 
 // ---------------------------------------------------------------------------
-// 3D LDS tile + z-marching register queue
+// 3D LDS plane ring + z-marching register queue
 // ---------------------------------------------------------------------------
-// NT: streaming (non-temporal) loads of u^{n-1} and m and stores of u^{n+1};
-// each is touched once per step and a level (N x 4 B) exceeds the caches.
-template <typename T, bool NT>
-__device__ __forceinline__ T ld_stream(const T *p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-template <typename T, bool NT>
-__device__ __forceinline__ void st_stream(T *p, T v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
-// Raw buffer loads over one level (N values): an offset at or past the end
-// returns zero, so a cell outside the grid takes the offset `end` (a select)
-// instead of a branch around its load.  NT: the non-temporal hint.
+// A thread owns VX = 16 / sizeof(T) consecutive x cells of RY rows, so every
+// access to the levels, the model and LDS is one 16-byte vector.
 template <typename T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t level_rsrc(const T *f, uint32_t end) {
+struct V16 {
+  static constexpr int n = 16 / (int)sizeof(T);
+  typedef T type __attribute__((ext_vector_type(16 / sizeof(T))));
+};
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Raw buffer over one plane (or nothing: `bytes` = 0): reads at or past the
+// end return zero and stores there are dropped, so a cell outside the grid
+// takes the offset kOff (a per-thread constant) and a plane outside the grid
+// an empty buffer; neither needs a branch or per-load arithmetic.
+constexpr uint32_t kOff = 0x80000000u;  // past the end of any plane (planes are below 2 GiB)
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const T *p, uint32_t bytes) {
   // gfx9 buffer descriptor word 3: 32-bit data format, no swizzle
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(f), (short)0, (int)end, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(p), (short)0, (int)bytes, 0x00020000);
 }
-template <bool NT>
-__device__ __forceinline__ float bload(__amdgpu_buffer_rsrc_t r, uint32_t o, float) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, NT ? 2 : 0));
+__device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, uint32_t o, float) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, 0));
 }
-template <bool NT>
-__device__ __forceinline__ double bload(__amdgpu_buffer_rsrc_t r, uint32_t o, double) {
-  return __builtin_bit_cast(double,
-                            __builtin_amdgcn_raw_buffer_load_b64(r, (int)o, 0, NT ? 2 : 0));
+__device__ __forceinline__ double bload1(__amdgpu_buffer_rsrc_t r, uint32_t o, double) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)o, 0, 0));
 }
-
-// element at a 32-bit byte offset from a base held in scalar registers (the
-// tiled kernels run on levels below 4 GiB)
-template <typename T>
-__device__ __forceinline__ T *at(T *p, uint32_t off) {
-  return reinterpret_cast<T *>(reinterpret_cast<char *>(p) + off);
+__device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, uint32_t o, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)o, 0, 0);
 }
-template <typename T>
-__device__ __forceinline__ const T *at(const T *p, uint32_t off) {
-  return reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + off);
+__device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, uint32_t o, double v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)o, 0, 0);
 }
 
+// Where one thread's vector of a plane sits: `full` its byte offset, or kOff;
+// with RAG (rows whose length is no multiple of VX) a vector that the row's
+// end cuts has full = kOff and its first np cells at `part`.
+struct VOff {
+  uint32_t full = kOff, part = kOff;
+  int np = 0;
+};
+template <typename T, bool RAG>
+__device__ __forceinline__ VOff vec_off(int ny, int nx, int y, int x) {
+  constexpr int VX = V16<T>::n;
+  VOff v;
+  if (y < 0 || y >= ny || x < 0 || x >= nx) return v;
+  const uint32_t o = ((uint32_t)y * (uint32_t)nx + (uint32_t)x) * (uint32_t)sizeof(T);
+  if (!RAG || x + VX <= nx) {
+    v.full = o;
+  } else {
+    v.part = o;
+    v.np = nx - x;
+  }
+  return v;
+}
+template <typename T, bool NT, bool RAG>
+__device__ __forceinline__ typename V16<T>::type vload(__amdgpu_buffer_rsrc_t r, const VOff &o) {
+  typedef typename V16<T>::type V;
+  V v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)o.full, 0, NT ? 2 : 0));
+  if constexpr (RAG) {
+    if (o.np > 0) {  // only the waves that hold a row's end
+#pragma unroll
+      for (int c = 0; c < V16<T>::n - 1; ++c)
+        v[c] = bload1(r, c < o.np ? o.part + c * (uint32_t)sizeof(T) : kOff, T(0));
+    }
+  }
+  return v;
+}
+template <typename T, bool NT, bool RAG>
+__device__ __forceinline__ void vstore(__amdgpu_buffer_rsrc_t r, const VOff &o,
+                                       typename V16<T>::type v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)o.full, 0,
+                                         NT ? 2 : 0);
+  if constexpr (RAG) {
+    if (o.np > 0) {
+#pragma unroll
+      for (int c = 0; c < V16<T>::n - 1; ++c)
+        bstore1(r, c < o.np ? o.part + c * (uint32_t)sizeof(T) : kOff, v[c]);
+    }
+  }
+}
+
+// Bound: beyond the caches by HBM (16 bytes per cell-update; 384 x 512 x 512
+// 261 us, 6.2 TB/s, where the copy kernel reaches 5.9-6.4), before that by the
+// latency of a step.  42 VALU instructions per cell-update (81 with one cell
+// per thread and lane-wise LDS reads, where vector issue bound the step as
+// much as HBM did: 286-318 us at 384 x 512 x 512, 188-255 at 320 x 448 x 448
+// now 173, 27 at 128^3 now 8.8).
 // One column tile (bx, by) over planes [z0, z1) of one level.  EPI adds a
 // cell-local epilogue for the exact comparator: EPI_D2 writes the second time
 // difference of the step, EPI_CORR subtracts (stored u_tt) x (new level) from
 // a gradient.
-// EH (early halo): the x/y halo of plane z is loaded together with the
-// column fronts of plane z (four planes ahead of its use) and held in a short
-// register queue, so that a tile's halo loads and its neighbours' interior
-// loads of the same plane are issued close together in time (L2 reuse).
+// The tile's planes (with their 4-cell x / y halo) pass through a ring of six
+// LDS planes: a plane is written when it is the lead plane z + 4 (its own
+// cells are the fronts of the register queue then) and read four planes later,
+// when it is the current one, so a tile's halo loads and its neighbours'
+// interior loads of a plane are issued close together in time (they meet in
+// L2) and no register waits for a halo.  Six slots make one barrier per plane
+// enough: the slot written before barrier i was last read before barrier
+// i - 1.  Six planes per loop trip turn the slots into immediate LDS offsets
+// and most moves of the register queue into renames.
+// LDS rows are TX cells (the x halo sits apart), so that the four rows of a
+// wave's 16-byte accesses fall on consecutive 16-byte chunks: no conflicts.
 // rev: march the chunk from z1 - 1 down to z0 instead of up (same per-cell
 // arithmetic: the z terms pair z + j with z - j in a commutative sum, so the
 // levels are bitwise the same either way).  Sweeps alternate the direction
 // from step to step, so that a step starts on the planes the previous step
 // touched last (still in the memory-side cache).
-template <typename T, int TX, int TYT, int RY, bool NT, int EPI = EPI_NONE, bool EH = false>
+template <typename T, int TX, int TYT, int RY, bool NT, int EPI, bool RAG>
 __device__ __forceinline__ void tiled_body(const StepArgs<T> &a, int bx, int by, int z0, int z1,
-                                           const EpiArgs<T> &e = EpiArgs<T>{}, bool rev = false) {
-  constexpr int NTH = TX * TYT;
+                                           const EpiArgs<T> &e, bool rev) {
+  typedef typename V16<T>::type V;
+  constexpr int VX = V16<T>::n;                  // cells per vector
+  constexpr int GX = TX / VX;                    // threads along x
+  constexpr int NTH = GX * TYT;
   constexpr int TY = TYT * RY;
-  constexpr int LX = TX + 8;
-  constexpr int LY = TY + 8;
-  constexpr int NHY = (8 + TYT - 1) / TYT;        // y-halo rows per thread
-  constexpr int NHX = (8 * TY + NTH - 1) / NTH;   // x-halo cells per thread
-  __shared__ T lds[2][LY * LX];
+  constexpr int XV = 4 / VX;                     // vectors of one side's x halo
+  constexpr int NYH = 8 * GX;                    // y-halo vectors of a plane
+  constexpr int NH = NYH + TY * 2 * XV;          // all halo vectors
+  constexpr int KH = (NH + NTH - 1) / NTH;       // per thread
+  constexpr int XH = (TY + 8) * TX;              // LDS: rows of TX cells, then x halos [TY][8]
+  constexpr int PS = XH + TY * 8;                // LDS cells of a plane
+  constexpr int SLOTS = 6;
+  __shared__ __attribute__((aligned(16))) T lds[SLOTS * PS];
 
   const int tid = threadIdx.x;
-  const int tx = tid % TX;
-  const int ty = tid / TX;
+  const int tx = tid % GX;
+  const int ty = tid / GX;
   const int x0 = bx * TX, y0 = by * TY;
-  const int x = x0 + tx;
-  const uint32_t sp = (uint32_t)a.ny * (uint32_t)a.nx;
-  const T *__restrict__ u = a.cur;
-  auto off = [&](int zz, int yy, int xx) -> uint32_t {
-    return ((uint32_t)zz * sp + (uint32_t)yy * (uint32_t)a.nx + (uint32_t)xx) * (uint32_t)sizeof(T);
-  };
+  const int x = x0 + tx * VX;
+  const int64_t sp = (int64_t)a.ny * a.nx;
+  const uint32_t pbytes = (uint32_t)(sp * (int64_t)sizeof(T));
 
-  int yr[RY];
-  bool in[RY];
+  VOff own[RY];
+  T fyx[RY][VX];  // dy^2 + dx^2 of the sponge (small integers, exact)
+  int lown[RY], lxl[RY][XV], lxr[RY][XV];  // LDS cells: own vector, x neighbours
 #pragma unroll
   for (int j = 0; j < RY; ++j) {
-    yr[j] = y0 + ty + j * TYT;
-    in[j] = (x < a.nx) && (yr[j] < a.ny);
-  }
-  const uint32_t end = (uint32_t)a.N * (uint32_t)sizeof(T);
-  const __amdgpu_buffer_rsrc_t ru = level_rsrc(u, end), rp = level_rsrc(a.prev, end),
-                               rm = level_rsrc(a.m, end);
-  // no short circuit: one select per load
-  auto ldu = [&](int zz, int yy, int xx) -> T {
-    const bool ok = (zz >= 0) & (zz < a.nz) & (yy >= 0) & (yy < a.ny) & (xx >= 0) & (xx < a.nx);
-    return bload<false>(ru, ok ? off(zz, yy, xx) : end, T(0));
-  };
-  // the cell's previous level and model value (m = 1 off the grid, never used)
-  auto ldpm = [&](int zz, int j, T &pvo, T &mmo) {
-    const uint32_t o = in[j] ? off(zz, yr[j], x) : end;
-    pvo = bload<NT>(rp, o, T(0));
-    const T mv = bload<NT>(rm, o, T(0));
-    mmo = in[j] ? mv : T(1);
-  };
-  // halo bookkeeping: y-halo rows hy = ty + TYT*k (LDS rows 0..3 and TY+4..TY+7),
-  // x-halo cells t = tid + NTH*k over TY rows x 8 columns
-  int hyr[NHY], hyg[NHY];
-  bool hyon[NHY];
+    const int r = ty + j * TYT;
+    own[j] = vec_off<T, RAG>(a.ny, a.nx, y0 + r, x);
+    const int dy = a.ny > 1 ? sponge_depth(y0 + r, a.ny, a.nb) : 0;
 #pragma unroll
-  for (int k = 0; k < NHY; ++k) {
-    const int hy = ty + TYT * k;
-    hyon[k] = hy < 8;
-    hyr[k] = hy < 4 ? hy : TY + hy;
-    hyg[k] = y0 - 4 + hyr[k];
-  }
-  int hxr[NHX], hxc[NHX];
-  bool hxon[NHX];
+    for (int c = 0; c < VX; ++c) {
+      const int dx = sponge_depth(x + c, a.nx, a.nb);
+      fyx[j][c] = T(dy * dy + dx * dx);
+    }
+    lown[j] = (r + 4) * TX + tx * VX;
 #pragma unroll
-  for (int k = 0; k < NHX; ++k) {
-    const int t = tid + NTH * k;
-    hxon[k] = t < 8 * TY;
-    const int row = t / 8, col = t % 8;
-    hxr[k] = 4 + row;
-    hxc[k] = col < 4 ? col : TX + col;
-  }
-
-  // queue slot k holds plane z + dz (k - 4); the march starts at zs
-  const int dz = rev ? -1 : 1;
-  const int zs = rev ? z1 - 1 : z0;
-  const int nz_chunk = z1 - z0;
-  T q[RY][9];
-  T front[RY], pv[RY], mm[RY], hyv[NHY], hxv[NHX];
-  T es[RY], eg[RY];  // EPI_CORR operands, fetched with the plane they belong to
-#pragma unroll
-  for (int j = 0; j < RY; ++j) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) q[j][k] = ldu(zs + dz * (k - 4), yr[j], x);
-    front[j] = ldu(zs + 4 * dz, yr[j], x);
-    const uint32_t o = off(zs, yr[j], x);
-    ldpm(zs, j, pv[j], mm[j]);
-    if constexpr (EPI == EPI_CORR) {
-      es[j] = in[j] ? ld_stream<T, NT>(at(e.s, o)) : T(0);
-      eg[j] = in[j] ? *at(e.g, o) : T(0);
+    for (int p = 0; p < XV; ++p) {
+      const int xl = tx * VX - 4 + p * VX, xr = tx * VX + VX + p * VX;
+      lxl[j][p] = xl < 0 ? XH + r * 8 + xl + 4 : (r + 4) * TX + xl;
+      lxr[j][p] = xr >= TX ? XH + r * 8 + 4 + xr - TX : (r + 4) * TX + xr;
     }
   }
-  // halo of one plane into hy / hx
-  auto ldhalo = [&](int zz, T *hy, T *hx) {
+  // halo vectors of this thread: y-halo rows first, then the x halos
+  VOff ho[KH];
+  int lh[KH];
+  bool hon[KH];
 #pragma unroll
-    for (int k = 0; k < NHY; ++k) hy[k] = hyon[k] ? ldu(zz, hyg[k], x) : T(0);
-#pragma unroll
-    for (int k = 0; k < NHX; ++k) hx[k] = hxon[k] ? ldu(zz, y0 - 4 + hxr[k], x0 - 4 + hxc[k]) : T(0);
-  };
-  constexpr int HQ = EH ? 4 : 1;  // early halo: planes z+1..z+4 queued, z+5 in flight
-  T hqy[HQ][NHY], hqx[HQ][NHX];
-  if constexpr (EH) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) ldhalo(zs + dz * d, hqy[d], hqx[d]);
-    ldhalo(zs + 4 * dz, hyv, hxv);
-  } else {
-    ldhalo(zs, hyv, hxv);
+  for (int k = 0; k < KH; ++k) {
+    const int t = tid + NTH * k;
+    hon[k] = t < NH;
+    if (t < NYH) {
+      const int hr = t / GX, row = hr < 4 ? hr : TY + hr;
+      ho[k] = vec_off<T, RAG>(a.ny, a.nx, y0 - 4 + row, x0 + (t % GX) * VX);
+      lh[k] = row * TX + (t % GX) * VX;
+    } else {
+      const int u = t - NYH, row = u / (2 * XV), p = u % (2 * XV);
+      const int xc = p < XV ? x0 - 4 + p * VX : x0 + TX + (p - XV) * VX;
+      ho[k] = hon[k] ? vec_off<T, RAG>(a.ny, a.nx, y0 + row, xc) : VOff();
+      lh[k] = XH + row * 8 + p * VX;
+    }
   }
 
-  for (int i = 0; i < nz_chunk; ++i) {
-    const int z = zs + dz * i;
-    T pvc[RY], mmc[RY], hyc[NHY], hxcv[NHX], esc[RY], egc[RY];
+  const int dz = rev ? -1 : 1;
+  const int zs = rev ? z1 - 1 : z0;
+  const int n = z1 - z0;
+  auto plane = [&](const T *f, int z) {
+    return plane_rsrc(f + (int64_t)z * sp, (z >= 0 && z < a.nz) ? pbytes : 0u);
+  };
+  V q[RY][9], front[RY], hv[KH], pv[RY], mv[RY], es[RY], eg[RY];
+  auto ldhalo = [&](__amdgpu_buffer_rsrc_t r, V *h) {
+#pragma unroll
+    for (int k = 0; k < KH; ++k)
+      if (KH == 1 || (k + 1) * NTH <= NH || hon[k]) h[k] = vload<T, false, RAG>(r, ho[k]);
+  };
+  auto sthalo = [&](T *L, const V *h) {
+#pragma unroll
+    for (int k = 0; k < KH; ++k)
+      if ((k + 1) * NTH <= NH || hon[k]) *reinterpret_cast<V *>(L + lh[k]) = h[k];
+  };
+  // operands of plane z that only its own cells need
+  auto ldcell = [&](int z) {
+    const __amdgpu_buffer_rsrc_t rp = plane(a.prev, z), rm = plane(a.m, z);
 #pragma unroll
     for (int j = 0; j < RY; ++j) {
-      q[j][8] = front[j];
+      pv[j] = vload<T, NT, RAG>(rp, own[j]);
+      mv[j] = vload<T, NT, RAG>(rm, own[j]);
+    }
+    if constexpr (EPI == EPI_CORR) {
+      const __amdgpu_buffer_rsrc_t rs = plane(e.s, z), rg = plane((const T *)e.g, z);
+#pragma unroll
+      for (int j = 0; j < RY; ++j) {
+        es[j] = vload<T, NT, RAG>(rs, own[j]);
+        eg[j] = vload<T, false, RAG>(rg, own[j]);
+      }
+    }
+  };
+  // the march's first nine planes; planes zs .. zs + 3 dz go to slots 0 .. 3
+  {
+    V h[4][KH];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const __amdgpu_buffer_rsrc_t r = plane(a.cur, zs + dz * (k - 4));
+#pragma unroll
+      for (int j = 0; j < RY; ++j) q[j][k] = vload<T, false, RAG>(r, own[j]);
+      if (k >= 4) ldhalo(r, h[k - 4]);
+    }
+    const __amdgpu_buffer_rsrc_t r = plane(a.cur, zs + 4 * dz);
+#pragma unroll
+    for (int j = 0; j < RY; ++j) front[j] = vload<T, false, RAG>(r, own[j]);
+    ldhalo(r, hv);
+    ldcell(zs);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+#pragma unroll
+      for (int j = 0; j < RY; ++j)
+        *reinterpret_cast<V *>(lds + d * PS + lown[j]) = q[j][4 + d];
+      sthalo(lds + d * PS, h[d]);
+    }
+  }
+
+  // plane i of the chunk (i mod 6 = S), queue entry k of it in q[.][S + k - 9 at
+  // most]: entries advance by one plane per step inside a trip of the loop
+  int z = zs;
+  auto step = [&](auto Sc, int i) {
+    constexpr int S = decltype(Sc)::value;
+    constexpr int W = (S + 4) % SLOTS;
+    V pvc[RY], mvc[RY], esc[RY], egc[RY];
+#pragma unroll
+    for (int j = 0; j < RY; ++j) {
+      q[j][(S + 8) % 9] = front[j];
+      *reinterpret_cast<V *>(lds + W * PS + lown[j]) = front[j];
       pvc[j] = pv[j];
-      mmc[j] = mm[j];
+      mvc[j] = mv[j];
       if constexpr (EPI == EPI_CORR) {
         esc[j] = es[j];
         egc[j] = eg[j];
       }
     }
-    if constexpr (EH) {
+    sthalo(lds + W * PS, hv);
+    if (i + 1 < n) {  // the next step's loads
+      const __amdgpu_buffer_rsrc_t r = plane(a.cur, z + 5 * dz);
 #pragma unroll
-      for (int k = 0; k < NHY; ++k) hyc[k] = hqy[0][k];
-#pragma unroll
-      for (int k = 0; k < NHX; ++k) hxcv[k] = hqx[0][k];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-#pragma unroll
-        for (int k = 0; k < NHY; ++k) hqy[d][k] = hqy[d + 1][k];
-#pragma unroll
-        for (int k = 0; k < NHX; ++k) hqx[d][k] = hqx[d + 1][k];
-      }
-#pragma unroll
-      for (int k = 0; k < NHY; ++k) hqy[3][k] = hyv[k];
-#pragma unroll
-      for (int k = 0; k < NHX; ++k) hqx[3][k] = hxv[k];
-    } else {
-#pragma unroll
-      for (int k = 0; k < NHY; ++k) hyc[k] = hyv[k];
-#pragma unroll
-      for (int k = 0; k < NHX; ++k) hxcv[k] = hxv[k];
+      for (int j = 0; j < RY; ++j) front[j] = vload<T, false, RAG>(r, own[j]);
+      ldhalo(r, hv);
+      ldcell(z + dz);
     }
-    // prefetch plane z + dz
-    if (i + 1 < nz_chunk) {
-#pragma unroll
-      for (int j = 0; j < RY; ++j) {
-        front[j] = ldu(z + 5 * dz, yr[j], x);
-        const uint32_t o = off(z + dz, yr[j], x);
-        ldpm(z + dz, j, pv[j], mm[j]);
-        if constexpr (EPI == EPI_CORR) {
-          es[j] = in[j] ? ld_stream<T, NT>(at(e.s, o)) : T(0);
-          eg[j] = in[j] ? *at(e.g, o) : T(0);
-        }
-      }
-      ldhalo(EH ? z + 5 * dz : z + dz, hyv, hxv);
-    }
-    T *L = lds[i & 1];
-#pragma unroll
-    for (int j = 0; j < RY; ++j) L[(ty + j * TYT + 4) * LX + tx + 4] = q[j][4];
-#pragma unroll
-    for (int k = 0; k < NHY; ++k)
-      if (hyon[k]) L[hyr[k] * LX + tx + 4] = hyc[k];
-#pragma unroll
-    for (int k = 0; k < NHX; ++k)
-      if (hxon[k]) L[hxr[k] * LX + hxc[k]] = hxcv[k];
     __syncthreads();
+    const T *L = lds + S * PS;
+    const int d = sponge_depth(z, a.nz, a.nb);
+    const T fz = T(d * d);
+    const __amdgpu_buffer_rsrc_t ro = plane(a.next, z);
 #pragma unroll
     for (int j = 0; j < RY; ++j) {
-      const int ly = ty + j * TYT + 4, lx = tx + 4;
-      const T *row = L + ly * LX + lx;
-      const T c = q[j][4];
-      const T lz = axis_sum(a, q[j][5], q[j][3], q[j][6], q[j][2], q[j][7], q[j][1], q[j][8],
-                            q[j][0]);
-      const T lyv = axis_sum(a, row[LX], row[-LX], row[2 * LX], row[-2 * LX], row[3 * LX],
-                             row[-3 * LX], row[4 * LX], row[-4 * LX]);
-      const T lxv = axis_sum(a, row[1], row[-1], row[2], row[-2], row[3], row[-3], row[4],
-                             row[-4]);
-      const T lap = ((a.cc * c + lz) + lyv) + lxv;
-      if (in[j]) {
-        const uint32_t o = off(z, yr[j], x);
-        const T nv = cell_update(a, c, pvc[j], mmc[j], lap, sponge_a(a, z, yr[j], x));
-        st_stream<T, NT>(at(a.next, o), nv);
-        if constexpr (EPI == EPI_D2)
-          st_stream<T, NT>(at(e.d2, o), (nv - T(2) * c + pvc[j]) * e.inv_dt2);
-        if constexpr (EPI == EPI_CORR) *at(e.g, o) = egc[j] - esc[j] * nv;
+      auto Q = [&](int k) -> const V & { return q[j][(S + k) % 9]; };
+      V yn[8];  // rows -4 .. -1, 1 .. 4
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        yn[k] = *reinterpret_cast<const V *>(L + lown[j] + (k - 4) * TX);
+        yn[4 + k] = *reinterpret_cast<const V *>(L + lown[j] + (k + 1) * TX);
+      }
+      T w[8 + VX];  // x - 4 .. x + VX + 3
+#pragma unroll
+      for (int p = 0; p < XV; ++p) {
+        const V l = *reinterpret_cast<const V *>(L + lxl[j][p]);
+        const V r = *reinterpret_cast<const V *>(L + lxr[j][p]);
+#pragma unroll
+        for (int c = 0; c < VX; ++c) {
+          w[p * VX + c] = l[c];
+          w[4 + VX + p * VX + c] = r[c];
+        }
       }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) q[j][k] = q[j][k + 1];
+      for (int c = 0; c < VX; ++c) w[4 + c] = Q(4)[c];
+      V out, d2;
+#pragma unroll
+      for (int c = 0; c < VX; ++c) {
+        const T u = Q(4)[c];
+        const T lz = axis_sum(a, Q(5)[c], Q(3)[c], Q(6)[c], Q(2)[c], Q(7)[c], Q(1)[c], Q(8)[c],
+                              Q(0)[c]);
+        const T ly = axis_sum(a, yn[4][c], yn[3][c], yn[5][c], yn[2][c], yn[6][c], yn[1][c],
+                              yn[7][c], yn[0][c]);
+        const T lx = axis_sum(a, w[c + 5], w[c + 3], w[c + 6], w[c + 2], w[c + 7], w[c + 1],
+                              w[c + 8], w[c]);
+        const T lap = (fma_t(a.cc, u, lz) + ly) + lx;
+        out[c] = cell_update(a, u, pvc[j][c], mvc[j][c], lap, sponge_mul(a.kd, fz + fyx[j][c]));
+        if constexpr (EPI == EPI_D2) d2[c] = (out[c] - T(2) * u + pvc[j][c]) * e.inv_dt2;
+        if constexpr (EPI == EPI_CORR) d2[c] = egc[j][c] - esc[j][c] * out[c];
+      }
+      vstore<T, NT, RAG>(ro, own[j], out);
+      if constexpr (EPI == EPI_D2) vstore<T, NT, RAG>(plane(e.d2, z), own[j], d2);
+      if constexpr (EPI == EPI_CORR) vstore<T, false, RAG>(plane(e.g, z), own[j], d2);
+    }
+    z += dz;
+  };
+  for (int i = 0; i < n;) {
+    step(std::integral_constant<int, 0>(), i);
+    if (++i == n) break;
+    step(std::integral_constant<int, 1>(), i);
+    if (++i == n) break;
+    step(std::integral_constant<int, 2>(), i);
+    if (++i == n) break;
+    step(std::integral_constant<int, 3>(), i);
+    if (++i == n) break;
+    step(std::integral_constant<int, 4>(), i);
+    if (++i == n) break;
+    step(std::integral_constant<int, 5>(), i);
+    ++i;
+    // a trip moved the queue by six entries: back to entry k in q[k]
+#pragma unroll
+    for (int j = 0; j < RY; ++j) {
+      V t[9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) t[k] = q[j][(6 + k) % 9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) q[j][k] = t[k];
     }
   }
 }
 
-template <typename T, int TX, int TYT, int RY, bool NT, int EPI = EPI_NONE, bool EH = false>
-__global__ __launch_bounds__(TX *TYT) void k_stencil3d_tiled(StepArgs<T> a, int ntx, int nty,
-                                                             int nzc, int zchunk,
-                                                             EpiArgs<T> e = EpiArgs<T>{},
-                                                             int rev = 0) {
+template <typename T, int TX, int TYT, int RY, bool NT, int EPI, bool RAG>
+__global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_tiled(StepArgs<T> a, int ntx,
+                                                                         int nty, int nzc,
+                                                                         int zchunk, EpiArgs<T> e,
+                                                                         int rev) {
   // XCD-aware order: consecutive hardware block ids go round-robin over the 8
   // XCDs; give each XCD a contiguous run of tiles so halo re-reads hit its L2.
   const int nblk = ntx * nty * nzc;
@@ -339,18 +436,18 @@ __global__ __launch_bounds__(TX *TYT) void k_stencil3d_tiled(StepArgs<T> a, int 
   b = xcd_block(b, nblk);
   const int bx = b % ntx;
   const int by = (b / ntx) % nty;
-  const int bz = b / (ntx * nty);
+  const int bz = rev ? nzc - 1 - b / (ntx * nty) : b / (ntx * nty);
   const int z0 = bz * zchunk;
-  tiled_body<T, TX, TYT, RY, NT, EPI, EH>(a, bx, by, z0, min(z0 + zchunk, a.nz), e, rev != 0);
+  tiled_body<T, TX, TYT, RY, NT, EPI, RAG>(a, bx, by, z0, min(z0 + zchunk, a.nz), e, rev != 0);
 }
 
 // Several shots (independent grids, one ring each) in one launch: entry e of
 // the tile table names the shot and the tile; the shot's step arguments come
 // from a device table (level pointers rebuilt from the step index s).
-template <typename T, int TX, int TYT, int RY, bool NT, bool EH = false>
-__global__ __launch_bounds__(TX *TYT) void k_stencil3d_batched(const ShotStep<T> *__restrict__ shots,
-                                                               const int4 *__restrict__ tiles,
-                                                               int ntiles, int s, int rev) {
+template <typename T, int TX, int TYT, int RY, bool NT, bool RAG>
+__global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_batched(
+    const ShotStep<T> *__restrict__ shots, const int4 *__restrict__ tiles, int ntiles, int s,
+    int rev) {
   int b = blockIdx.x;
   b = xcd_block(b, ntiles);
   const int4 t = tiles[b];  // (shot, bx | by << 16, z0, z1)
@@ -359,68 +456,127 @@ __global__ __launch_bounds__(TX *TYT) void k_stencil3d_batched(const ShotStep<T>
   a.cur = sh.ring + (int64_t)(((s + 1) % sh.R)) * sh.ld;
   a.prev = sh.ring + (int64_t)(((s + sh.R) % sh.R)) * sh.ld;
   a.next = sh.ring + (int64_t)(((s + 2) % sh.R)) * sh.ld;
-  tiled_body<T, TX, TYT, RY, NT, EPI_NONE, EH>(a, t.y & 0xffff, t.y >> 16, t.z, t.w,
-                                              EpiArgs<T>{}, rev != 0);
+  tiled_body<T, TX, TYT, RY, NT, EPI_NONE, RAG>(a, t.y & 0xffff, t.y >> 16, t.z, t.w,
+                                               EpiArgs<T>{}, rev != 0);
 }
 
-template <typename T, int TX, int TYT, int RY, bool NT, int EPI = EPI_NONE, bool EH = false>
-static void launch_tiled(const StepArgs<T> &a, int target_blocks, hipStream_t st,
+template <typename T, int TX, int TYT, int RY, bool NT, int EPI = EPI_NONE>
+static void launch_tiled(const StepArgs<T> &a, int nzc, hipStream_t st,
                          const EpiArgs<T> &e = EpiArgs<T>{}, int rev = 0) {
   constexpr int TY = TYT * RY;
+  constexpr int NTH = TX / V16<T>::n * TYT;
   const int ntx = (a.nx + TX - 1) / TX;
   const int nty = (a.ny + TY - 1) / TY;
-  // split z so that the launch has at least target_blocks workgroups of 256
-  // threads' worth (fewer, larger workgroups for the 512 / 1024 thread shapes)
-  const int64_t want = (int64_t)target_blocks * 256 / (TX * TYT);
-  const int64_t tiles = (int64_t)ntx * nty;
-  int nzc = (int)std::min<int64_t>((want + tiles - 1) / tiles, std::max(1, a.nz / 16));
-  if (nzc < 1) nzc = 1;
-  const int zchunk = (a.nz + nzc - 1) / nzc;  // chunks of at least 16 planes
+  const int zchunk = (a.nz + nzc - 1) / nzc;
   nzc = (a.nz + zchunk - 1) / zchunk;
-  hipLaunchKernelGGL((k_stencil3d_tiled<T, TX, TYT, RY, NT, EPI, EH>), dim3(ntx * nty * nzc),
-                     dim3(TX * TYT), 0, st, a, ntx, nty, nzc, zchunk, e, rev);
+  if (a.nx % V16<T>::n == 0)
+    hipLaunchKernelGGL((k_stencil3d_tiled<T, TX, TYT, RY, NT, EPI, false>), dim3(ntx * nty * nzc),
+                       dim3(NTH), 0, st, a, ntx, nty, nzc, zchunk, e, rev);
+  else
+    hipLaunchKernelGGL((k_stencil3d_tiled<T, TX, TYT, RY, NT, EPI, true>), dim3(ntx * nty * nzc),
+                       dim3(NTH), 0, st, a, ntx, nty, nzc, zchunk, e, rev);
 }
 
-// tiled variants: id -> (TX, threads in y, rows per thread, non-temporal)
-//   1: 64 x 16 (4 x 4)    2: 64 x 32 (4 x 8)    3: 64 x 16 (8 x 2, 512 thr)
-//   4: 64 x 16 (2 x 8, 128 thr)    5: 32 x 32 (8 x 4)    6: 128 x 8 (2 x 4)
-//   7: as 1, non-temporal          8: as 2, non-temporal
-//   9: 64 x 32 (8 x 4, 512 thr), non-temporal
-//  10: 64 x 32 (16 x 2, 1024 thr), non-temporal
-//  11: as 3, non-temporal
-//  12: as 7 and 13: as 9, with early halo loads
+// z chunks of a tile shape: the fewest (of at least `minp` planes) that give
+// `target` workgroups of 256 threads' worth
+static int z_split(int nz, int64_t tiles, int threads, int target, int minp) {
+  const int64_t want = (int64_t)target * 256 / threads;
+  return (int)std::max<int64_t>(
+      1, std::min<int64_t>((want + tiles - 1) / tiles, std::max(1, nz / minp)));
+}
+
+// tiled variants: id -> tile (x cells x y rows), threads
+//   1: 64 x 16, 256     2: 64 x 32, 512     3: 64 x 32, 256 (two rows each)
+//   4: 64 x 8, 128      5: 32 x 32, 256     6: 128 x 8, 256
+//   7 .. 12: as 1 .. 6, non-temporal         13: 32 x 16, 128
+// (FP64: half as many rows)
+struct TileShape {
+  int tx, ty, threads;
+};
+template <typename T>
+static TileShape tile_shape(int variant) {
+  static const TileShape k[6] = {{64, 16, 256}, {64, 32, 512}, {64, 32, 256},
+                                 {64, 8, 128},  {32, 32, 256}, {128, 8, 256}};
+  TileShape t = variant == 13 ? TileShape{32, 16, 128} : k[(variant - 1) % 6];
+  t.ty /= (int)sizeof(T) / 4;
+  return t;
+}
+
+// Automatic choice of the kernel and its z chunks (us per step, F32 unless
+// said; v: the variant).
+//   Grids below kSimpleCells run one thread per cell: the tiled kernel's nine
+//   plane loads and barriers are a longer chain than a step has work for
+//   (40 x 36 x 70: 4.3 against 6.2; 64^3: 5.8 both, FP64 6.1 against 5.8).
+//   While the four arrays of a step (16 N bytes) stay near the 256 MB
+//   memory-side cache, ordinary loads and short chunks (from four planes: a
+//   chunk re-reads eight, but they hit the caches) on 64 x 16 tiles:
+//   128^3: 8.8 with chunks of 4 planes, 14.3 of 16; 200^3: 26.9 against 38.3
+//   non-temporal; 300^3: 96 against 103.  FP64: 96 x 90 x 110 9.8, 128^3 13.4
+//   (one thread per cell 15.8 and 28); 300^3 166 non-temporal, 200 not.
+//   Beyond that the levels stream from HBM: non-temporal, 64 x 32 tiles.  If
+//   one or more whole chunks per column fill nearly all 256 CUs with one
+//   workgroup each, that is fastest (384 x 512 x 512: 2 chunks, 256
+//   workgroups, 261; 16-plane chunks 288), else chunks of 16 planes (320 x 448
+//   x 448: 173; 196 workgroups of 160 planes 181; v1 220).
+constexpr int64_t kSimpleCells = 200000;
+constexpr int64_t kStreamBytes = 640000000;
+template <typename T>
+static int auto_variant(const StepArgs<T> &a, int *nzc) {
+  if (a.N < kSimpleCells) return kStencilSimple;
+  const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
+  const int v = stream ? 8 : 1;
+  const TileShape t = tile_shape<T>(v);
+  const int64_t tiles = (int64_t)((a.nx + t.tx - 1) / t.tx) * ((a.ny + t.ty - 1) / t.ty);
+  if (!stream) {
+    *nzc = z_split(a.nz, tiles, t.threads, kAutoBlocks, 4);
+  } else {
+    const int c = (int)std::min<int64_t>(256 / tiles, a.nz / 16);
+    *nzc = c >= 1 && c * tiles >= 230 ? c : std::max(1, a.nz / 16);
+  }
+  return v;
+}
+
 template <typename T>
 hipError_t launch_stencil(int ndim, const StepArgs<T> &a, int variant, int target_blocks,
                           hipStream_t st, int rev) {
+  constexpr int F = sizeof(T) / 4;
   const EpiArgs<T> e{};
-  // the tiled kernels address a level with 32-bit byte offsets
-  const bool fits = a.N * (int64_t)sizeof(T) < (int64_t(1) << 32);
-  if (ndim == 3 && fits && variant >= kStencilTiled && variant <= kStencilVariants) {
-    if constexpr (sizeof(T) == 4) {
-      switch (variant) {
-        case 2: launch_tiled<T, 64, 4, 8, false>(a, target_blocks, st, e, rev); break;
-        case 3: launch_tiled<T, 64, 8, 2, false>(a, target_blocks, st, e, rev); break;
-        case 4: launch_tiled<T, 64, 2, 8, false>(a, target_blocks, st, e, rev); break;
-        case 5: launch_tiled<T, 32, 8, 4, false>(a, target_blocks, st, e, rev); break;
-        case 6: launch_tiled<T, 128, 2, 4, false>(a, target_blocks, st, e, rev); break;
-        case 7: launch_tiled<T, 64, 4, 4, true>(a, target_blocks, st, e, rev); break;
-        case 8: launch_tiled<T, 64, 4, 8, true>(a, target_blocks, st, e, rev); break;
-        case 9: launch_tiled<T, 64, 8, 4, true>(a, target_blocks, st, e, rev); break;
-        case 10: launch_tiled<T, 64, 16, 2, true>(a, target_blocks, st, e, rev); break;
-        case 11: launch_tiled<T, 64, 8, 2, true>(a, target_blocks, st, e, rev); break;
-        case 12: launch_tiled<T, 64, 4, 4, true, EPI_NONE, true>(a, target_blocks, st, e, rev); break;
-        case 13: launch_tiled<T, 64, 8, 4, true, EPI_NONE, true>(a, target_blocks, st, e, rev); break;
-        default: launch_tiled<T, 64, 4, 4, false>(a, target_blocks, st, e, rev); break;
-      }
-    } else {
-      launch_tiled<T, 64, 4, 4, false>(a, target_blocks, st, e, rev);
+  // a plane is addressed with 32-bit byte offsets below kOff
+  const bool fits = (int64_t)a.ny * a.nx * (int64_t)sizeof(T) < (int64_t)kOff;
+  int nzc = 1;
+  const bool rule = variant < 0;
+  if (ndim != 3 || !fits) {
+    variant = kStencilSimple;
+  } else if (rule) {
+    variant = auto_variant(a, &nzc);
+  }
+  if (variant != kStencilSimple && (!rule || target_blocks != kAutoBlocks)) {
+    const TileShape t = tile_shape<T>(variant);
+    nzc = z_split(a.nz, (int64_t)((a.nx + t.tx - 1) / t.tx) * ((a.ny + t.ty - 1) / t.ty),
+                  t.threads, target_blocks, 4);
+  }
+  switch (variant) {
+    case kStencilSimple: {
+      const unsigned nblk = (unsigned)((a.N + 255) / 256);
+      if (ndim == 3)
+        hipLaunchKernelGGL((k_stencil_simple<T, 3>), dim3(nblk), dim3(256), 0, st, a);
+      else
+        hipLaunchKernelGGL((k_stencil_simple<T, 2>), dim3(nblk), dim3(256), 0, st, a);
+      break;
     }
-  } else {
-    const unsigned nblk = (unsigned)((a.N + 255) / 256);
-    if (ndim == 3)
-      hipLaunchKernelGGL((k_stencil_simple<T, 3>), dim3(nblk), dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_stencil_simple<T, 2>), dim3(nblk), dim3(256), 0, st, a);
+    case 2: launch_tiled<T, 64, 32 / F, 1, false>(a, nzc, st, e, rev); break;
+    case 3: launch_tiled<T, 64, 16 / F, 2, false>(a, nzc, st, e, rev); break;
+    case 4: launch_tiled<T, 64, 8 / F, 1, false>(a, nzc, st, e, rev); break;
+    case 5: launch_tiled<T, 32, 32 / F, 1, false>(a, nzc, st, e, rev); break;
+    case 6: launch_tiled<T, 128, 8 / F, 1, false>(a, nzc, st, e, rev); break;
+    case 7: launch_tiled<T, 64, 16 / F, 1, true>(a, nzc, st, e, rev); break;
+    case 8: launch_tiled<T, 64, 32 / F, 1, true>(a, nzc, st, e, rev); break;
+    case 9: launch_tiled<T, 64, 16 / F, 2, true>(a, nzc, st, e, rev); break;
+    case 10: launch_tiled<T, 64, 8 / F, 1, true>(a, nzc, st, e, rev); break;
+    case 11: launch_tiled<T, 32, 32 / F, 1, true>(a, nzc, st, e, rev); break;
+    case 12: launch_tiled<T, 128, 8 / F, 1, true>(a, nzc, st, e, rev); break;
+    case 13: launch_tiled<T, 32, 16 / F, 1, false>(a, nzc, st, e, rev); break;
+    default: launch_tiled<T, 64, 16 / F, 1, false>(a, nzc, st, e, rev); break;
   }
   return hipGetLastError();
 }
@@ -429,24 +585,27 @@ template hipError_t launch_stencil<float>(int, const StepArgs<float> &, int, int
 template hipError_t launch_stencil<double>(int, const StepArgs<double> &, int, int, hipStream_t,
                                            int);
 
-// Stencil step with an exact-comparator epilogue (3D F32, tiled variants 1
-// and 7; other variants use variant 7).  Returns hipErrorInvalidValue for
+// Stencil step with an exact-comparator epilogue (3D F32, 64 x 16 tiles with
+// the z split of the plain step's rule).  Returns hipErrorInvalidValue for
 // grids the tiled kernel does not serve, so the caller falls back to the
 // separate kernels.
 template <typename T>
 hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, int variant, int target_blocks,
                               int epi, const EpiArgs<T> &e, hipStream_t st, int rev) {
-  if (ndim != 3 || sizeof(T) != 4 || variant < kStencilTiled ||
-      a.N * (int64_t)sizeof(T) >= (int64_t(1) << 32))
+  if (ndim != 3 || sizeof(T) != 4 || variant == kStencilSimple ||
+      (int64_t)a.ny * a.nx * (int64_t)sizeof(T) >= (int64_t)kOff)
     return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 4) {
-    const bool nt = variant != 1;
+    const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
+    const bool nt = variant < 0 ? stream : variant >= 7 && variant <= 12;
+    const int64_t tiles = (int64_t)((a.nx + 63) / 64) * ((a.ny + 15) / 16);
+    const int nzc = z_split(a.nz, tiles, 256, target_blocks, stream ? 16 : 4);
     if (epi == EPI_D2) {
-      if (nt) launch_tiled<T, 64, 4, 4, true, EPI_D2>(a, target_blocks, st, e, rev);
-      else launch_tiled<T, 64, 4, 4, false, EPI_D2>(a, target_blocks, st, e, rev);
+      if (nt) launch_tiled<T, 64, 16, 1, true, EPI_D2>(a, nzc, st, e, rev);
+      else launch_tiled<T, 64, 16, 1, false, EPI_D2>(a, nzc, st, e, rev);
     } else if (epi == EPI_CORR) {
-      if (nt) launch_tiled<T, 64, 4, 4, true, EPI_CORR>(a, target_blocks, st, e, rev);
-      else launch_tiled<T, 64, 4, 4, false, EPI_CORR>(a, target_blocks, st, e, rev);
+      if (nt) launch_tiled<T, 64, 16, 1, true, EPI_CORR>(a, nzc, st, e, rev);
+      else launch_tiled<T, 64, 16, 1, false, EPI_CORR>(a, nzc, st, e, rev);
     } else {
       return hipErrorInvalidValue;
     }
@@ -591,37 +750,18 @@ hipError_t launch_sample(const PointTables<T> &pt, const T *field, T *out, hipSt
 // ---------------------------------------------------------------------------
 template <typename T>
 hipError_t launch_stencil_batched(const ShotStep<T> *shots, const int4 *tiles, int ntiles, int s,
-                                  int variant, hipStream_t st, int rev) {
+                                  int variant, bool ragged, hipStream_t st, int rev) {
   if (ntiles <= 0) return hipSuccess;
-  if constexpr (sizeof(T) == 4) {
-    switch (variant) {
-      case 3:
-        hipLaunchKernelGGL((k_stencil3d_batched<T, 64, 8, 2, false>), dim3(ntiles), dim3(512), 0,
-                           st, shots, tiles, ntiles, s, rev);
-        break;
-      case 11:
-        hipLaunchKernelGGL((k_stencil3d_batched<T, 64, 8, 2, true>), dim3(ntiles), dim3(512), 0,
-                           st, shots, tiles, ntiles, s, rev);
-        break;
-      case 12:
-      case 13:
-        hipLaunchKernelGGL((k_stencil3d_batched<T, 64, 4, 4, true, true>), dim3(ntiles),
-                           dim3(256), 0, st, shots, tiles, ntiles, s, rev);
-        break;
-      case 7:
-      case 8:
-      case 9:
-      case 10:  // 64 x 32 variants run the 64 x 16 tile table with the variant 7 kernel
-        hipLaunchKernelGGL((k_stencil3d_batched<T, 64, 4, 4, true>), dim3(ntiles), dim3(256), 0,
-                           st, shots, tiles, ntiles, s, rev);
-        break;
-      default:
-        hipLaunchKernelGGL((k_stencil3d_batched<T, 64, 4, 4, false>), dim3(ntiles), dim3(256), 0,
-                           st, shots, tiles, ntiles, s, rev);
-    }
+  const bool nt = variant >= 7 && variant <= 12;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(ntiles), dim3(256), 0, st, shots, tiles, ntiles, s, rev);
+  };
+  if (ragged) {
+    if (nt) go(k_stencil3d_batched<T, 64, 16, 1, true, true>);
+    else go(k_stencil3d_batched<T, 64, 16, 1, false, true>);
   } else {
-    hipLaunchKernelGGL((k_stencil3d_batched<T, 64, 4, 4, false>), dim3(ntiles), dim3(256), 0, st,
-                       shots, tiles, ntiles, s, rev);
+    if (nt) go(k_stencil3d_batched<T, 64, 16, 1, true, false>);
+    else go(k_stencil3d_batched<T, 64, 16, 1, false, false>);
   }
   return hipGetLastError();
 }
@@ -683,7 +823,7 @@ hipError_t launch_sample_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
   return hipGetLastError();
 }
 template hipError_t launch_stencil_batched<float>(const ShotStep<float> *, const int4 *, int, int,
-                                                  int, hipStream_t, int);
+                                                  int, bool, hipStream_t, int);
 template hipError_t launch_inject_batched<float>(const ShotStep<float> *, const ShotIO<float> *,
                                                  const BatchPoints<float> &, int, int,
                                                  hipStream_t);

@@ -22,4 +22,13 @@ __device__ __forceinline__ T sponge_a(const StepArgs<T> &a, int z, int y, int x)
   return a.kd * T(dz * dz + dy * dy + dx * dx);
 }
 
+// kd * d2 as a rounded product: the step kernels add it to and subtract it
+// from m, and a contraction into those sums would round differently from the
+// kernels that form it in sponge_a
+template <typename T>
+__device__ __forceinline__ T sponge_mul(T kd, T d2) {
+#pragma clang fp contract(off)
+  return kd * d2;
+}
+
 }  // namespace rtm
