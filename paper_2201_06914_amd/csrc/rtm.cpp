@@ -114,10 +114,6 @@ struct Region {
   size_t off = 0, bytes = 0;
 };
 
-struct PointRegion {  // device layout of one point set's tables
-  Region soff, sidx, sw, icell, ioff, ipt, iw;
-  int32_t cap = 0;  // points
-};
 
 struct rtm_plan {
   rtm_desc d;
@@ -127,8 +123,8 @@ struct rtm_plan {
   size_t esz = 0;
   Region ring, red, status;  // status: the non-finite watch word (uint32)
   Region queue;              // work-queue counter of the probe launches (int32)
-  PointRegion src, rec;
-  size_t tab_off = 0, tab_bytes = 0;
+  size_t smap = 0, rmap = 0;           // capacities of the folded injections' maps (ints)
+  size_t tab_off = 0, tab_bytes = 0;   // point tables, packed by each call
   size_t total = 0;
 };
 
@@ -148,16 +144,21 @@ static void place(size_t &cur, Region &r, size_t bytes) {
   cur = align256(cur + bytes);
 }
 
-static void place_points(size_t &cur, PointRegion &pr, int32_t n, size_t esz) {
+// Ints set aside for the map of a point set's folded injection: a dense plane
+// of points needs one per point, between grid points two to four, and a spread
+// with every seventh point about fourteen.  Sets over a larger box inject with
+// a launch of their own.
+static size_t map_cap(int32_t n, int64_t N) {
+  return n > 0 ? (size_t)std::min<int64_t>((int64_t)16 * n + 64, N) : 0;
+}
+
+// bytes one point set's tables take at most (`per_point` more per point)
+static size_t point_bytes(int32_t n, size_t esz, size_t map_ints, size_t per_point = 0,
+                          size_t per_cell = 0) {
   const size_t c = (size_t)8 * n;  // at most 8 corners per point
-  pr.cap = n;
-  place(cur, pr.soff, 4 * ((size_t)n + 1));
-  place(cur, pr.sidx, 4 * c);
-  place(cur, pr.sw, esz * c);
-  place(cur, pr.icell, 4 * c);
-  place(cur, pr.ioff, 4 * (c + 1));
-  place(cur, pr.ipt, 4 * c);
-  place(cur, pr.iw, esz * c);
+  return align256(4 * ((size_t)n + 1)) + 3 * align256(4 * c) + align256(4 * (c + 1)) +
+         2 * align256(esz * c) + align256(4 * map_ints) + 2 * align256(per_point * (size_t)n) +
+         align256(per_cell * c);
 }
 
 extern "C" double rtm_cfl_bound(int32_t ndim) {
@@ -296,16 +297,23 @@ extern "C" rtm_status rtm_plan_create(const rtm_desc *desc, rtm_plan **out) {
   p->Npad = (N + 31) / 32 * 32;
   p->R = d.k_block + 2;
   p->esz = d.field_dtype == RTM_F64 ? 8 : 4;
-  size_t cur = 0;
-  place(cur, p->ring, (size_t)p->R * p->ld * p->esz);
-  place(cur, p->red, sizeof(double) * (kReduceBlocks + 8));
-  place(cur, p->status, sizeof(uint32_t));
-  place(cur, p->queue, sizeof(int32_t));
-  p->tab_off = cur;
-  place_points(cur, p->src, d.nsrc, p->esz);
-  place_points(cur, p->rec, d.nrec, p->esz);
-  p->tab_bytes = cur - p->tab_off;
-  p->total = cur;
+  auto layout = [&](bool maps) {
+    size_t cur = 0;
+    place(cur, p->ring, (size_t)p->R * p->ld * p->esz);
+    place(cur, p->red, sizeof(double) * (kReduceBlocks + 8));
+    place(cur, p->status, sizeof(uint32_t));
+    place(cur, p->queue, sizeof(int32_t));
+    p->tab_off = cur;
+    p->smap = maps ? map_cap(d.nsrc, N) : 0;
+    p->rmap = maps ? map_cap(d.nrec, N) : 0;
+    p->tab_bytes = point_bytes(d.nsrc, p->esz, p->smap) + point_bytes(d.nrec, p->esz, p->rmap);
+    p->total = cur + p->tab_bytes;
+  };
+  layout(false);
+  const size_t bare = p->total;
+  layout(true);
+  // a plan that fits fwi_gradient_noalloc's array without the maps goes without
+  if (bare <= RTM_NOALLOC_SCRATCH_BYTES && p->total > RTM_NOALLOC_SCRATCH_BYTES) layout(false);
   *out = p;
   return RTM_OK;
 }
@@ -321,37 +329,45 @@ extern "C" rtm_status rtm_plan_workspace_bytes(const rtm_plan *p, size_t *bytes)
 // ---------------------------------------------------------------------------
 // point tables
 // ---------------------------------------------------------------------------
+// Tables of one or several point sets in host memory (T: the field type).
+template <typename T>
 struct HostPoints {
-  std::vector<int32_t> soff, sidx, icell, ioff, ipt;
-  std::vector<double> sw, iw;
+  std::vector<int32_t> soff{0}, sidx, icell, ioff{0}, ipt;
+  std::vector<T> sw, iw;
+  // of the set added last: its first distinct cell, its cells' bounding box (half open)
+  size_t c0 = 0;
+  int64_t lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
 };
 
-// Multilinear weights of each point; injection entries grouped by cell
-// (points in increasing order within a cell) so that the injection kernel
-// sums a cell's contributions in a fixed order without atomics.
-static rtm_status build_points(const rtm_plan *P, int32_t n, const double *pos, HostPoints &hp) {
+// Adds a point set: multilinear weights of each point; injection entries
+// grouped by cell (points in increasing order within a cell) so that the
+// injection sums a cell's contributions in a fixed order without atomics.
+template <typename T>
+static rtm_status add_points(const rtm_plan *P, int32_t n, const double *pos, HostPoints<T> &hp) {
   const rtm_desc &d = P->d;
   const int64_t dims[3] = {d.nz, d.ny, d.nx};
-  struct Entry {
-    int32_t cell, pt;
-    double w;
-  };
-  std::vector<Entry> ent;
-  ent.reserve((size_t)n * 8);
-  hp.soff.assign(1, 0);
+  hp.c0 = hp.icell.size();
+  const size_t e0 = hp.sidx.size();
+  hp.soff.reserve(hp.soff.size() + n);
+  hp.sidx.reserve(e0 + n);
+  hp.sw.reserve(e0 + n);
+  std::vector<int32_t> pt;  // the point of each entry
+  pt.reserve(n);
+  bool sorted = true;
   for (int32_t p = 0; p < n; ++p) {
     int64_t base[3];
     double frac[3];
     int ncor[3];
     for (int a = 0; a < 3; ++a) {
-      double v = (a == 1 && d.ndim == 2) ? 0.0 : pos[3 * (size_t)p + a];
+      const double v = (a == 1 && d.ndim == 2) ? 0.0 : pos[3 * (size_t)p + a];
       if (!(v >= 0.0 && v <= (double)(dims[a] - 1)))
         return fail(RTM_E_POINTS, "point %d axis %d at %g is outside [0, %lld]", p, a, v,
                     (long long)(dims[a] - 1));
-      const double f = std::floor(v);
-      base[a] = (int64_t)f;
-      frac[a] = v - f;
+      base[a] = (int64_t)v;  // v >= 0: the floor
+      frac[a] = v - (double)base[a];
       ncor[a] = frac[a] > 0.0 ? 2 : 1;
+      hp.lo[a] = p ? std::min(hp.lo[a], base[a]) : base[a];
+      hp.hi[a] = p ? std::max(hp.hi[a], base[a] + ncor[a]) : base[a] + ncor[a];
     }
     for (int iz = 0; iz < ncor[0]; ++iz)
       for (int iy = 0; iy < ncor[1]; ++iy)
@@ -359,58 +375,107 @@ static rtm_status build_points(const rtm_plan *P, int32_t n, const double *pos, 
           const double w = (iz ? frac[0] : 1.0 - frac[0]) * (iy ? frac[1] : 1.0 - frac[1]) *
                            (ix ? frac[2] : 1.0 - frac[2]);
           const int64_t cell = ((base[0] + iz) * d.ny + (base[1] + iy)) * d.nx + (base[2] + ix);
+          sorted = sorted && (pt.empty() || hp.sidx.back() <= (int32_t)cell);
           hp.sidx.push_back((int32_t)cell);
-          hp.sw.push_back(w);
-          ent.push_back({(int32_t)cell, p, w});
+          hp.sw.push_back((T)w);
+          pt.push_back(p);
         }
     hp.soff.push_back((int32_t)hp.sidx.size());
   }
-  std::stable_sort(ent.begin(), ent.end(),
-                   [](const Entry &a, const Entry &b) { return a.cell < b.cell; });
-  hp.ioff.assign(1, 0);
-  for (size_t e = 0; e < ent.size(); ++e) {
-    if (e == 0 || ent[e].cell != ent[e - 1].cell) {
-      if (e) hp.ioff.push_back((int32_t)e);
-      hp.icell.push_back(ent[e].cell);
-    }
-    hp.ipt.push_back(ent[e].pt);
-    hp.iw.push_back(ent[e].w);
+  // entries by cell, then by point: (cell, entry) keys, in order already for
+  // points along the grid's rows
+  const size_t ne = pt.size();
+  std::vector<uint64_t> order(sorted ? 0 : ne);
+  if (!sorted) {
+    for (size_t e = 0; e < ne; ++e)
+      order[e] = (uint64_t)(uint32_t)hp.sidx[e0 + e] << 32 | (uint64_t)e;
+    std::sort(order.begin(), order.end());
   }
-  hp.ioff.push_back((int32_t)ent.size());
-  if (ent.empty()) hp.ioff.assign(1, 0);
+  hp.icell.reserve(hp.icell.size() + ne);
+  hp.ioff.reserve(hp.ioff.size() + ne);
+  hp.ipt.reserve(hp.ipt.size() + ne);
+  hp.iw.reserve(hp.iw.size() + ne);
+  for (size_t k = 0; k < ne; ++k) {
+    const size_t e = sorted ? k : (size_t)(order[k] & 0xffffffffu);
+    const int32_t cell = hp.sidx[e0 + e];
+    if (k == 0 || cell != hp.icell.back()) {
+      if (k) hp.ioff.push_back((int32_t)hp.ipt.size());
+      hp.icell.push_back(cell);
+    }
+    hp.ipt.push_back(pt[e]);
+    hp.iw.push_back(hp.sw[e0 + e]);
+  }
+  if (ne) hp.ioff.push_back((int32_t)hp.ipt.size());
   return RTM_OK;
 }
 
+// The map of the folded injection (InjMap) of the set added last, if its
+// cells' bounding box has at most `cap` cells.
 template <typename T>
-static void stage_points(const rtm_plan *P, const PointRegion &pr, const HostPoints &hp,
-                         std::vector<unsigned char> &host) {
-  auto put = [&](const Region &r, const void *src, size_t bytes) {
-    if (bytes) std::memcpy(host.data() + (r.off - P->tab_off), src, bytes);
-  };
-  put(pr.soff, hp.soff.data(), 4 * hp.soff.size());
-  put(pr.sidx, hp.sidx.data(), 4 * hp.sidx.size());
-  std::vector<T> sw(hp.sw.begin(), hp.sw.end()), iw(hp.iw.begin(), hp.iw.end());
-  put(pr.sw, sw.data(), sizeof(T) * sw.size());
-  put(pr.icell, hp.icell.data(), 4 * hp.icell.size());
-  put(pr.ioff, hp.ioff.data(), 4 * hp.ioff.size());
-  put(pr.ipt, hp.ipt.data(), 4 * hp.ipt.size());
-  put(pr.iw, iw.data(), sizeof(T) * iw.size());
+static bool make_map(const rtm_plan *P, const HostPoints<T> &hp, size_t cap,
+                     std::vector<int32_t> &map, InjMap<T> *j) {
+  if (hp.icell.size() == hp.c0) return false;
+  const int64_t by = hp.hi[1] - hp.lo[1], bx = hp.hi[2] - hp.lo[2];
+  const int64_t vol = (hp.hi[0] - hp.lo[0]) * by * bx;
+  if (vol > (int64_t)cap) return false;
+  map.assign((size_t)vol, -1);
+  const uint32_t nx = (uint32_t)P->d.nx, ny = (uint32_t)P->d.ny;
+  for (size_t c = hp.c0; c < hp.icell.size(); ++c) {
+    const uint32_t i = (uint32_t)hp.icell[c], zy = i / nx, x = i - zy * nx, z = zy / ny,
+                   y = zy - z * ny;
+    const int32_t e = hp.ioff[c];
+    const bool one = hp.ioff[c + 1] == e + 1 && hp.iw[e] == T(1);
+    map[(size_t)((((int64_t)z - hp.lo[0]) * by + ((int64_t)y - hp.lo[1])) * bx + x - hp.lo[2])] =
+        one ? hp.ipt[e] : -2 - (int32_t)c;
+  }
+  j->z0 = (int)hp.lo[0];
+  j->z1 = (int)hp.hi[0];
+  j->y0 = (int)hp.lo[1];
+  j->y1 = (int)hp.hi[1];
+  j->x0 = (int)hp.lo[2];
+  j->x1 = (int)hp.hi[2];
+  return true;
 }
 
+// Packs tables for one upload: only what a call uses travels (the layout is
+// the call's own, within the bytes that the plan set aside).
+struct Pack {
+  std::vector<unsigned char> host;
+  char *dev;  // where the packed bytes go
+  explicit Pack(char *d) : dev(d) {}
+  template <typename T>
+  const T *put(const std::vector<T> &v) {
+    const size_t at = host.size();
+    host.resize(align256(at + sizeof(T) * v.size()));
+    if (!v.empty()) std::memcpy(host.data() + at, v.data(), sizeof(T) * v.size());
+    return reinterpret_cast<const T *>(dev + at);
+  }
+};
+
 template <typename T>
-static PointTables<T> device_points(const PointRegion &pr, char *work, int32_t npts,
-                                    int32_t ncell) {
-  PointTables<T> t;
-  t.soff = reinterpret_cast<const int32_t *>(work + pr.soff.off);
-  t.sidx = reinterpret_cast<const int32_t *>(work + pr.sidx.off);
-  t.sw = reinterpret_cast<const T *>(work + pr.sw.off);
-  t.icell = reinterpret_cast<const int32_t *>(work + pr.icell.off);
-  t.ioff = reinterpret_cast<const int32_t *>(work + pr.ioff.off);
-  t.ipt = reinterpret_cast<const int32_t *>(work + pr.ipt.off);
-  t.iw = reinterpret_cast<const T *>(work + pr.iw.off);
-  t.npts = npts;
-  t.ncell = ncell;
-  return t;
+static rtm_status pack_points(const rtm_plan *P, int32_t n, const double *pos, size_t map_cap_,
+                              Pack &pk, PointTables<T> *t) {
+  HostPoints<T> hp;
+  rtm_status s = add_points(P, n, pos, hp);
+  if (s) return s;
+  std::vector<int32_t> map;
+  const bool fold = make_map(P, hp, map_cap_, map, &t->inj);
+  t->soff = pk.put(hp.soff);
+  t->sidx = pk.put(hp.sidx);
+  t->sw = pk.put(hp.sw);
+  t->icell = pk.put(hp.icell);
+  t->ioff = pk.put(hp.ioff);
+  t->ipt = pk.put(hp.ipt);
+  t->iw = pk.put(hp.iw);
+  t->npts = n;
+  t->ncell = (int32_t)hp.icell.size();
+  if (fold) {
+    t->inj.map = pk.put(map);
+    t->inj.ioff = t->ioff;
+    t->inj.ipt = t->ipt;
+    t->inj.iw = t->iw;
+  }
+  return RTM_OK;
 }
 
 static uint32_t *status_word(const rtm_plan *P, char *work) {
@@ -425,23 +490,15 @@ template <typename T>
 static rtm_status upload_points(const rtm_plan *P, char *work, hipStream_t st,
                                 const double *src_pos, PointTables<T> *src_t,
                                 const double *rec_pos, PointTables<T> *rec_t) {
-  std::vector<unsigned char> host(P->tab_bytes, 0);
-  HostPoints hs, hr;
-  if (src_pos && src_t) {
-    rtm_status s = build_points(P, P->d.nsrc, src_pos, hs);
-    if (s) return s;
-    stage_points<T>(P, P->src, hs, host);
-    *src_t = device_points<T>(P->src, work, P->d.nsrc, (int32_t)hs.icell.size());
-  }
-  if (rec_pos && rec_t) {
-    rtm_status s = build_points(P, P->d.nrec, rec_pos, hr);
-    if (s) return s;
-    stage_points<T>(P, P->rec, hr, host);
-    *rec_t = device_points<T>(P->rec, work, P->d.nrec, (int32_t)hr.icell.size());
-  }
+  Pack pk(work + P->tab_off);
+  rtm_status s;
+  if (src_pos && src_t && (s = pack_points<T>(P, P->d.nsrc, src_pos, P->smap, pk, src_t))) return s;
+  if (rec_pos && rec_t && (s = pack_points<T>(P, P->d.nrec, rec_pos, P->rmap, pk, rec_t))) return s;
+  if (pk.host.size() > P->tab_bytes) return fail(RTM_E_WORKSPACE, "point tables do not fit");
   HIP_TRY(launch_status_clear(status_word(P, work), st));
-  if (P->tab_bytes) {
-    HIP_TRY(hipMemcpyAsync(work + P->tab_off, host.data(), P->tab_bytes, hipMemcpyHostToDevice, st));
+  if (!pk.host.empty()) {
+    HIP_TRY(hipMemcpyAsync(work + P->tab_off, pk.host.data(), pk.host.size(), hipMemcpyHostToDevice,
+                           st));
     HIP_TRY(hipStreamSynchronize(st));
   }
   return RTM_OK;
@@ -500,6 +557,15 @@ struct SweepIO {
   uint64_t sketch_seed = 0;
 };
 
+// the folded injection of time index n (no map: none)
+template <typename T>
+static InjMap<T> step_inj(const PointTables<T> &pt, const T *vals, int n) {
+  if (!pt.inj.map || !vals) return InjMap<T>();
+  InjMap<T> j = pt.inj;
+  j.vals = vals + (int64_t)n * pt.npts;
+  return j;
+}
+
 template <typename T>
 static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTables<T> &inj,
                             const PointTables<T> &smp, char *work, hipStream_t st) {
@@ -533,15 +599,19 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
     a.next = level(s + 1);
     TimedLaunch tl;
     prof_begin(KT_STENCIL, s, st, &tl);
-    HIP_TRY(launch_stencil<T>(ndim, a, variant, g_stencil_blocks, st,
+    HIP_TRY(launch_stencil<T>(ndim, a, step_inj(inj, inj_vals, n), variant, g_stencil_blocks, st,
                               g_stencil_alternate ? (s & 1) : 0));
     prof_end(st, &tl);
-    if (inj.ncell > 0 && inj_vals)
+    if (inj.ncell > 0 && inj_vals && !inj.inj.map)
       HIP_TRY(launch_inject<T>(a, inj, inj_vals + (int64_t)n * inj.npts, a.next, st));
-    if (smp_out && smp.npts > 0)
-      HIP_TRY(launch_sample<T>(smp, a.next, smp_out + (int64_t)n * smp.npts, st));
-    if ((bar || io.fuse_img || io.sketch_Y) &&
-        (s + 1 - s0 == d.k_block || s == d.nt - 1 || s == ne - 1)) {
+    const bool block_end = s + 1 - s0 == d.k_block || s == d.nt - 1 || s == ne - 1;
+    if (block_end && smp_out)
+      HIP_TRY(launch_sample_block<T>(smp, ring, nullptr, P->ld, P->R, s0, s + 1 - s0,
+                                     io.adjoint ? -1 : 1,
+                                     smp_out + (int64_t)(io.adjoint ? d.nt - 1 - s0 : s0) * smp.npts,
+                                     st));
+    if (block_end && !bar && !io.fuse_img && !io.sketch_Y) s0 = s + 1;
+    else if (block_end) {
       ProbeArgs<T> p{};
       p.ring = ring;
       p.ld = P->ld;
@@ -986,6 +1056,14 @@ static rtm_status gradient_impl(const rtm_plan *P, const void *m, const double *
   key = key_mix(key, (uint64_t)src_t.ncell * 4096 + (uint64_t)src_t.npts);
   key = key_mix(key, (uint64_t)rec_t.ncell * 4096 + (uint64_t)rec_t.npts);
   key = key_mix(key, (uint64_t)(scale * 1e6));
+  for (const PointTables<T> *t : {&src_t, &rec_t}) {  // the tables and the folded injection's box
+    const InjMap<T> &j = t->inj;
+    for (const void *p : {(const void *)t->soff, (const void *)t->sidx, (const void *)t->sw,
+                          (const void *)t->icell, (const void *)t->ioff, (const void *)t->ipt,
+                          (const void *)t->iw, (const void *)j.map})
+      key = key_mix(key, (uint64_t)(uintptr_t)p);
+    for (int v : {j.z0, j.z1, j.y0, j.y1, j.x0, j.x1}) key = key_mix(key, (uint64_t)(uint32_t)v);
+  }
   return run_launches(key, st, [&](hipStream_t ls) -> rtm_status {
     hipStream_t st = ls;  // the stream the launches go to (caller's, or the capture stream)
     rtm_status s;
@@ -1231,11 +1309,16 @@ static rtm_status exact_impl(const rtm_plan *P, const void *mv, const double *sr
     a.next = lvA(n + 1);
     TimedLaunch tl;
     prof_begin(KT_STENCIL, n, st, &tl);
-    HIP_TRY(launch_stencil<T>(ndim, a, variant, g_stencil_blocks, st,
+    HIP_TRY(launch_stencil<T>(ndim, a, step_inj(src_t, q, n), variant, g_stencil_blocks, st,
                               g_stencil_alternate ? (n & 1) : 0));
     prof_end(st, &tl);
-    if (src_t.ncell > 0) HIP_TRY(launch_inject<T>(a, src_t, q + (int64_t)n * src_t.npts, a.next, st));
-    if (rec_t.npts > 0) HIP_TRY(launch_sample<T>(rec_t, a.next, resid + (int64_t)n * rec_t.npts, st));
+    if (src_t.ncell > 0 && !src_t.inj.map)
+      HIP_TRY(launch_inject<T>(a, src_t, q + (int64_t)n * src_t.npts, a.next, st));
+    if ((n + 1) % d.k_block == 0 || n == nt - 1) {  // the block's levels are in ring A
+      const int n0 = n - n % d.k_block;
+      HIP_TRY(launch_sample_block<T>(rec_t, ringA, nullptr, ld, P->R, n0, n + 1 - n0, 1,
+                                     resid + (int64_t)n0 * rec_t.npts, st));
+    }
   }
   // 2. residual and misfit
   double *part = reinterpret_cast<double *>(w + P->red.off);
@@ -1263,15 +1346,16 @@ static rtm_status exact_impl(const rtm_plan *P, const void *mv, const double *sr
       e.d2 = S + (int64_t)(n - n_lo) * ld;
       e.inv_dt2 = inv_dt2;
       const int rf = g_stencil_alternate ? (n & 1) : 0;
-      if (fused && launch_stencil_epi<T>(ndim, fa, variant, g_stencil_blocks, EPI_D2, e, st, rf) ==
-                       hipSuccess) {
+      const InjMap<T> ij = step_inj(src_t, q, n);
+      if (fused && launch_stencil_epi<T>(ndim, fa, ij, variant, g_stencil_blocks, EPI_D2, e, st,
+                                         rf) == hipSuccess) {
         // u_tt written by the stencil's epilogue; the injection adds its share
-        if (src_t.ncell > 0)
+        if (src_t.ncell > 0 && !ij.map)
           HIP_TRY(launch_inject_epi<T>(fa, src_t, q + (int64_t)n * src_t.npts, fa.next, EPI_D2,
                                        e, st));
       } else {
-        HIP_TRY(launch_stencil<T>(ndim, fa, variant, g_stencil_blocks, st, rf));
-        if (src_t.ncell > 0)
+        HIP_TRY(launch_stencil<T>(ndim, fa, ij, variant, g_stencil_blocks, st, rf));
+        if (src_t.ncell > 0 && !ij.map)
           HIP_TRY(launch_inject<T>(fa, src_t, q + (int64_t)n * src_t.npts, fa.next, st));
         HIP_TRY(launch_second_diff<T>(fa.next, fa.cur, fa.prev, inv_dt2, N, e.d2, st));
       }
@@ -1285,14 +1369,15 @@ static rtm_status exact_impl(const rtm_plan *P, const void *mv, const double *sr
       e.s = S + (int64_t)(n - n_lo) * ld;
       e.g = grad;
       const int ra = g_stencil_alternate ? (sa & 1) : 0;
-      if (fused && launch_stencil_epi<T>(ndim, a, variant, g_stencil_blocks, EPI_CORR, e, st, ra) ==
-                       hipSuccess) {
-        if (rec_t.ncell > 0)
+      const InjMap<T> ij = step_inj(rec_t, (const T *)resid, n);
+      if (fused && launch_stencil_epi<T>(ndim, a, ij, variant, g_stencil_blocks, EPI_CORR, e, st,
+                                         ra) == hipSuccess) {
+        if (rec_t.ncell > 0 && !ij.map)
           HIP_TRY(launch_inject_epi<T>(a, rec_t, resid + (int64_t)n * rec_t.npts, a.next,
                                        EPI_CORR, e, st));
       } else {
-        HIP_TRY(launch_stencil<T>(ndim, a, variant, g_stencil_blocks, st, ra));
-        if (rec_t.ncell > 0)
+        HIP_TRY(launch_stencil<T>(ndim, a, ij, variant, g_stencil_blocks, st, ra));
+        if (rec_t.ncell > 0 && !ij.map)
           HIP_TRY(launch_inject<T>(a, rec_t, resid + (int64_t)n * rec_t.npts, a.next, st));
         HIP_TRY(launch_correlate<T>(grad, e.s, a.next, N, st));
       }
@@ -1348,7 +1433,7 @@ static rtm_status autotune_impl(const rtm_plan *P, const void *mv, char *w, int 
   const T amp = (T)1e-3;
   HIP_TRY(launch_pattern<T>(s0, N, 0x1234567u, amp, st));
   HIP_TRY(launch_pattern<T>(s1, N, 0x89abcdefu, amp, st));
-  HIP_TRY(launch_stencil<T>(P->d.ndim, a, kStencilSimple, g_stencil_blocks, st));
+  HIP_TRY(launch_stencil<T>(P->d.ndim, a, InjMap<T>(), kStencilSimple, g_stencil_blocks, st));
   HIP_TRY(launch_copy<T>(s3, s2, N, st));
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
@@ -1363,14 +1448,14 @@ static rtm_status autotune_impl(const rtm_plan *P, const void *mv, char *w, int 
     unsigned long long diff = 0;
     hipError_t e = launch_fill<double>(reinterpret_cast<double *>(cnt), 1, 0.0, st);
     for (int rev = 0; rev < 2 && e == hipSuccess; ++rev) {
-      e = launch_stencil<T>(P->d.ndim, a, v, g_stencil_blocks, st, rev);
+      e = launch_stencil<T>(P->d.ndim, a, InjMap<T>(), v, g_stencil_blocks, st, rev);
       if (e == hipSuccess) e = launch_count_diff<T>(s2, s3, N, cnt, st);
     }
     if (e == hipSuccess) e = hipMemcpyAsync(&diff, cnt, sizeof diff, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e == hipSuccess) e = hipEventRecord(e0, st);
     for (int i = 0; i < steps && e == hipSuccess; ++i)
-      e = launch_stencil<T>(P->d.ndim, a, v, g_stencil_blocks, st,
+      e = launch_stencil<T>(P->d.ndim, a, InjMap<T>(), v, g_stencil_blocks, st,
                             g_stencil_alternate ? (i & 1) : 0);
     if (e == hipSuccess) e = hipEventRecord(e1, st);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -1411,18 +1496,12 @@ extern "C" rtm_status rtm_autotune_stencil(const rtm_plan *P, const void *m, voi
 // ---------------------------------------------------------------------------
 // batched shots: one launch per step for all shots, optional hipGraph
 // ---------------------------------------------------------------------------
-struct BatchPointRegion {
-  Region soff, sidx, sw, sshot, slocal, icell, ishot, ioff, ipt, iw;
-  int32_t cap = 0;
-};
-
 struct rtm_batch {
   int ns = 0;
   std::vector<rtm_plan *> P;
   std::vector<size_t> ring_off;
-  Region red, status, shots, io_fwd, io_adj, tiles;
+  Region red, status;
   Region queue;  // work-queue counter of the probe launches (int32)
-  BatchPointRegion src, rec;
   size_t tab_off = 0, tab_bytes = 0, total = 0;
   std::vector<int4> tile_host;
   int32_t nsrc_total = 0, nrec_total = 0;
@@ -1432,21 +1511,6 @@ struct rtm_batch {
   hipGraphExec_t gexec = nullptr;
   uint64_t gkey = 0;
 };
-
-static void place_batch_points(size_t &cur, BatchPointRegion &pr, int32_t n, size_t esz) {
-  const size_t c = (size_t)8 * n;
-  pr.cap = n;
-  place(cur, pr.soff, 4 * ((size_t)n + 1));
-  place(cur, pr.sidx, 4 * c);
-  place(cur, pr.sw, esz * c);
-  place(cur, pr.sshot, 4 * (size_t)n);
-  place(cur, pr.slocal, 4 * (size_t)n);
-  place(cur, pr.icell, 4 * c);
-  place(cur, pr.ishot, 4 * c);
-  place(cur, pr.ioff, 4 * (c + 1));
-  place(cur, pr.ipt, 4 * c);
-  place(cur, pr.iw, esz * c);
-}
 
 extern "C" void rtm_batch_destroy(rtm_batch *b) {
   if (!b) return;
@@ -1530,13 +1594,17 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
   place(cur, b->status, sizeof(uint32_t));
   place(cur, b->queue, sizeof(int32_t));
   b->tab_off = cur;
-  place(cur, b->shots, sizeof(ShotStep<float>) * nshots);
-  place(cur, b->io_fwd, sizeof(ShotIO<float>) * nshots);
-  place(cur, b->io_adj, sizeof(ShotIO<float>) * nshots);
-  place(cur, b->tiles, sizeof(int4) * b->tile_host.size());
-  place_batch_points(cur, b->src, b->nsrc_total, 4);
-  place_batch_points(cur, b->rec, b->nrec_total, 4);
-  b->tab_bytes = cur - b->tab_off;
+  size_t smap = 0, rmap = 0;
+  for (auto *p : b->P) {
+    smap += map_cap(p->d.nsrc, p->N) + 64;  // each map is packed by itself
+    rmap += map_cap(p->d.nrec, p->N) + 64;
+  }
+  b->tab_bytes = align256(sizeof(ShotStep<float>) * nshots) +
+                 2 * align256(sizeof(ShotIO<float>) * nshots) +
+                 align256(sizeof(int4) * b->tile_host.size()) +
+                 point_bytes(b->nsrc_total, 4, smap, 4, 4) +
+                 point_bytes(b->nrec_total, 4, rmap, 4, 4);
+  cur += b->tab_bytes;
   b->total = cur;
   *out = b;
   return RTM_OK;
@@ -1548,91 +1616,65 @@ extern "C" rtm_status rtm_batch_workspace_bytes(const rtm_batch *b, size_t *byte
   return RTM_OK;
 }
 
-// merged CSR tables of one point set across shots (host staging)
-static rtm_status stage_batch_points(const rtm_batch *b, const BatchPointRegion &pr,
-                                     const rtm_shot_io *io, bool rec, std::vector<unsigned char> &host,
-                                     int32_t *npts, int32_t *ncell, uint64_t *hash) {
-  std::vector<int32_t> soff(1, 0), sidx, sshot, slocal, icell, ishot, ioff(1, 0), ipt;
-  std::vector<float> sw, iw;
+// device tables of one batched call
+struct BatchTables {
+  const ShotStep<float> *shots = nullptr;
+  const ShotIO<float> *iof = nullptr, *ioa = nullptr;
+  const int4 *tiles = nullptr;
+  BatchPoints<float> src, rec;
+};
+
+// merged CSR tables of one point set across shots, with the shots' injection
+// maps into `sio` (mapped: every shot's fits)
+static rtm_status pack_batch_points(const rtm_batch *b, const rtm_shot_io *io, bool rec, Pack &pk,
+                                    std::vector<ShotIO<float>> &sio, BatchPoints<float> *t) {
+  HostPoints<float> hp;
+  std::vector<int32_t> sshot, slocal, ishot, map;
+  t->mapped = true;
   for (int i = 0; i < b->ns; ++i) {
     const rtm_plan *P = b->P[i];
     const int32_t n = rec ? P->d.nrec : P->d.nsrc;
     const double *pos = rec ? io[i].rec_pos : io[i].src_pos;
     if (n > 0 && !pos) return fail(RTM_E_ARG, "shot %d: positions missing", i);
-    for (int32_t k = 0; k < 3 * n; ++k) {
-      uint64_t v;
-      std::memcpy(&v, pos + k, 8);
-      *hash = (*hash ^ v) * 1099511628211ull;
-    }
-    HostPoints hp;
-    rtm_status st = build_points(P, n, pos, hp);
+    rtm_status st = add_points(P, n, pos, hp);
     if (st) return st;
-    for (int32_t p = 0; p < n; ++p) {
-      for (int32_t j = hp.soff[p]; j < hp.soff[p + 1]; ++j) {
-        sidx.push_back(hp.sidx[j]);
-        sw.push_back((float)hp.sw[j]);
-      }
-      soff.push_back((int32_t)sidx.size());
-      sshot.push_back(i);
-      slocal.push_back(p);
-    }
-    for (size_t c = 0; c < hp.icell.size(); ++c) {
-      icell.push_back(hp.icell[c]);
-      ishot.push_back(i);
-      for (int32_t j = hp.ioff[c]; j < hp.ioff[c + 1]; ++j) {
-        ipt.push_back(hp.ipt[j]);
-        iw.push_back((float)hp.iw[j]);
-      }
-      ioff.push_back((int32_t)ipt.size());
-    }
+    InjMap<float> &m = sio[i].map;
+    if (make_map(P, hp, map_cap(n, P->N), map, &m)) m.map = pk.put(map);
+    else if (n > 0) t->mapped = false;
+    sshot.insert(sshot.end(), n, i);
+    for (int32_t p = 0; p < n; ++p) slocal.push_back(p);
+    ishot.resize(hp.icell.size(), i);
   }
-  auto put = [&](const Region &r, const void *src, size_t bytes) {
-    if (bytes) std::memcpy(host.data() + (r.off - b->tab_off), src, bytes);
-  };
-  put(pr.soff, soff.data(), 4 * soff.size());
-  put(pr.sidx, sidx.data(), 4 * sidx.size());
-  put(pr.sw, sw.data(), 4 * sw.size());
-  put(pr.sshot, sshot.data(), 4 * sshot.size());
-  put(pr.slocal, slocal.data(), 4 * slocal.size());
-  put(pr.icell, icell.data(), 4 * icell.size());
-  put(pr.ishot, ishot.data(), 4 * ishot.size());
-  put(pr.ioff, ioff.data(), 4 * ioff.size());
-  put(pr.ipt, ipt.data(), 4 * ipt.size());
-  put(pr.iw, iw.data(), 4 * iw.size());
-  *npts = (int32_t)sshot.size();
-  *ncell = (int32_t)icell.size();
+  t->soff = pk.put(hp.soff);
+  t->sidx = pk.put(hp.sidx);
+  t->sw = pk.put(hp.sw);
+  t->sshot = pk.put(sshot);
+  t->slocal = pk.put(slocal);
+  t->icell = pk.put(hp.icell);
+  t->ishot = pk.put(ishot);
+  t->ioff = pk.put(hp.ioff);
+  t->ipt = pk.put(hp.ipt);
+  t->iw = pk.put(hp.iw);
+  t->npts = (int32_t)sshot.size();
+  t->ncell = (int32_t)hp.icell.size();
+  for (auto &x : sio) {
+    x.map.ioff = t->ioff;
+    x.map.ipt = t->ipt;
+    x.map.iw = t->iw;
+  }
   return RTM_OK;
-}
-
-static BatchPoints<float> batch_points(const BatchPointRegion &pr, char *w, int32_t npts,
-                                       int32_t ncell) {
-  BatchPoints<float> t;
-  t.soff = reinterpret_cast<const int32_t *>(w + pr.soff.off);
-  t.sidx = reinterpret_cast<const int32_t *>(w + pr.sidx.off);
-  t.sw = reinterpret_cast<const float *>(w + pr.sw.off);
-  t.sshot = reinterpret_cast<const int32_t *>(w + pr.sshot.off);
-  t.slocal = reinterpret_cast<const int32_t *>(w + pr.slocal.off);
-  t.icell = reinterpret_cast<const int32_t *>(w + pr.icell.off);
-  t.ishot = reinterpret_cast<const int32_t *>(w + pr.ishot.off);
-  t.ioff = reinterpret_cast<const int32_t *>(w + pr.ioff.off);
-  t.ipt = reinterpret_cast<const int32_t *>(w + pr.ipt.off);
-  t.iw = reinterpret_cast<const float *>(w + pr.iw.off);
-  t.npts = npts;
-  t.ncell = ncell;
-  return t;
 }
 
 // The whole batched gradient as a stream-ordered launch sequence (captured
 // into a graph when requested).
 static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, double *misfit,
-                                char *w, const BatchPoints<float> &src_t,
-                                const BatchPoints<float> &rec_t, int variant, hipStream_t st) {
+                                char *w, const BatchTables &bt, int variant, hipStream_t st) {
   const rtm_desc &d = b->P[0]->d;
   const int nt = d.nt, k = d.k_block;
-  const auto *shots = reinterpret_cast<const ShotStep<float> *>(w + b->shots.off);
-  const auto *iof = reinterpret_cast<const ShotIO<float> *>(w + b->io_fwd.off);
-  const auto *ioa = reinterpret_cast<const ShotIO<float> *>(w + b->io_adj.off);
-  const auto *tiles = reinterpret_cast<const int4 *>(w + b->tiles.off);
+  const ShotStep<float> *shots = bt.shots;
+  const ShotIO<float> *iof = bt.iof, *ioa = bt.ioa;
+  const int4 *tiles = bt.tiles;
+  const BatchPoints<float> &src_t = bt.src, &rec_t = bt.rec;
   const int ntiles = (int)b->tile_host.size();
   auto ring = [&](int i) { return reinterpret_cast<float *>(w + b->ring_off[i]); };
   auto lvl = [&](int i, int j) {
@@ -1675,11 +1717,11 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   }
   int s0 = 0;
   for (int s = 0; s < nt; ++s) {
-    HIP_TRY(launch_stencil_batched<float>(shots, tiles, ntiles, s, variant, b->ragged, st,
-                                          g_stencil_alternate ? (s & 1) : 0));
-    HIP_TRY(launch_inject_batched<float>(shots, iof, src_t, s, s, st));
-    HIP_TRY(launch_sample_batched<float>(shots, iof, rec_t, s, s, st));
+    HIP_TRY(launch_stencil_batched<float>(shots, iof, src_t.mapped, tiles, ntiles, s, s, variant,
+                                          b->ragged, st, g_stencil_alternate ? (s & 1) : 0));
+    if (!src_t.mapped) HIP_TRY(launch_inject_batched<float>(shots, iof, src_t, s, s, st));
     if (s + 1 - s0 == k || s == nt - 1) {
+      HIP_TRY(launch_sample_batched<float>(shots, iof, rec_t, s0, s + 1 - s0, st));
       if ((s_ = probe(false, s0, s + 1 - s0))) return s_;
       s0 = s + 1;
     }
@@ -1699,9 +1741,10 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   }
   s0 = 0;
   for (int s = 0; s < nt; ++s) {
-    HIP_TRY(launch_stencil_batched<float>(shots, tiles, ntiles, s, variant, b->ragged, st,
+    HIP_TRY(launch_stencil_batched<float>(shots, ioa, rec_t.mapped, tiles, ntiles, s, nt - 1 - s,
+                                          variant, b->ragged, st,
                                           g_stencil_alternate ? (s & 1) : 0));
-    HIP_TRY(launch_inject_batched<float>(shots, ioa, rec_t, s, nt - 1 - s, st));
+    if (!rec_t.mapped) HIP_TRY(launch_inject_batched<float>(shots, ioa, rec_t, s, nt - 1 - s, st));
     if (s + 1 - s0 == k || s == nt - 1) {
       if ((s_ = probe(true, s0, s + 1 - s0))) return s_;
       s0 = s + 1;
@@ -1761,11 +1804,7 @@ extern "C" rtm_status fwi_gradient_batched(rtm_batch *b, const rtm_shot_io *io, 
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   char *w = static_cast<char *>(work);
-  // stage every table (shot steps, io, tiles, points) and upload once
-  std::vector<unsigned char> host(b->tab_bytes, 0);
-  auto put = [&](const Region &r, const void *src, size_t bytes) {
-    std::memcpy(host.data() + (r.off - b->tab_off), src, bytes);
-  };
+  // pack every table (shot steps, io, tiles, points) and upload once
   std::vector<ShotStep<float>> shots(b->ns);
   std::vector<ShotIO<float>> iof(b->ns), ioa(b->ns);
   uint64_t key = 1469598103934665603ull;
@@ -1779,28 +1818,43 @@ extern "C" rtm_status fwi_gradient_batched(rtm_batch *b, const rtm_shot_io *io, 
     shots[i].ld = P->ld;
     shots[i].R = P->R;
     iof[i] = {static_cast<const float *>(io[i].q), static_cast<float *>(io[i].resid), P->d.nsrc,
-              P->d.nrec};
-    ioa[i] = {static_cast<const float *>(io[i].resid), nullptr, P->d.nrec, 0};
+              P->d.nrec, {}};
+    ioa[i] = {static_cast<const float *>(io[i].resid), nullptr, P->d.nrec, 0, {}};
     for (const void *p : {io[i].m, io[i].q, io[i].d_obs, io[i].Z, (const void *)io[i].Ubar,
                           (const void *)io[i].resid, (const void *)io[i].grad})
       mix(p);
   }
-  put(b->shots, shots.data(), sizeof(ShotStep<float>) * b->ns);
-  put(b->io_fwd, iof.data(), sizeof(ShotIO<float>) * b->ns);
-  put(b->io_adj, ioa.data(), sizeof(ShotIO<float>) * b->ns);
-  put(b->tiles, b->tile_host.data(), sizeof(int4) * b->tile_host.size());
-  int32_t snp = 0, snc = 0, rnp = 0, rnc = 0;
-  rtm_status s = stage_batch_points(b, b->src, io, false, host, &snp, &snc, &key);
+  Pack pk(w + b->tab_off);
+  BatchTables bt;
+  bt.shots = pk.put(shots);
+  bt.tiles = pk.put(b->tile_host);
+  const size_t at_f = pk.host.size();
+  bt.iof = pk.put(iof);  // rewritten below, with the maps
+  const size_t at_a = pk.host.size();
+  bt.ioa = pk.put(ioa);
+  rtm_status s = pack_batch_points(b, io, false, pk, iof, &bt.src);
   if (s) return s;
-  if ((s = stage_batch_points(b, b->rec, io, true, host, &rnp, &rnc, &key))) return s;
+  if ((s = pack_batch_points(b, io, true, pk, ioa, &bt.rec))) return s;
+  std::memcpy(pk.host.data() + at_f, iof.data(), sizeof(ShotIO<float>) * b->ns);
+  std::memcpy(pk.host.data() + at_a, ioa.data(), sizeof(ShotIO<float>) * b->ns);
+  if (use_graph)  // a captured sequence holds pointers into the packed tables
+    for (int i = 0; i < b->ns; ++i)
+      for (int rec = 0; rec < 2; ++rec) {
+        const double *pos = rec ? io[i].rec_pos : io[i].src_pos;
+        const int32_t n = rec ? b->P[i]->d.nrec : b->P[i]->d.nsrc;
+        for (size_t k = 0; k < 3 * (size_t)n; ++k) {
+          uint64_t v;
+          std::memcpy(&v, pos + k, 8);
+          key = key_mix(key, v);
+        }
+      }
   int variant = g_stencil_variant >= kStencilTiled ? g_stencil_variant : b->stream ? 7 : 1;
   key = (key ^ (uint64_t)variant) * 1099511628211ull;
   key = (key ^ (uint64_t)(g_stencil_alternate + 64)) * 1099511628211ull;
-  HIP_TRY(hipMemcpyAsync(w + b->tab_off, host.data(), b->tab_bytes, hipMemcpyHostToDevice, st));
+  if (pk.host.size() > b->tab_bytes) return fail(RTM_E_WORKSPACE, "point tables do not fit");
+  HIP_TRY(hipMemcpyAsync(w + b->tab_off, pk.host.data(), pk.host.size(), hipMemcpyHostToDevice, st));
   HIP_TRY(hipStreamSynchronize(st));
-  BatchPoints<float> src_t = batch_points(b->src, w, snp, snc);
-  BatchPoints<float> rec_t = batch_points(b->rec, w, rnp, rnc);
-  if (!use_graph) return batch_enqueue(b, io, misfit, w, src_t, rec_t, variant, st);
+  if (!use_graph) return batch_enqueue(b, io, misfit, w, bt, variant, st);
   if (!b->gexec || b->gkey != key) {
     if (b->gexec) {
       (void)hipGraphExecDestroy(b->gexec);
@@ -1810,7 +1864,7 @@ extern "C" rtm_status fwi_gradient_batched(rtm_batch *b, const rtm_shot_io *io, 
     HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
     const int saved = g_prof_stride;
     g_prof_stride = 0;  // no event records inside a capture
-    s = batch_enqueue(b, io, misfit, w, src_t, rec_t, variant, st);
+    s = batch_enqueue(b, io, misfit, w, bt, variant, st);
     g_prof_stride = saved;
     hipError_t e = hipStreamEndCapture(st, &g);
     if (s) {
@@ -1897,13 +1951,15 @@ static rtm_status run_tti_sweep(const rtm_plan *P, const TtiIO &io, const PointT
       HIP_TRY(launch_inject<T>(a, inj, vals + (int64_t)n * inj.npts, pn, st));
       if (!io.adjoint) HIP_TRY(launch_inject<T>(a, inj, vals + (int64_t)n * inj.npts, qn, st));
     }
-    if (out && smp.npts > 0) {
-      if (!io.adjoint)
-        HIP_TRY(launch_sample<T>(smp, pn, out + (int64_t)n * smp.npts, st));
-      else
-        HIP_TRY(launch_sample_sum<T>(smp, pn, qn, out + (int64_t)n * smp.npts, st));
-    }
-    if ((bar || io.fuse_img) && (s + 1 - s0 == d.k_block || s == d.nt - 1)) {
+    const bool block_end = s + 1 - s0 == d.k_block || s == d.nt - 1;
+    // the adjoint samples p + q: the transpose of injecting into both fields
+    if (out && block_end)
+      HIP_TRY(launch_sample_block<T>(smp, ringP, io.adjoint ? ringQ : nullptr, ld, P->R, s0,
+                                     s + 1 - s0, io.adjoint ? -1 : 1,
+                                     out + (int64_t)(io.adjoint ? d.nt - 1 - s0 : s0) * smp.npts,
+                                     st));
+    if (block_end && !bar && !io.fuse_img) s0 = s + 1;
+    else if (block_end) {
       for (int f = 0; f < 2; ++f) {
         ProbeArgs<T> p{};
         p.ring = f == 0 ? ringP : ringQ;

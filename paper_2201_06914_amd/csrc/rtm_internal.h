@@ -29,6 +29,19 @@ struct StepArgs {
   T kd;              // sponge coefficient per squared cell depth
 };
 
+// Injection folded into the step kernels: the bounding box of the injected
+// cells (half open) with one int per cell of it: -1 nothing; p >= 0 the single
+// point p with weight one; -2 - c the entries of distinct cell c.  map is NULL
+// when nothing is folded in.
+template <typename T>
+struct InjMap {
+  const int32_t *map = nullptr;
+  const int32_t *ioff = nullptr, *ipt = nullptr;
+  const T *iw = nullptr;
+  const T *vals = nullptr;  // this step's point values
+  int z0 = 0, z1 = 0, y0 = 0, y1 = 0, x0 = 0, x1 = 0;
+};
+
 // One shot of a batched sweep: its step arguments (level pointers are
 // rebuilt per step from the ring: level j in slot (j+1) mod R).
 template <typename T>
@@ -63,6 +76,7 @@ struct PointTables {
   const T *iw = nullptr;
   int32_t npts = 0;
   int32_t ncell = 0;
+  InjMap<T> inj;  // map set when the step kernels take the injection (vals per step)
 };
 
 // Point tables of a batch of shots: one CSR across all shots.  Sampling is
@@ -75,12 +89,14 @@ struct BatchPoints {
   const int32_t *icell = nullptr, *ishot = nullptr, *ioff = nullptr, *ipt = nullptr;
   const T *iw = nullptr;
   int32_t npts = 0, ncell = 0;
+  bool mapped = false;  // every shot's injection is folded into the steps
 };
 template <typename T>
 struct ShotIO {
   const T *inj;   // [nt][n_inj] values injected at this shot's points
   T *out;         // [nt][n_smp] sampled traces, or NULL
   int32_t n_inj, n_smp;
+  InjMap<T> map;  // vals: set per step from inj
 };
 
 // operand type of the MFMA probe path: bf16, bf16 hi + lo, or float16 with a
@@ -116,14 +132,16 @@ struct ProbeArgs {
 // variant -1: chosen from the grid, and so are its z chunks if target_blocks
 // is kAutoBlocks
 // rev != 0: the tiled kernels march each z-chunk downwards (same results)
+// inj: the step's injection where it has a map (else launch_inject after it)
 template <typename T>
-hipError_t launch_stencil(int ndim, const StepArgs<T> &a, int variant, int target_blocks,
-                          hipStream_t st, int rev = 0);
+hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, int variant,
+                          int target_blocks, hipStream_t st, int rev = 0);
 // exact comparator: stencil step with a fused epilogue (hipErrorInvalidValue
 // when no tiled kernel serves the grid), and the matching injection
 template <typename T>
-hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, int variant, int target_blocks,
-                              int epi, const EpiArgs<T> &e, hipStream_t st, int rev = 0);
+hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, int variant,
+                              int target_blocks, int epi, const EpiArgs<T> &e, hipStream_t st,
+                              int rev = 0);
 template <typename T>
 hipError_t launch_inject_epi(const StepArgs<T> &a, const PointTables<T> &pt, const T *vals,
                              T *field, int epi, const EpiArgs<T> &e, hipStream_t st);
@@ -143,16 +161,19 @@ template <typename T>
 hipError_t launch_offset_gathers(const T *U, const T *V, int nfield, int64_t fstride, int64_t N,
                                  int nx, int r, int nh, double scale, T *G, hipStream_t st);
 // batched sweep step (all shots, one launch each): stencil over the tile
-// table, then injection / sampling of level s+1 for time index n
+// table for time index n (with the injection of the io entries' maps if
+// `mapped`), injection into level s+1; sampling of levels s0+1 .. s0+kb
+// (forward) into rows s0 .. s0+kb-1
 template <typename T>
-hipError_t launch_stencil_batched(const ShotStep<T> *shots, const int4 *tiles, int ntiles, int s,
-                                  int variant, bool ragged, hipStream_t st, int rev = 0);
+hipError_t launch_stencil_batched(const ShotStep<T> *shots, const ShotIO<T> *io, bool mapped,
+                                  const int4 *tiles, int ntiles, int s, int n, int variant,
+                                  bool ragged, hipStream_t st, int rev = 0);
 template <typename T>
 hipError_t launch_inject_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
                                  const BatchPoints<T> &pt, int s, int n, hipStream_t st);
 template <typename T>
 hipError_t launch_sample_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
-                                 const BatchPoints<T> &pt, int s, int n, hipStream_t st);
+                                 const BatchPoints<T> &pt, int s0, int kb, hipStream_t st);
 // TTI: per-cell coefficients [5][N] = (1 + 2 eps, sqrt(1 + 2 delta), n_z, n_y,
 // n_x) from aniso [4][N] = (eps, delta, theta, phi); one step of the coupled
 // system (adjoint = exact transpose) with intermediates g [8][N]; sampling of
@@ -175,9 +196,6 @@ template <typename T>
 hipError_t launch_tti_step(const StepArgs<T> &a, double h, bool adjoint, const T *coef,
                            const T *p, const T *pp, const T *q, const T *qp, T *pn, T *qn, T *g,
                            int shape, int target_blocks, hipStream_t st);
-template <typename T>
-hipError_t launch_sample_sum(const PointTables<T> &pt, const T *f1, const T *f2, T *out,
-                             hipStream_t st);
 // autotuning: hash pattern fill, count of bitwise-different elements (atomic
 // integer add into *count)
 template <typename T>
@@ -188,8 +206,12 @@ hipError_t launch_count_diff(const T *a, const T *b, int64_t n, unsigned long lo
 template <typename T>
 hipError_t launch_inject(const StepArgs<T> &a, const PointTables<T> &pt, const T *vals,
                          T *field, hipStream_t st);
+// samples the kb levels s0+1 .. s0+kb of a ring (level j in slot (j+1) mod R;
+// a second ring is added if not NULL) at every point: level s0+1+t to
+// out + t * dir * npts
 template <typename T>
-hipError_t launch_sample(const PointTables<T> &pt, const T *field, T *out, hipStream_t st);
+hipError_t launch_sample_block(const PointTables<T> &pt, const T *ring, const T *ring2, int64_t ld,
+                               int R, int s0, int kb, int dir, T *out, hipStream_t st);
 template <typename T>
 hipError_t launch_probe_vec(const ProbeArgs<T> &p, const void *Z, bool z_is_i8,
                             hipStream_t st);

@@ -58,11 +58,32 @@ __device__ __forceinline__ T cell_update(const StepArgs<T> &a, T u, T up, T m, T
   return quot(fma_t(a.dt2, lap, v), m + damp);
 }
 
+// The folded injection: the sum of weight x value over the entries of cell
+// (z, y, x), in the order of k_inject; false where the cell has none.
+template <typename T>
+__device__ __forceinline__ bool inj_sum(const InjMap<T> &j, int z, int y, int x, T &acc) {
+  acc = T(0);
+  if (z < j.z0 || z >= j.z1 || y < j.y0 || y >= j.y1 || x < j.x0 || x >= j.x1) return false;
+  const int v = j.map[((int64_t)(z - j.z0) * (j.y1 - j.y0) + (y - j.y0)) * (j.x1 - j.x0) + x - j.x0];
+  if (v >= 0) {
+    acc += j.vals[v];
+  } else if (v < -1) {
+    const int c = -2 - v;
+    for (int e = j.ioff[c]; e < j.ioff[c + 1]; ++e) acc = fma_t(j.iw[e], j.vals[j.ipt[e]], acc);
+  }
+  return v != -1;
+}
+// what the injection adds to the new level (`mpa` = m + damping)
+template <typename T>
+__device__ __forceinline__ T inj_term(const StepArgs<T> &a, T acc, T mpa) {
+  return a.dt2 * acc / mpa;
+}
+
 // ---------------------------------------------------------------------------
 // one thread per cell
 // ---------------------------------------------------------------------------
 template <typename T, int NDIM>
-__global__ __launch_bounds__(256) void k_stencil_simple(StepArgs<T> a) {
+__global__ __launch_bounds__(256) void k_stencil_simple(StepArgs<T> a, InjMap<T> inj) {
   const uint32_t i = blockIdx.x * 256u + threadIdx.x;  // N < 2^31
   if (i >= (uint32_t)a.N) return;
   const uint32_t zy = i / (uint32_t)a.nx;
@@ -88,7 +109,11 @@ __global__ __launch_bounds__(256) void k_stencil_simple(StepArgs<T> a) {
   } else {
     lap = fma_t(a.cc, c, lz) + lx;
   }
-  a.next[i] = cell_update(a, c, a.prev[i], a.m[i], lap, sponge_a(a, z, y, x));
+  const T damp = sponge_a(a, z, y, x);
+  T v = cell_update(a, c, a.prev[i], a.m[i], lap, damp);
+  T acc;
+  if (inj.map && inj_sum(inj, z, y, x, acc)) v += inj_term(a, acc, a.m[i] + damp);
+  a.next[i] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -202,8 +227,8 @@ __device__ __forceinline__ void vstore(__amdgpu_buffer_rsrc_t r, const VOff &o,
 // from step to step, so that a step starts on the planes the previous step
 // touched last (still in the memory-side cache).
 template <typename T, int TX, int TYT, int RY, bool NT, int EPI, bool RAG>
-__device__ __forceinline__ void tiled_body(const StepArgs<T> &a, int bx, int by, int z0, int z1,
-                                           const EpiArgs<T> &e, bool rev) {
+__device__ __forceinline__ void tiled_body(const StepArgs<T> &a, const InjMap<T> &inj, int bx,
+                                           int by, int z0, int z1, const EpiArgs<T> &e, bool rev) {
   typedef typename V16<T>::type V;
   constexpr int VX = V16<T>::n;                  // cells per vector
   constexpr int GX = TX / VX;                    // threads along x
@@ -274,6 +299,8 @@ __device__ __forceinline__ void tiled_body(const StepArgs<T> &a, int bx, int by,
     return plane_rsrc(f + (int64_t)z * sp, (z >= 0 && z < a.nz) ? pbytes : 0u);
   };
   V q[RY][9], front[RY], hv[KH], pv[RY], mv[RY], es[RY], eg[RY];
+  // folded injection: only tiles over its box look
+  const bool itile = inj.map && x0 < inj.x1 && x0 + TX > inj.x0 && y0 < inj.y1 && y0 + TY > inj.y0;
   auto ldhalo = [&](__amdgpu_buffer_rsrc_t r, V *h) {
 #pragma unroll
     for (int k = 0; k < KH; ++k)
@@ -390,8 +417,21 @@ __device__ __forceinline__ void tiled_body(const StepArgs<T> &a, int bx, int by,
                               w[c + 8], w[c]);
         const T lap = (fma_t(a.cc, u, lz) + ly) + lx;
         out[c] = cell_update(a, u, pvc[j][c], mvc[j][c], lap, sponge_mul(a.kd, fz + fyx[j][c]));
-        if constexpr (EPI == EPI_D2) d2[c] = (out[c] - T(2) * u + pvc[j][c]) * e.inv_dt2;
-        if constexpr (EPI == EPI_CORR) d2[c] = egc[j][c] - esc[j][c] * out[c];
+        if constexpr (EPI == EPI_D2)
+          d2[c] = (fma_t(T(-2), u, out[c]) + pvc[j][c]) * e.inv_dt2;
+        if constexpr (EPI == EPI_CORR) d2[c] = fma_t(-esc[j][c], out[c], egc[j][c]);
+      }
+      if (itile && z >= inj.z0 && z < inj.z1) {
+#pragma unroll
+        for (int c = 0; c < VX; ++c) {
+          T acc;
+          if (inj_sum(inj, z, y0 + ty + j * TYT, x + c, acc)) {
+            const T t = inj_term(a, acc, mvc[j][c] + sponge_mul(a.kd, fz + fyx[j][c]));
+            out[c] += t;
+            if constexpr (EPI == EPI_D2) d2[c] = fma_t(t, e.inv_dt2, d2[c]);
+            if constexpr (EPI == EPI_CORR) d2[c] = fma_t(-esc[j][c], t, d2[c]);
+          }
+        }
       }
       vstore<T, NT, RAG>(ro, own[j], out);
       if constexpr (EPI == EPI_D2) vstore<T, NT, RAG>(plane(e.d2, z), own[j], d2);
@@ -425,10 +465,8 @@ __device__ __forceinline__ void tiled_body(const StepArgs<T> &a, int bx, int by,
 }
 
 template <typename T, int TX, int TYT, int RY, bool NT, int EPI, bool RAG>
-__global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_tiled(StepArgs<T> a, int ntx,
-                                                                         int nty, int nzc,
-                                                                         int zchunk, EpiArgs<T> e,
-                                                                         int rev) {
+__global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_tiled(
+    StepArgs<T> a, InjMap<T> inj, int ntx, int nty, int nzc, int zchunk, EpiArgs<T> e, int rev) {
   // XCD-aware order: consecutive hardware block ids go round-robin over the 8
   // XCDs; give each XCD a contiguous run of tiles so halo re-reads hit its L2.
   const int nblk = ntx * nty * nzc;
@@ -438,7 +476,7 @@ __global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_tiled(StepArg
   const int by = (b / ntx) % nty;
   const int bz = rev ? nzc - 1 - b / (ntx * nty) : b / (ntx * nty);
   const int z0 = bz * zchunk;
-  tiled_body<T, TX, TYT, RY, NT, EPI, RAG>(a, bx, by, z0, min(z0 + zchunk, a.nz), e, rev != 0);
+  tiled_body<T, TX, TYT, RY, NT, EPI, RAG>(a, inj, bx, by, z0, min(z0 + zchunk, a.nz), e, rev != 0);
 }
 
 // Several shots (independent grids, one ring each) in one launch: entry e of
@@ -446,8 +484,8 @@ __global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_tiled(StepArg
 // from a device table (level pointers rebuilt from the step index s).
 template <typename T, int TX, int TYT, int RY, bool NT, bool RAG>
 __global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_batched(
-    const ShotStep<T> *__restrict__ shots, const int4 *__restrict__ tiles, int ntiles, int s,
-    int rev) {
+    const ShotStep<T> *__restrict__ shots, const ShotIO<T> *__restrict__ io, int mapped,
+    const int4 *__restrict__ tiles, int ntiles, int s, int n, int rev) {
   int b = blockIdx.x;
   b = xcd_block(b, ntiles);
   const int4 t = tiles[b];  // (shot, bx | by << 16, z0, z1)
@@ -456,12 +494,17 @@ __global__ __launch_bounds__(TX / V16<T>::n *TYT) void k_stencil3d_batched(
   a.cur = sh.ring + (int64_t)(((s + 1) % sh.R)) * sh.ld;
   a.prev = sh.ring + (int64_t)(((s + sh.R) % sh.R)) * sh.ld;
   a.next = sh.ring + (int64_t)(((s + 2) % sh.R)) * sh.ld;
-  tiled_body<T, TX, TYT, RY, NT, EPI_NONE, RAG>(a, t.y & 0xffff, t.y >> 16, t.z, t.w,
+  InjMap<T> inj;
+  if (mapped) {
+    inj = io[t.x].map;
+    inj.vals = io[t.x].inj + (int64_t)n * io[t.x].n_inj;
+  }
+  tiled_body<T, TX, TYT, RY, NT, EPI_NONE, RAG>(a, inj, t.y & 0xffff, t.y >> 16, t.z, t.w,
                                                EpiArgs<T>{}, rev != 0);
 }
 
 template <typename T, int TX, int TYT, int RY, bool NT, int EPI = EPI_NONE>
-static void launch_tiled(const StepArgs<T> &a, int nzc, hipStream_t st,
+static void launch_tiled(const StepArgs<T> &a, const InjMap<T> &inj, int nzc, hipStream_t st,
                          const EpiArgs<T> &e = EpiArgs<T>{}, int rev = 0) {
   constexpr int TY = TYT * RY;
   constexpr int NTH = TX / V16<T>::n * TYT;
@@ -471,10 +514,10 @@ static void launch_tiled(const StepArgs<T> &a, int nzc, hipStream_t st,
   nzc = (a.nz + zchunk - 1) / zchunk;
   if (a.nx % V16<T>::n == 0)
     hipLaunchKernelGGL((k_stencil3d_tiled<T, TX, TYT, RY, NT, EPI, false>), dim3(ntx * nty * nzc),
-                       dim3(NTH), 0, st, a, ntx, nty, nzc, zchunk, e, rev);
+                       dim3(NTH), 0, st, a, inj, ntx, nty, nzc, zchunk, e, rev);
   else
     hipLaunchKernelGGL((k_stencil3d_tiled<T, TX, TYT, RY, NT, EPI, true>), dim3(ntx * nty * nzc),
-                       dim3(NTH), 0, st, a, ntx, nty, nzc, zchunk, e, rev);
+                       dim3(NTH), 0, st, a, inj, ntx, nty, nzc, zchunk, e, rev);
 }
 
 // z chunks of a tile shape: the fewest (of at least `minp` planes) that give
@@ -537,8 +580,8 @@ static int auto_variant(const StepArgs<T> &a, int *nzc) {
 }
 
 template <typename T>
-hipError_t launch_stencil(int ndim, const StepArgs<T> &a, int variant, int target_blocks,
-                          hipStream_t st, int rev) {
+hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, int variant,
+                          int target_blocks, hipStream_t st, int rev) {
   constexpr int F = sizeof(T) / 4;
   const EpiArgs<T> e{};
   // a plane is addressed with 32-bit byte offsets below kOff
@@ -559,39 +602,41 @@ hipError_t launch_stencil(int ndim, const StepArgs<T> &a, int variant, int targe
     case kStencilSimple: {
       const unsigned nblk = (unsigned)((a.N + 255) / 256);
       if (ndim == 3)
-        hipLaunchKernelGGL((k_stencil_simple<T, 3>), dim3(nblk), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_stencil_simple<T, 3>), dim3(nblk), dim3(256), 0, st, a, inj);
       else
-        hipLaunchKernelGGL((k_stencil_simple<T, 2>), dim3(nblk), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_stencil_simple<T, 2>), dim3(nblk), dim3(256), 0, st, a, inj);
       break;
     }
-    case 2: launch_tiled<T, 64, 32 / F, 1, false>(a, nzc, st, e, rev); break;
-    case 3: launch_tiled<T, 64, 16 / F, 2, false>(a, nzc, st, e, rev); break;
-    case 4: launch_tiled<T, 64, 8 / F, 1, false>(a, nzc, st, e, rev); break;
-    case 5: launch_tiled<T, 32, 32 / F, 1, false>(a, nzc, st, e, rev); break;
-    case 6: launch_tiled<T, 128, 8 / F, 1, false>(a, nzc, st, e, rev); break;
-    case 7: launch_tiled<T, 64, 16 / F, 1, true>(a, nzc, st, e, rev); break;
-    case 8: launch_tiled<T, 64, 32 / F, 1, true>(a, nzc, st, e, rev); break;
-    case 9: launch_tiled<T, 64, 16 / F, 2, true>(a, nzc, st, e, rev); break;
-    case 10: launch_tiled<T, 64, 8 / F, 1, true>(a, nzc, st, e, rev); break;
-    case 11: launch_tiled<T, 32, 32 / F, 1, true>(a, nzc, st, e, rev); break;
-    case 12: launch_tiled<T, 128, 8 / F, 1, true>(a, nzc, st, e, rev); break;
-    case 13: launch_tiled<T, 32, 16 / F, 1, false>(a, nzc, st, e, rev); break;
-    default: launch_tiled<T, 64, 16 / F, 1, false>(a, nzc, st, e, rev); break;
+    case 2: launch_tiled<T, 64, 32 / F, 1, false>(a, inj, nzc, st, e, rev); break;
+    case 3: launch_tiled<T, 64, 16 / F, 2, false>(a, inj, nzc, st, e, rev); break;
+    case 4: launch_tiled<T, 64, 8 / F, 1, false>(a, inj, nzc, st, e, rev); break;
+    case 5: launch_tiled<T, 32, 32 / F, 1, false>(a, inj, nzc, st, e, rev); break;
+    case 6: launch_tiled<T, 128, 8 / F, 1, false>(a, inj, nzc, st, e, rev); break;
+    case 7: launch_tiled<T, 64, 16 / F, 1, true>(a, inj, nzc, st, e, rev); break;
+    case 8: launch_tiled<T, 64, 32 / F, 1, true>(a, inj, nzc, st, e, rev); break;
+    case 9: launch_tiled<T, 64, 16 / F, 2, true>(a, inj, nzc, st, e, rev); break;
+    case 10: launch_tiled<T, 64, 8 / F, 1, true>(a, inj, nzc, st, e, rev); break;
+    case 11: launch_tiled<T, 32, 32 / F, 1, true>(a, inj, nzc, st, e, rev); break;
+    case 12: launch_tiled<T, 128, 8 / F, 1, true>(a, inj, nzc, st, e, rev); break;
+    case 13: launch_tiled<T, 32, 16 / F, 1, false>(a, inj, nzc, st, e, rev); break;
+    default: launch_tiled<T, 64, 16 / F, 1, false>(a, inj, nzc, st, e, rev); break;
   }
   return hipGetLastError();
 }
 
-template hipError_t launch_stencil<float>(int, const StepArgs<float> &, int, int, hipStream_t, int);
-template hipError_t launch_stencil<double>(int, const StepArgs<double> &, int, int, hipStream_t,
-                                           int);
+template hipError_t launch_stencil<float>(int, const StepArgs<float> &, const InjMap<float> &, int,
+                                          int, hipStream_t, int);
+template hipError_t launch_stencil<double>(int, const StepArgs<double> &, const InjMap<double> &,
+                                           int, int, hipStream_t, int);
 
 // Stencil step with an exact-comparator epilogue (3D F32, 64 x 16 tiles with
 // the z split of the plain step's rule).  Returns hipErrorInvalidValue for
 // grids the tiled kernel does not serve, so the caller falls back to the
 // separate kernels.
 template <typename T>
-hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, int variant, int target_blocks,
-                              int epi, const EpiArgs<T> &e, hipStream_t st, int rev) {
+hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, int variant,
+                              int target_blocks, int epi, const EpiArgs<T> &e, hipStream_t st,
+                              int rev) {
   if (ndim != 3 || sizeof(T) != 4 || variant == kStencilSimple ||
       (int64_t)a.ny * a.nx * (int64_t)sizeof(T) >= (int64_t)kOff)
     return hipErrorInvalidValue;
@@ -601,20 +646,22 @@ hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, int variant, int t
     const int64_t tiles = (int64_t)((a.nx + 63) / 64) * ((a.ny + 15) / 16);
     const int nzc = z_split(a.nz, tiles, 256, target_blocks, stream ? 16 : 4);
     if (epi == EPI_D2) {
-      if (nt) launch_tiled<T, 64, 16, 1, true, EPI_D2>(a, nzc, st, e, rev);
-      else launch_tiled<T, 64, 16, 1, false, EPI_D2>(a, nzc, st, e, rev);
+      if (nt) launch_tiled<T, 64, 16, 1, true, EPI_D2>(a, inj, nzc, st, e, rev);
+      else launch_tiled<T, 64, 16, 1, false, EPI_D2>(a, inj, nzc, st, e, rev);
     } else if (epi == EPI_CORR) {
-      if (nt) launch_tiled<T, 64, 16, 1, true, EPI_CORR>(a, nzc, st, e, rev);
-      else launch_tiled<T, 64, 16, 1, false, EPI_CORR>(a, nzc, st, e, rev);
+      if (nt) launch_tiled<T, 64, 16, 1, true, EPI_CORR>(a, inj, nzc, st, e, rev);
+      else launch_tiled<T, 64, 16, 1, false, EPI_CORR>(a, inj, nzc, st, e, rev);
     } else {
       return hipErrorInvalidValue;
     }
   }
   return hipGetLastError();
 }
-template hipError_t launch_stencil_epi<float>(int, const StepArgs<float> &, int, int, int,
-                                              const EpiArgs<float> &, hipStream_t, int);
-template hipError_t launch_stencil_epi<double>(int, const StepArgs<double> &, int, int, int,
+template hipError_t launch_stencil_epi<float>(int, const StepArgs<float> &, const InjMap<float> &,
+                                              int, int, int, const EpiArgs<float> &, hipStream_t,
+                                              int);
+template hipError_t launch_stencil_epi<double>(int, const StepArgs<double> &,
+                                               const InjMap<double> &, int, int, int,
                                                const EpiArgs<double> &, hipStream_t, int);
 
 // Injection whose increment d = dt^2 acc / (m + a) also updates an
@@ -718,14 +765,23 @@ __global__ __launch_bounds__(256) void k_inject(StepArgs<T> a, PointTables<T> pt
   field[i] += a.dt2 * acc / (a.m[i] + sponge_a(a, z, y, x));
 }
 
+// A block's levels are all in the ring when it ends, so one launch samples
+// them (a launch per step cost 4.6 us of a 128^3 step's 18).
 template <typename T>
-__global__ __launch_bounds__(256) void k_sample(PointTables<T> pt, const T *__restrict__ field,
-                                                T *__restrict__ out) {
+__global__ __launch_bounds__(256) void k_sample_block(PointTables<T> pt, const T *__restrict__ ring,
+                                                      const T *__restrict__ ring2, int64_t ld,
+                                                      int R, int s0, int dir, T *__restrict__ out) {
   const int p = blockIdx.x * 256 + threadIdx.x;
   if (p >= pt.npts) return;
+  const int t = blockIdx.y;
+  const int64_t slot = (int64_t)((s0 + t + 2) % R) * ld;  // level s0 + 1 + t
+  const T *f = ring + slot, *f2 = ring2 ? ring2 + slot : nullptr;
   T s = T(0);
-  for (int j = pt.soff[p]; j < pt.soff[p + 1]; ++j) s += pt.sw[j] * field[pt.sidx[j]];
-  out[p] = s;
+  for (int j = pt.soff[p]; j < pt.soff[p + 1]; ++j) {
+    const T v = f2 ? f[pt.sidx[j]] + f2[pt.sidx[j]] : f[pt.sidx[j]];
+    s = fma_t(pt.sw[j], v, s);
+  }
+  out[(int64_t)t * dir * pt.npts + p] = s;
 }
 
 template <typename T>
@@ -738,10 +794,11 @@ hipError_t launch_inject(const StepArgs<T> &a, const PointTables<T> &pt, const T
 }
 
 template <typename T>
-hipError_t launch_sample(const PointTables<T> &pt, const T *field, T *out, hipStream_t st) {
-  if (pt.npts <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_sample<T>), dim3((pt.npts + 255) / 256), dim3(256), 0, st, pt, field,
-                     out);
+hipError_t launch_sample_block(const PointTables<T> &pt, const T *ring, const T *ring2, int64_t ld,
+                               int R, int s0, int kb, int dir, T *out, hipStream_t st) {
+  if (pt.npts <= 0 || kb <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_sample_block<T>), dim3((pt.npts + 255) / 256, kb), dim3(256), 0, st, pt,
+                     ring, ring2, ld, R, s0, dir, out);
   return hipGetLastError();
 }
 
@@ -749,12 +806,14 @@ hipError_t launch_sample(const PointTables<T> &pt, const T *field, T *out, hipSt
 // batched shots
 // ---------------------------------------------------------------------------
 template <typename T>
-hipError_t launch_stencil_batched(const ShotStep<T> *shots, const int4 *tiles, int ntiles, int s,
-                                  int variant, bool ragged, hipStream_t st, int rev) {
+hipError_t launch_stencil_batched(const ShotStep<T> *shots, const ShotIO<T> *io, bool mapped,
+                                  const int4 *tiles, int ntiles, int s, int n, int variant,
+                                  bool ragged, hipStream_t st, int rev) {
   if (ntiles <= 0) return hipSuccess;
   const bool nt = variant >= 7 && variant <= 12;
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(ntiles), dim3(256), 0, st, shots, tiles, ntiles, s, rev);
+    hipLaunchKernelGGL(kern, dim3(ntiles), dim3(256), 0, st, shots, io, (int)mapped, tiles,
+                       ntiles, s, n, rev);
   };
   if (ragged) {
     if (nt) go(k_stencil3d_batched<T, 64, 16, 1, true, true>);
@@ -795,14 +854,15 @@ __global__ __launch_bounds__(256) void k_inject_batched(const ShotStep<T> *__res
 template <typename T>
 __global__ __launch_bounds__(256) void k_sample_batched(const ShotStep<T> *__restrict__ shots,
                                                         const ShotIO<T> *__restrict__ io,
-                                                        BatchPoints<T> pt, int s, int n) {
+                                                        BatchPoints<T> pt, int s0) {
   const int p = blockIdx.x * 256 + threadIdx.x;
   if (p >= pt.npts) return;
   const int sh = pt.sshot[p];
   if (!io[sh].out) return;
-  const T *field = next_level(shots[sh], s);
+  const int n = s0 + blockIdx.y;
+  const T *field = next_level(shots[sh], n);
   T v = T(0);
-  for (int j = pt.soff[p]; j < pt.soff[p + 1]; ++j) v += pt.sw[j] * field[pt.sidx[j]];
+  for (int j = pt.soff[p]; j < pt.soff[p + 1]; ++j) v = fma_t(pt.sw[j], field[pt.sidx[j]], v);
   io[sh].out[(int64_t)n * io[sh].n_smp + pt.slocal[p]] = v;
 }
 
@@ -816,14 +876,15 @@ hipError_t launch_inject_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
 }
 template <typename T>
 hipError_t launch_sample_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
-                                 const BatchPoints<T> &pt, int s, int n, hipStream_t st) {
-  if (pt.npts <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_sample_batched<T>), dim3((pt.npts + 255) / 256), dim3(256), 0, st, shots,
-                     io, pt, s, n);
+                                 const BatchPoints<T> &pt, int s0, int kb, hipStream_t st) {
+  if (pt.npts <= 0 || kb <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_sample_batched<T>), dim3((pt.npts + 255) / 256, kb), dim3(256), 0, st,
+                     shots, io, pt, s0);
   return hipGetLastError();
 }
-template hipError_t launch_stencil_batched<float>(const ShotStep<float> *, const int4 *, int, int,
-                                                  int, bool, hipStream_t, int);
+template hipError_t launch_stencil_batched<float>(const ShotStep<float> *, const ShotIO<float> *,
+                                                  bool, const int4 *, int, int, int, int, bool,
+                                                  hipStream_t, int);
 template hipError_t launch_inject_batched<float>(const ShotStep<float> *, const ShotIO<float> *,
                                                  const BatchPoints<float> &, int, int,
                                                  hipStream_t);
@@ -835,9 +896,11 @@ template hipError_t launch_inject<float>(const StepArgs<float> &, const PointTab
                                          const float *, float *, hipStream_t);
 template hipError_t launch_inject<double>(const StepArgs<double> &, const PointTables<double> &,
                                           const double *, double *, hipStream_t);
-template hipError_t launch_sample<float>(const PointTables<float> &, const float *, float *,
-                                         hipStream_t);
-template hipError_t launch_sample<double>(const PointTables<double> &, const double *, double *,
-                                          hipStream_t);
+template hipError_t launch_sample_block<float>(const PointTables<float> &, const float *,
+                                               const float *, int64_t, int, int, int, int, float *,
+                                               hipStream_t);
+template hipError_t launch_sample_block<double>(const PointTables<double> &, const double *,
+                                                const double *, int64_t, int, int, int, int,
+                                                double *, hipStream_t);
 
 }  // namespace rtm

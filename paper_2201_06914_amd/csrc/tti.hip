@@ -205,17 +205,6 @@ __global__ __launch_bounds__(256) void k_tti_adj(TtiArgs<T> t, const T *__restri
   t.qn[i] = damped_update(a, t.q[i], t.qp[i], m, hz2, damp);
 }
 
-// out[n] = Pr (p + q): the adjoint of injecting into both fields
-template <typename T>
-__global__ __launch_bounds__(256) void k_sample_sum(PointTables<T> pt, const T *__restrict__ f1,
-                                                    const T *__restrict__ f2, T *__restrict__ out) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= pt.npts) return;
-  T s = T(0);
-  for (int j = pt.soff[p]; j < pt.soff[p + 1]; ++j) s += pt.sw[j] * (f1[pt.sidx[j]] + f2[pt.sidx[j]]);
-  out[p] = s;
-}
-
 static unsigned cells_grid(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 template <typename T>
@@ -243,15 +232,6 @@ hipError_t launch_tti_step(const StepArgs<T> &a, double h, bool adjoint, const T
     hipLaunchKernelGGL((k_tti_flux<T>), dim3(nb), dim3(256), 0, st, t, F);
     hipLaunchKernelGGL((k_tti_adj<T>), dim3(nb), dim3(256), 0, st, t, (const T *)F);
   }
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_sample_sum(const PointTables<T> &pt, const T *f1, const T *f2, T *out,
-                             hipStream_t st) {
-  if (pt.npts <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_sample_sum<T>), dim3((pt.npts + 255) / 256), dim3(256), 0, st, pt, f1,
-                     f2, out);
   return hipGetLastError();
 }
 
@@ -454,9 +434,5 @@ template hipError_t launch_tti_step<double>(const StepArgs<double> &, double, bo
                                             const double *, const double *, const double *,
                                             const double *, double *, double *, double *, int,
                                             int, hipStream_t);
-template hipError_t launch_sample_sum<float>(const PointTables<float> &, const float *,
-                                             const float *, float *, hipStream_t);
-template hipError_t launch_sample_sum<double>(const PointTables<double> &, const double *,
-                                              const double *, double *, hipStream_t);
 
 }  // namespace rtm
