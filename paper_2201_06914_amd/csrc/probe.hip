@@ -14,12 +14,13 @@
 //                 MFMAs, 16-bit mantissa), or (F16S) scaled by a power of two
 //                 per 16-step chunk and rounded to float16 (11-bit mantissa,
 //                 v_mfma_f32_32x32x16_f16), the partial product rescaled
-//                 exactly between chunks.  One wave owns one 32-cell tile and
-//                 up to 128 probe rows at a time; Z sits in LDS in A-operand
-//                 order.
-//   k_probe_vec   FP64 / FP32 FMA path (any real Z), thread per cell, 32
-//                 probe rows per pass; the accumulation order is the per-step
-//                 order bar += z_n s^n.
+//                 exactly between chunks; or (F32) kept in FP32 with FP32
+//                 products and sums (v_mfma_f32_32x32x2_f32).  One wave owns
+//                 one 32-cell tile and up to 128 probe rows at a time; Z sits
+//                 in LDS in A-operand order.
+//   k_probe_vec   FMA path (any real Z): FP64, and FP32 blocks whose probe
+//                 operand exceeds the MFMA path's LDS.  Thread per cell, 32
+//                 probe rows per pass, in the per-step order bar += z_n s^n.
 #include "ring.h"
 
 namespace rtm {
@@ -27,6 +28,17 @@ namespace rtm {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
+
+// one lane's operand of a 16-step chunk: 8 values
+template <int OP>
+struct Operand {
+  typedef bf16x8 type;
+};
+template <>
+struct Operand<OP_F32> {
+  typedef f32x8 type;
+};
 
 __device__ __forceinline__ int64_t bar_index(int64_t x, int i, int r) {
   return ((x >> 5) * r + i) * 32 + (x & 31);
@@ -42,6 +54,8 @@ __global__ __launch_bounds__(256) void k_probe_vec(ProbeArgs<T> p, const ZT *__r
   T *zs = reinterpret_cast<T *>(smem_raw);  // [kb][RC]
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const bool valid = c < p.N;
+  if (p.first && !valid && c < (p.N + 31) / 32 * 32)  // padding cells hold zeros
+    for (int i = 0; i < p.r; ++i) p.bar[bar_index(c, i, p.r)] = T(0);
   for (int r0 = 0; r0 < p.r; r0 += RC) {
     const int rc = min(RC, p.r - r0);
     __syncthreads();
@@ -53,7 +67,7 @@ __global__ __launch_bounds__(256) void k_probe_vec(ProbeArgs<T> p, const ZT *__r
     if (!valid) continue;
     T acc[RC];
 #pragma unroll
-    for (int i = 0; i < RC; ++i) acc[i] = i < rc ? p.bar[bar_index(c, r0 + i, p.r)] : T(0);
+    for (int i = 0; i < RC; ++i) acc[i] = i < rc && !p.first ? p.bar[bar_index(c, r0 + i, p.r)] : T(0);
     for (int t = 0; t < p.kb; ++t) {
       const T s = probed(p, t, c);
 #pragma unroll
@@ -150,10 +164,36 @@ __device__ __forceinline__ void fill_probe_lds_q(const ProbeArgs<float> &p, cons
   __syncthreads();
 }
 
+// FP32 operands: MFMA q of a chunk (v_mfma_f32_32x32x2_f32: A lane l holds
+// row l % 32 of inner index l / 32) multiplies steps ks 16 + q (lanes 0..31)
+// and ks 16 + 8 + q, so a lane's 8 values are the steps of the bf16 order.
+template <typename ZT>
+__device__ __forceinline__ void fill_probe_lds_f32(const ProbeArgs<float> &p, const ZT *Z, int MT,
+                                                   int KS, f32x8 *ldsA) {
+  for (int e = threadIdx.x; e < MT * KS * 64; e += blockDim.x) {
+    const int l = e & 63;
+    const int ks = (e >> 6) % KS;
+    const int mt = (e >> 6) / KS;
+    const int i = mt * 32 + (l & 31);
+    f32x8 v;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int t = ks * 16 + 8 * (l >> 5) + q;
+      v[q] = t < p.kb && i < p.r ? (float)Z[(int64_t)(p.zrow0 + p.zdir * t) * p.r + i] : 0.f;
+    }
+    ldsA[e] = v;
+  }
+  __syncthreads();
+}
+
 template <bool QF, int OP>
 __device__ __forceinline__ void fill_a(const ProbeArgs<float> &p, const void *Z, int MT, int KS,
-                                       bf16x8 *ldsA) {
-  if constexpr (QF) fill_probe_lds_q(p, static_cast<const float *>(Z), MT, KS, ldsA);
+                                       typename Operand<OP>::type *ldsA) {
+  if constexpr (OP == OP_F32 && QF)
+    fill_probe_lds_f32(p, static_cast<const float *>(Z), MT, KS, ldsA);
+  else if constexpr (OP == OP_F32)
+    fill_probe_lds_f32(p, static_cast<const int8_t *>(Z), MT, KS, ldsA);
+  else if constexpr (QF) fill_probe_lds_q(p, static_cast<const float *>(Z), MT, KS, ldsA);
   else fill_probe_lds<OP>(p, static_cast<const int8_t *>(Z), MT, KS, ldsA);
 }
 
@@ -163,36 +203,46 @@ __device__ __forceinline__ void fill_a(const ProbeArgs<float> &p, const void *Z,
 // 16 x 32 values (the whole wave) share one power-of-two scale 2^-e with e
 // from their largest magnitude (below 2^15 after scaling, so every value is
 // in float16 range), and hi holds the float16 rounding of the scaled values;
-// e is wave-uniform.  FAST: no masking needed.
-template <int MODE, int OP, bool FAST>
+// e is wave-uniform.  FAST: the cell is inside the grid.  FULL: kb is 16 KS;
+// else steps at or past kb give zeros (their loads go to the block's last
+// level, which is valid).
+template <int MODE, int OP, bool FAST, bool FULL>
 __device__ __forceinline__ void probe_operand(const ProbeArgs<float> &p, int ks, int half,
-                                              int64_t c, bool valid, bf16x8 &bhi, bf16x8 &blo,
-                                              int &e) {
+                                              int64_t c, bool valid,
+                                              typename Operand<OP>::type &bhi,
+                                              typename Operand<OP>::type &blo, int &e) {
   const int tb = ks * 16 + 8 * half;
-  float sv[8];
+  float sv[8];                 // the probed values: dv * scale, rounded
+  float dv[8];
+  const float scale = MODE == PROBE_UTT ? p.inv_dt2 : 1.f;
   if (MODE == PROBE_UTT) {
     float lv[10];
 #pragma unroll
     for (int q = 0; q < 10; ++q) {
-      const int t = tb + q - 1;  // level s0 + t, inside [-1, kb] whenever FAST
-      const bool ok = FAST || (valid && t >= -1 && t <= p.kb);
-      lv[q] = ok ? ring_level(p, p.s0 + t)[c] : 0.f;
+      // level s0 + t, inside [-1, kb]
+      const int t = FULL ? tb + q - 1 : min(tb + q - 1, p.kb);
+      lv[q] = FAST || valid ? ring_level(p, p.s0 + t)[c] : 0.f;
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const float d2 = (lv[q + 2] - 2.f * lv[q + 1] + lv[q]) * p.inv_dt2;
-      sv[q] = (FAST || tb + q < p.kb) ? d2 : 0.f;
+      const float d2 = __builtin_fmaf(-2.f, lv[q + 1], lv[q + 2]) + lv[q];
+      dv[q] = FULL || tb + q < p.kb ? d2 : 0.f;
+      sv[q] = dv[q] * scale;
     }
   } else {
+    const int shift = p.mode == PROBE_NEW ? 1 : 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int t = tb + q;
-      const int lev = p.s0 + t + (MODE == PROBE_NEW ? 1 : 0);
-      const bool ok = FAST || (valid && t < p.kb);
-      sv[q] = ok ? ring_level(p, lev)[c] : 0.f;
+      const int t = FULL ? tb + q : min(tb + q, p.kb - 1);
+      const float v = FAST || valid ? ring_level(p, p.s0 + t + shift)[c] : 0.f;
+      sv[q] = dv[q] = FULL || tb + q < p.kb ? v : 0.f;
     }
   }
-  if constexpr (OP == OP_F16S) {
+  if constexpr (OP == OP_F32) {
+    e = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) bhi[q] = sv[q];
+  } else if constexpr (OP == OP_F16S) {
     float mx = 0.f;
 #pragma unroll
     for (int q = 0; q < 8; ++q) mx = fmaxf(mx, fabsf(sv[q]));
@@ -210,7 +260,9 @@ __device__ __forceinline__ void probe_operand(const ProbeArgs<float> &p, int ks,
     for (int q = 0; q < 8; ++q) {
       const __bf16 hb = (__bf16)sv[q];
       bhi[q] = hb;
-      if (OP == OP_BF16X2) blo[q] = (__bf16)(sv[q] - (float)hb);
+      // the remainder of the unrounded product, spelled out so that every
+      // kernel rounds alike
+      if (OP == OP_BF16X2) blo[q] = (__bf16)__builtin_fmaf(dv[q], scale, -(float)hb);
     }
   }
 }
@@ -218,9 +270,16 @@ __device__ __forceinline__ void probe_operand(const ProbeArgs<float> &p, int ks,
 // acc += A * B for one 16-step chunk, in the operand type of OP (QF: real
 // probes split into hi + lo A operands, B hi only)
 template <int OP, bool QF>
-__device__ __forceinline__ f32x16 chunk_mfma(const bf16x8 &a, const bf16x8 &alo, const bf16x8 &bhi,
-                                             const bf16x8 &blo, f32x16 acc) {
-  if constexpr (OP == OP_F16S) {
+__device__ __forceinline__ f32x16 chunk_mfma(const typename Operand<OP>::type &a,
+                                             const typename Operand<OP>::type &alo,
+                                             const typename Operand<OP>::type &bhi,
+                                             const typename Operand<OP>::type &blo, f32x16 acc) {
+  if constexpr (OP == OP_F32) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], bhi[q], acc, 0, 0, 0);
+    return acc;
+  } else if constexpr (OP == OP_F16S) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
                                                   __builtin_bit_cast(f16x8, bhi), acc, 0, 0, 0);
   } else {
@@ -231,43 +290,42 @@ __device__ __forceinline__ f32x16 chunk_mfma(const bf16x8 &a, const bf16x8 &alo,
   }
 }
 
-// Fast kernel: full 32-cell tiles [0, tile_end), kb == 16 KS, MT % MTC == 0 -
-// no load or store is masked.  MTC row tiles (32 probes each) are accumulated
-// together, so their 16 x MTC loads per lane are in flight at once.
-// NTB: the compressed fields (Ubar / Vbar, the fused adjoint's forward field)
-// are read and written with the non-temporal hint (each is touched once per
-// block)
-template <typename T, bool NT>
-__device__ __forceinline__ T ldb(const T *p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-template <typename T, bool NT>
-__device__ __forceinline__ void stb(T *p, T v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
-
+// Fast kernel: full 32-cell tiles [0, tile_end).  MTC row tiles (32 probes
+// each) are accumulated together, so their 16 x MTC loads per lane are in
+// flight at once.  MTC > 1: MT % MTC == 0, whole row tiles and blocks of 16 KS
+// steps, nothing masked.  MTC = 1: any block, r a multiple of 8 (rows are
+// masked in whole register groups of 8, wave-uniform); masks in the wider
+// kernels would cost them waves.  The compressed fields (Ubar / Vbar, the fused
+// adjoint's forward field) are read and written with the non-temporal hint
+// (each is touched once per block).  FIRST: the field starts from zero and is
+// not read (a template, not a branch: merging loaded and zero accumulators took
+// the k = 32 kernel from 90 to 138 VGPRs).
 constexpr int kQueueChunk = 4;  // tiles per work-queue grab
 
 __global__ void k_queue_reset(int *q) {
   if (threadIdx.x == 0) *q = 0;
 }
 
-template <int KS, int OP, int MODE, bool FUSED, int MTC, bool QF, bool NTB = false>
+template <int KS, int OP, int MODE, bool FUSED, int MTC, bool QF, bool FIRST = false>
 __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
                                                          const void *__restrict__ Z, int MT,
                                                          const float *__restrict__ Uf,
                                                          float *__restrict__ img, float scale,
                                                          int64_t tile_end) {
-  extern __shared__ bf16x8 ldsA[];
+  typedef typename Operand<OP>::type Op;
+  extern __shared__ __attribute__((aligned(32))) unsigned char smem_a[];
+  Op *ldsA = reinterpret_cast<Op *>(smem_a);
   fill_a<QF, OP>(p, Z, MT, KS, ldsA);
-  const int alo_off = MT * KS * 64;  // QF: the lo halves of A
+  constexpr bool kLo = QF && OP != OP_F32;  // the lo halves of A follow
+  const int alo_off = MT * KS * 64;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int col = lane & 31;
   const int half = lane >> 5;
   const int loff = half * 4 * 32 + col;
+  // register group v / 4 of row tile mt: rows inside r
+  constexpr bool kAll = MTC > 1;
+  auto rows = [&](int mt, int v) { return kAll || mt * 32 + 8 * (v >> 2) < p.r; };
   // tiles: each wave strides over them, or (p.queue) takes chunks of kQueueChunk
   // consecutive tiles from a counter, so the tiles in flight stay in one band
   // that moves through the field in order; every wave leaves once a chunk
@@ -286,12 +344,12 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
     // blocks (KS >= 4): build each right before its MFMAs to bound registers
     constexpr bool kEarly = KS <= 2;
     constexpr bool F16 = OP == OP_F16S;
-    bf16x8 bhi_e[kEarly ? KS : 1], blo_e[kEarly ? KS : 1];
+    Op bhi_e[kEarly ? KS : 1], blo_e[kEarly ? KS : 1];
     int e_e[kEarly ? KS : 1];
     if (kEarly) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        probe_operand<MODE, OP, true>(p, ks, half, c, true, bhi_e[kEarly ? ks : 0],
+        probe_operand<MODE, OP, true, kAll>(p, ks, half, c, true, bhi_e[kEarly ? ks : 0],
                                       blo_e[kEarly ? ks : 0], e_e[kEarly ? ks : 0]);
     }
     float part = 0.f;
@@ -307,7 +365,10 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             acc[j][v] = 0.f;
-            uf[(FUSED || F16) ? j : 0][v] = ldb<float, NTB>(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32);
+            uf[(FUSED || F16) ? j : 0][v] =
+                rows(mt0 + j, v) && !FIRST
+                    ? __builtin_nontemporal_load(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32)
+                    : 0.f;
           }
       } else {
         const float *Ut = p.bar + tbase + mt0 * 32 * 32 + loff;
@@ -315,7 +376,9 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
         for (int j = 0; j < MTC; ++j)
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            acc[j][v] = ldb<float, NTB>(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32);
+            acc[j][v] = rows(mt0 + j, v) && !FIRST
+                            ? __builtin_nontemporal_load(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32)
+                            : 0.f;
       }
       int ecur = 0;  // F16S: acc holds the block's partial product in units of 2^ecur
       // step chunks in groups of at most four, the groups in a rolled loop:
@@ -326,7 +389,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
 #pragma unroll
         for (int kk = 0; kk < KSB; ++kk) {
           const int ks = kEarly ? kk : ks0 + kk;
-          bf16x8 bhi, blo;
+          Op bhi, blo;
           int eks;
           if (kEarly) {
             bhi = bhi_e[kEarly ? kk : 0];
@@ -334,7 +397,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
             eks = e_e[kEarly ? kk : 0];
           } else {
             __builtin_amdgcn_sched_barrier(0);
-            probe_operand<MODE, OP, true>(p, ks, half, c, true, bhi, blo, eks);
+            probe_operand<MODE, OP, true, kAll>(p, ks, half, c, true, bhi, blo, eks);
           }
           if (F16) {  // move the partial product to this chunk's units (exact)
 #pragma unroll
@@ -346,7 +409,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
 #pragma unroll
           for (int j = 0; j < MTC; ++j) {
             const int ai = ((mt0 + j) * KS + ks) * 64 + lane;
-            acc[j] = chunk_mfma<OP, QF>(ldsA[ai], QF ? ldsA[alo_off + ai] : ldsA[ai], bhi, blo,
+            acc[j] = chunk_mfma<OP, QF>(ldsA[ai], kLo ? ldsA[alo_off + ai] : ldsA[ai], bhi, blo,
                                         acc[j]);
           }
         }
@@ -371,7 +434,8 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
         for (int j = 0; j < MTC; ++j)
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            stb<float, NTB>(Uo + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32, acc[j][v]);
+            if (rows(mt0 + j, v))
+              __builtin_nontemporal_store(acc[j][v], Uo + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32);
       }
     }
     if (FUSED) {
@@ -382,7 +446,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
 }
 
 // Edge kernel: tiles [tile_begin, ntiles) with any masking (ragged last tile,
-// a block shorter than 16 KS, r not a multiple of 32).  One row tile at a time.
+// r not a multiple of 8) and ordinary accesses.  One row tile at a time.
 template <int KS, int OP, int MODE, bool FUSED, bool QF>
 __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
                                                          const void *__restrict__ Z, int MT,
@@ -390,8 +454,11 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
                                                          float *__restrict__ img, float scale,
                                                          int64_t tile_begin) {
   constexpr bool F16 = OP == OP_F16S;
-  extern __shared__ bf16x8 ldsA[];
+  typedef typename Operand<OP>::type Op;
+  extern __shared__ __attribute__((aligned(32))) unsigned char smem_a[];
+  Op *ldsA = reinterpret_cast<Op *>(smem_a);
   fill_a<QF, OP>(p, Z, MT, KS, ldsA);
+  constexpr bool kLo = QF && OP != OP_F32;
   const int alo_off = MT * KS * 64;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -404,11 +471,11 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
     const int64_t c = tile * 32 + col;
     const bool valid = c < p.N;
     const int64_t tbase = tile * (int64_t)p.r * 32;
-    bf16x8 bhi[KS], blo[KS];
+    Op bhi[KS], blo[KS];
     int eks[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      probe_operand<MODE, OP, false>(p, ks, half, c, valid, bhi[ks], blo[ks], eks[ks]);
+      probe_operand<MODE, OP, false, false>(p, ks, half, c, valid, bhi[ks], blo[ks], eks[ks]);
     float part = 0.f;
     for (int mt = 0; mt < MT; ++mt) {
       const float *Ut = (FUSED ? Uf : p.bar) + tbase + mt * 32 * 32 + loff;
@@ -417,7 +484,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int rr = 8 * (v >> 2) + (v & 3);
-        const bool ok = valid && mt * 32 + rr + 4 * half < p.r;
+        const bool ok = valid && mt * 32 + rr + 4 * half < p.r && (FUSED || !p.first);
         const float val = ok ? Ut[rr * 32] : 0.f;
         acc[v] = (FUSED || F16) ? 0.f : val;
         uf[v] = val;
@@ -431,7 +498,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
           ecur = eks[ks];
         }
         const int ai = (mt * KS + ks) * 64 + lane;
-        acc = chunk_mfma<OP, QF>(ldsA[ai], QF ? ldsA[alo_off + ai] : ldsA[ai], bhi[ks], blo[ks],
+        acc = chunk_mfma<OP, QF>(ldsA[ai], kLo ? ldsA[alo_off + ai] : ldsA[ai], bhi[ks], blo[ks],
                                  acc);
       }
       if (F16) {
@@ -447,8 +514,8 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
         const int rr = 8 * (v >> 2) + (v & 3);
         if (FUSED)
           part += uf[v] * acc[v];
-        else if (valid && mt * 32 + rr + 4 * half < p.r)
-          Uo[rr * 32] = acc[v];
+        else if ((valid || p.first) && mt * 32 + rr + 4 * half < p.r)
+          Uo[rr * 32] = acc[v];  // padding cells: zeros, written once
       }
     }
     if (FUSED) {
@@ -510,7 +577,8 @@ struct FuseArgs {
 template <int KS, int OP, int MODE, bool FUSED, bool QF>
 static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int MT,
                                  const FuseArgs &f, hipStream_t st) {
-  const size_t shm = sizeof(bf16x8) * (size_t)MT * KS * 64 * (QF ? 2 : 1);
+  const size_t shm = (OP == OP_F32 ? sizeof(f32x8) : sizeof(bf16x8) * (QF ? 2 : 1)) * (size_t)MT *
+                     KS * 64;
   const int64_t ntiles = (p.N + 31) / 32;
   const int64_t nfull = p.N / 32;
   const int set = g_probe_grid[FUSED ? 1 : 0];
@@ -540,27 +608,30 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
   } else {
     pq.queue = nullptr;
   }
-  // the fast kernel reads and writes whole 32-row tiles and whole 16-step chunks
-  const bool fastk = p.kb == 16 * KS && p.r % 32 == 0;
+  // four row tiles at a time where they divide (the fused kernel, which also
+  // holds the forward field: two), else one (r = 32, 48, 96; short blocks).
+  // All are bound by HBM: r = 128, k = 32 on 320 x 448 x 448 12.8 ms (5.8
+  // TB/s), r = 32 on 100^3 59 us (6.6 TB/s; the edge kernel 61 us)
   int64_t done = 0;
-  if (fastk && nfull > 0 && MT % 4 == 0 && !FUSED) {
-    if (g_probe_nt)
-      hipLaunchKernelGGL((k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF, true>),
-                         dim3(grid_for(nfull)), dim3(256), shm, st, pq, Z, MT, f.Uf, f.img, f.scale,
-                         nfull);
-    else
-      hipLaunchKernelGGL((k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF>), dim3(grid_for(nfull)),
-                         dim3(256), shm, st, pq, Z, MT, f.Uf, f.img, f.scale, nfull);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid_for(nfull)), dim3(256), shm, st, pq, Z, MT, f.Uf, f.img,
+                       f.scale, nfull);
     done = nfull;
-  } else if (fastk && nfull > 0 && MT % 2 == 0) {
-    if (g_probe_nt)
-      hipLaunchKernelGGL((k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF, true>),
-                         dim3(grid_for(nfull)), dim3(256), shm, st, pq, Z, MT, f.Uf, f.img, f.scale,
-                         nfull);
-    else
-      hipLaunchKernelGGL((k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF>), dim3(grid_for(nfull)),
-                         dim3(256), shm, st, pq, Z, MT, f.Uf, f.img, f.scale, nfull);
-    done = nfull;
+  };
+  if (g_probe_nt && p.r % 8 == 0 && nfull > 0) {
+    const bool whole = p.r % 32 == 0 && p.kb == 16 * KS;
+    if (whole && MT % 4 == 0 && !FUSED) {
+      if constexpr (!FUSED) {
+        if (p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF, true>);
+        else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF>);
+      }
+    } else if (whole && MT % 2 == 0) {
+      if (!FUSED && p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF, !FUSED>);
+      else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF>);
+    } else {
+      if (!FUSED && p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 1, QF, !FUSED>);
+      else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 1, QF>);
+    }
   }
   if (done < ntiles)
     hipLaunchKernelGGL((k_probe_mfma_edge<KS, OP, MODE, FUSED, QF>), dim3(grid_for(ntiles - done)),
@@ -570,21 +641,27 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
 template <int KS, int OP, bool QF>
 static void launch_mfma_mode(const ProbeArgs<float> &p, const void *Z, int MT,
                              const FuseArgs &f, hipStream_t st) {
-  if (f.img) {  // fused imaging: adjoint levels only
-    launch_probe_kernels<KS, OP, PROBE_NEW, true, QF>(p, Z, MT, f, st);
-    return;
+  // MODE: u_tt or one level (which one: p.mode)
+  if constexpr (OP != OP_F32) {
+    if (f.img) {  // fused imaging: adjoint levels only
+      launch_probe_kernels<KS, OP, PROBE_NEW, true, QF>(p, Z, MT, f, st);
+      return;
+    }
   }
-  switch (p.mode) {
-    case PROBE_UTT: launch_probe_kernels<KS, OP, PROBE_UTT, false, QF>(p, Z, MT, f, st); break;
-    case PROBE_NEW: launch_probe_kernels<KS, OP, PROBE_NEW, false, QF>(p, Z, MT, f, st); break;
-    default: launch_probe_kernels<KS, OP, PROBE_CUR, false, QF>(p, Z, MT, f, st);
-  }
+  if (p.mode == PROBE_UTT)
+    launch_probe_kernels<KS, OP, PROBE_UTT, false, QF>(p, Z, MT, f, st);
+  else
+    launch_probe_kernels<KS, OP, PROBE_NEW, false, QF>(p, Z, MT, f, st);
 }
 
 template <int KS>
 static void launch_mfma_ks(const ProbeArgs<float> &p, const void *Z, bool zf32, int op,
                            int MT, const FuseArgs &f, hipStream_t st) {
-  if (zf32)
+  if (op == OP_F32 && zf32)
+    launch_mfma_mode<KS, OP_F32, true>(p, Z, MT, f, st);
+  else if (op == OP_F32)
+    launch_mfma_mode<KS, OP_F32, false>(p, Z, MT, f, st);
+  else if (zf32)
     launch_mfma_mode<KS, OP_BF16X2, true>(p, Z, MT, f, st);
   else if (op == OP_BF16X2)
     launch_mfma_mode<KS, OP_BF16X2, false>(p, Z, MT, f, st);
@@ -594,14 +671,20 @@ static void launch_mfma_ks(const ProbeArgs<float> &p, const void *Z, bool zf32, 
     launch_mfma_mode<KS, OP_BF16, false>(p, Z, MT, f, st);
 }
 
-// op: OP_BF16, OP_BF16X2 or OP_F16S; real probes (zf32) need OP_BF16X2
+// op: OP_BF16, OP_BF16X2, OP_F16S or OP_F32 (FP32 products, no fused imaging);
+// real probes (zf32) need OP_BF16X2 or OP_F32.  FP32 products on the matrix
+// cores: r = 48, k = 32 on 150 x 200 x 226 0.65 ms (5.4 TB/s), where the vector
+// kernel, which reads the levels once per 32 rows, took 1.34.  OP_F32 blocks whose operand
+// takes more than 64 KB of LDS run the vector kernel: two workgroups per CU
+// (160 KB) keep its loads in flight.
 hipError_t launch_probe_mfma(const ProbeArgs<float> &p, const void *Z, bool zf32, int op,
                              const float *Uf, float *img, float scale, hipStream_t st) {
   const FuseArgs f{Uf, img, scale};
   const int MT = (p.r + 31) / 32;
   int KS = (p.kb + 15) / 16;
   KS = KS <= 1 ? 1 : KS <= 2 ? 2 : KS <= 4 ? 4 : 8;
-  if (p.kb > 128 || (zf32 && op != OP_BF16X2)) return hipErrorInvalidValue;
+  if (op == OP_F32 && (p.kb > 128 || MT * KS > 32)) return launch_probe_vec<float>(p, Z, !zf32, st);
+  if (p.kb > 128 || (zf32 && op != OP_BF16X2 && op != OP_F32)) return hipErrorInvalidValue;
   switch (KS) {
     case 1: launch_mfma_ks<1>(p, Z, zf32, op, MT, f, st); break;
     case 2: launch_mfma_ks<2>(p, Z, zf32, op, MT, f, st); break;

@@ -135,7 +135,10 @@ static bool mfma_probe(rtm_dtype pd) {
   return pd == RTM_BF16 || pd == RTM_BF16X2 || pd == RTM_F16S;
 }
 static int probe_op(rtm_dtype pd) {
-  return pd == RTM_BF16X2 ? OP_BF16X2 : pd == RTM_F16S ? OP_F16S : OP_BF16;
+  return pd == RTM_BF16X2 ? OP_BF16X2
+         : pd == RTM_F16S ? OP_F16S
+         : pd == RTM_F32  ? OP_F32
+                          : OP_BF16;
 }
 
 static void place(size_t &cur, Region &r, size_t bytes) {
@@ -588,7 +591,6 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
     HIP_TRY(launch_fill<T>(level(nb), P->N, T(0), st));
   }
   T *bar = static_cast<T *>(io.bar);
-  if (bar && nb == 0) HIP_TRY(launch_fill<T>(bar, (int64_t)d.r * P->Npad, T(0), st));
   const T *inj_vals = static_cast<const T *>(io.inj_vals);
   T *smp_out = static_cast<T *>(io.smp_out);
   int s0 = nb;
@@ -626,6 +628,7 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
       p.bar = bar;
       p.inv_dt2 = (T)(1.0 / (d.dt * d.dt));
       p.mode = io.mode;
+      p.first = s0 == 0;
       p.queue = reinterpret_cast<int *>(work + P->queue.off);
       if (io.sketch_Y) {
         ProbeArgs<T> ps = p;
@@ -639,13 +642,9 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
       TimedLaunch tp;
       prof_begin(io.adjoint ? KT_PROBE_ADJ : KT_PROBE, s, st, &tp);
       if constexpr (sizeof(T) == 4) {
-        if (mfma_probe(d.probe_dtype)) {
-          HIP_TRY(launch_probe_mfma(p, io.Z, io.zt == RTM_F32, probe_op(d.probe_dtype),
-                                    static_cast<const float *>(io.fuse_U),
-                                    static_cast<float *>(io.fuse_img), (float)io.fuse_scale, st));
-        } else {
-          HIP_TRY(launch_probe_vec<T>(p, io.Z, io.zt == RTM_I8, st));
-        }
+        HIP_TRY(launch_probe_mfma(p, io.Z, io.zt == RTM_F32, probe_op(d.probe_dtype),
+                                  static_cast<const float *>(io.fuse_U),
+                                  static_cast<float *>(io.fuse_img), (float)io.fuse_scale, st));
       } else {
         HIP_TRY(launch_probe_vec<T>(p, io.Z, io.zt == RTM_I8, st));
       }
@@ -1698,6 +1697,7 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
       p.bar = adj ? nullptr : static_cast<float *>(io[i].Ubar);
       p.inv_dt2 = (float)(1.0 / (d.dt * d.dt));
       p.mode = adj ? PROBE_NEW : PROBE_UTT;
+      p.first = s0 == 0;
       p.queue = reinterpret_cast<int *>(w + b->queue.off);
       HIP_TRY(launch_probe_mfma(p, io[i].Z, false, probe_op(d.probe_dtype),
                                 adj ? static_cast<const float *>(io[i].Ubar) : nullptr,
@@ -1713,7 +1713,6 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   for (int i = 0; i < b->ns; ++i) {
     HIP_TRY(launch_fill<float>(lvl(i, -1), b->P[i]->N, 0.f, st));
     HIP_TRY(launch_fill<float>(lvl(i, 0), b->P[i]->N, 0.f, st));
-    HIP_TRY(launch_fill<float>(static_cast<float *>(io[i].Ubar), (int64_t)d.r * b->P[i]->Npad, 0.f, st));
   }
   int s0 = 0;
   for (int s = 0; s < nt; ++s) {
@@ -1848,7 +1847,8 @@ extern "C" rtm_status fwi_gradient_batched(rtm_batch *b, const rtm_shot_io *io, 
           key = key_mix(key, v);
         }
       }
-  int variant = g_stencil_variant >= kStencilTiled ? g_stencil_variant : b->stream ? 7 : 1;
+  int variant = g_stencil_variant >= kStencilTiled ? g_stencil_variant
+                                                   : b->stream && !b->ragged ? 7 : 1;
   key = (key ^ (uint64_t)variant) * 1099511628211ull;
   key = (key ^ (uint64_t)(g_stencil_alternate + 64)) * 1099511628211ull;
   if (pk.host.size() > b->tab_bytes) return fail(RTM_E_WORKSPACE, "point tables do not fit");
@@ -1934,7 +1934,6 @@ static rtm_status run_tti_sweep(const rtm_plan *P, const TtiIO &io, const PointT
     HIP_TRY(launch_fill<T>(lv(ring, 0), N, T(0), st));
   }
   T *bar = static_cast<T *>(io.bar);
-  if (bar) HIP_TRY(launch_fill<T>(bar, 2 * barn, T(0), st));
   const T *vals = static_cast<const T *>(io.inj_vals);
   T *out = static_cast<T *>(io.smp_out);
   int s0 = 0;
@@ -1975,15 +1974,14 @@ static rtm_status run_tti_sweep(const rtm_plan *P, const TtiIO &io, const PointT
         p.bar = bar ? bar + f * barn : nullptr;
         p.inv_dt2 = (T)(1.0 / (d.dt * d.dt));
         p.mode = io.adjoint ? PROBE_NEW : PROBE_UTT;
+        p.first = s0 == 0;
         if constexpr (sizeof(T) == 4) {
-          if (mfma_probe(d.probe_dtype)) {
-            const float *Uf = io.fuse_img ? static_cast<const float *>(io.fuse_U) + f * barn : nullptr;
-            HIP_TRY(launch_probe_mfma(p, io.Z, io.zt == RTM_F32, probe_op(d.probe_dtype), Uf,
-                                      static_cast<float *>(io.fuse_img), (float)io.fuse_scale, st));
-            continue;
-          }
+          const float *Uf = io.fuse_img ? static_cast<const float *>(io.fuse_U) + f * barn : nullptr;
+          HIP_TRY(launch_probe_mfma(p, io.Z, io.zt == RTM_F32, probe_op(d.probe_dtype), Uf,
+                                    static_cast<float *>(io.fuse_img), (float)io.fuse_scale, st));
+        } else {
+          HIP_TRY(launch_probe_vec<T>(p, io.Z, io.zt == RTM_I8, st));
         }
-        HIP_TRY(launch_probe_vec<T>(p, io.Z, io.zt == RTM_I8, st));
       }
       s0 = s + 1;
     }

@@ -99,9 +99,9 @@ struct ShotIO {
   InjMap<T> map;  // vals: set per step from inj
 };
 
-// operand type of the MFMA probe path: bf16, bf16 hi + lo, or float16 with a
-// power-of-two scale per 16-step chunk and 32-cell tile
-enum ProbeOp : int { OP_BF16 = 0, OP_BF16X2 = 1, OP_F16S = 2 };
+// operand type of the MFMA probe path: bf16, bf16 hi + lo, float16 with a
+// power-of-two scale per 16-step chunk and 32-cell tile, or FP32
+enum ProbeOp : int { OP_BF16 = 0, OP_BF16X2 = 1, OP_F16S = 2, OP_F32 = 3 };
 enum ProbeMode : int {
   PROBE_CUR = 0,  // level s          (forward u^n)
   PROBE_UTT = 1,  // levels s-1, s, s+1, second difference / dt^2
@@ -123,6 +123,7 @@ struct ProbeArgs {
   T *bar;            // tile-major [ceil(N/32)][r][32]
   T inv_dt2;
   int mode;
+  bool first;        // bar starts from zero: written, not read (padding cells too)
   // optional work-queue counter (device int) for the probe launches that hand
   // out tiles in order; nullptr: each wave strides over the tiles
   int *queue = nullptr;

@@ -560,21 +560,25 @@ static TileShape tile_shape(int variant) {
 //   one or more whole chunks per column fill nearly all 256 CUs with one
 //   workgroup each, that is fastest (384 x 512 x 512: 2 chunks, 256
 //   workgroups, 261; 16-plane chunks 288), else chunks of 16 planes (320 x 448
-//   x 448: 173; 196 workgroups of 160 planes 181; v1 220).
+//   x 448: 173; 196 workgroups of 160 planes 181; v1 220).  Rows that are no
+//   multiple of the vector cut cache lines at every tile's edge, which the
+//   hint would send to HBM twice: ordinary accesses (400 x 400 x 401: 250
+//   against 275 non-temporal; 320 x 448 x 447: 257 against 274).
 constexpr int64_t kSimpleCells = 200000;
 constexpr int64_t kStreamBytes = 640000000;
 template <typename T>
 static int auto_variant(const StepArgs<T> &a, int *nzc) {
   if (a.N < kSimpleCells) return kStencilSimple;
   const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
-  const int v = stream ? 8 : 1;
+  const bool ragged = a.nx % V16<T>::n != 0;
+  const int v = !stream ? 1 : ragged ? 2 : 8;
   const TileShape t = tile_shape<T>(v);
   const int64_t tiles = (int64_t)((a.nx + t.tx - 1) / t.tx) * ((a.ny + t.ty - 1) / t.ty);
   if (!stream) {
     *nzc = z_split(a.nz, tiles, t.threads, kAutoBlocks, 4);
   } else {
     const int c = (int)std::min<int64_t>(256 / tiles, a.nz / 16);
-    *nzc = c >= 1 && c * tiles >= 230 ? c : std::max(1, a.nz / 16);
+    *nzc = c >= 1 && c * tiles >= 230 && !ragged ? c : std::max(1, a.nz / 16);
   }
   return v;
 }
@@ -642,7 +646,7 @@ hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, const InjMap<T> &i
     return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 4) {
     const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
-    const bool nt = variant < 0 ? stream : variant >= 7 && variant <= 12;
+    const bool nt = variant < 0 ? stream && a.nx % V16<T>::n == 0 : variant >= 7 && variant <= 12;
     const int64_t tiles = (int64_t)((a.nx + 63) / 64) * ((a.ny + 15) / 16);
     const int nzc = z_split(a.nz, tiles, 256, target_blocks, stream ? 16 : 4);
     if (epi == EPI_D2) {
