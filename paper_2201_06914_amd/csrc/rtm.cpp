@@ -1549,9 +1549,9 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
   // has >= 2 x rtm_set_stencil_blocks workgroups (default 4096): the windows
   // are shallow (128-256 planes) and the extra waves in flight outweigh the
   // chunks' warm-up planes.  Chunks of at least 16 planes where the shots'
-  // levels stream from HBM, of 4 where they stay in the memory-side cache
-  // (the warm-up planes then cost less than idle CUs).  Fixed when the batch
-  // is created.
+  // levels stream from HBM, shorter where they stay in the memory-side cache
+  // (the warm-up planes then cost less than idle CUs and a long chain of
+  // planes).  Fixed when the batch is created.
   int nzc = 1;
   auto count = [&](int z) {
     int64_t t = 0;
@@ -1566,7 +1566,8 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
     b->ragged |= p->d.nx % 4 != 0;
   }
   b->stream = 16 * cells > (int64_t)640000000;
-  while (count(nzc) < 2 * (int64_t)g_stencil_blocks && minz / (nzc * 2) >= (b->stream ? 16 : 4)) nzc *= 2;
+  const int minp = b->stream ? 16 : min_planes(4 * cells);
+  while (count(nzc) < 2 * (int64_t)g_stencil_blocks && minz / (nzc * 2) >= minp) nzc *= 2;
   for (int i = 0; i < nshots; ++i) {
     const rtm_desc &d = b->P[i]->d;
     const int ntx = (int)((d.nx + 63) / 64), nty = (int)((d.ny + 15) / 16);

@@ -129,6 +129,10 @@ struct ProbeArgs {
   int *queue = nullptr;
 };
 
+// the shortest z chunks of the tiled stencil for a step over levels of this
+// many bytes that stay in the caches (stencil.hip)
+int min_planes(int64_t bytes);
+
 // launchers (stream-ordered; return the launch status)
 // variant -1: chosen from the grid, and so are its z chunks if target_blocks
 // is kAutoBlocks

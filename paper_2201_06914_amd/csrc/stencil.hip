@@ -528,6 +528,16 @@ static int z_split(int nz, int64_t tiles, int threads, int target, int minp) {
       1, std::min<int64_t>((want + tiles - 1) / tiles, std::max(1, nz / minp)));
 }
 
+// The shortest z chunks worth their warm-up, by the bytes of a level (all
+// shots together): us per step with chunks of 1 / 2 / 4 / 6 / 8 planes: 64^3
+// 4.0 / 5.1 / 5.9 / 7.7 / 8.3 (one thread per cell 5.8); 100^3 8.4 / 7.2 / 7.7 /
+// 8.3 / 9.6; 128^3 10.8 / 9.3 / 8.9 / 10.4 / 9.9; 160^3 19.8 / 16.0 / 14.6 /
+// 14.0 / 15.0; 200^3 39 / 31 / 27.5 / 26.9 / 26.7.  Loads two or three planes
+// ahead instead of one changed none of them by more than 0.2.
+int min_planes(int64_t bytes) {
+  return bytes < 1600000 ? 1 : bytes < 6000000 ? 2 : bytes < 12000000 ? 4 : 6;
+}
+
 // tiled variants: id -> tile (x cells x y rows), threads
 //   1: 64 x 16, 256     2: 64 x 32, 512     3: 64 x 32, 256 (two rows each)
 //   4: 64 x 8, 128      5: 32 x 32, 256     6: 128 x 8, 256
@@ -547,13 +557,14 @@ static TileShape tile_shape(int variant) {
 
 // Automatic choice of the kernel and its z chunks (us per step, F32 unless
 // said; v: the variant).
-//   Grids below kSimpleCells run one thread per cell: the tiled kernel's nine
-//   plane loads and barriers are a longer chain than a step has work for
-//   (40 x 36 x 70: 4.3 against 6.2; 64^3: 5.8 both, FP64 6.1 against 5.8).
+//   Grids below kSimpleCells run one thread per cell: as fast as the tiled
+//   kernel (40 x 36 x 70: 4.3 against 4.2), and a folded injection waits for
+//   one cell's entries per thread, not four's (gradient there 1.40 against
+//   1.55 ms).  64^3: 5.8 against 4.0.
 //   While the four arrays of a step (16 N bytes) stay near the 256 MB
-//   memory-side cache, ordinary loads and short chunks (from four planes: a
-//   chunk re-reads eight, but they hit the caches) on 64 x 16 tiles:
-//   128^3: 8.8 with chunks of 4 planes, 14.3 of 16; 200^3: 26.9 against 38.3
+//   memory-side cache, ordinary loads and short chunks on 64 x 16 tiles: a
+//   chunk re-reads eight planes, but they hit the caches, and a step is a chain
+//   of waits, one per plane (min_planes).  200^3: 26.9 against 38.3
 //   non-temporal; 300^3: 96 against 103.  FP64: 96 x 90 x 110 9.8, 128^3 13.4
 //   (one thread per cell 15.8 and 28); 300^3 166 non-temporal, 200 not.
 //   Beyond that the levels stream from HBM: non-temporal, 64 x 32 tiles.  If
@@ -564,7 +575,7 @@ static TileShape tile_shape(int variant) {
 //   multiple of the vector cut cache lines at every tile's edge, which the
 //   hint would send to HBM twice: ordinary accesses (400 x 400 x 401: 250
 //   against 275 non-temporal; 320 x 448 x 447: 257 against 274).
-constexpr int64_t kSimpleCells = 200000;
+constexpr int64_t kSimpleCells = 150000;
 constexpr int64_t kStreamBytes = 640000000;
 template <typename T>
 static int auto_variant(const StepArgs<T> &a, int *nzc) {
@@ -575,7 +586,7 @@ static int auto_variant(const StepArgs<T> &a, int *nzc) {
   const TileShape t = tile_shape<T>(v);
   const int64_t tiles = (int64_t)((a.nx + t.tx - 1) / t.tx) * ((a.ny + t.ty - 1) / t.ty);
   if (!stream) {
-    *nzc = z_split(a.nz, tiles, t.threads, kAutoBlocks, 4);
+    *nzc = z_split(a.nz, tiles, t.threads, kAutoBlocks, min_planes(a.N * (int)sizeof(T)));
   } else {
     const int c = (int)std::min<int64_t>(256 / tiles, a.nz / 16);
     *nzc = c >= 1 && c * tiles >= 230 && !ragged ? c : std::max(1, a.nz / 16);
@@ -648,7 +659,8 @@ hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, const InjMap<T> &i
     const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
     const bool nt = variant < 0 ? stream && a.nx % V16<T>::n == 0 : variant >= 7 && variant <= 12;
     const int64_t tiles = (int64_t)((a.nx + 63) / 64) * ((a.ny + 15) / 16);
-    const int nzc = z_split(a.nz, tiles, 256, target_blocks, stream ? 16 : 4);
+    const int nzc = z_split(a.nz, tiles, 256, target_blocks,
+                            stream ? 16 : min_planes(a.N * (int)sizeof(T)));
     if (epi == EPI_D2) {
       if (nt) launch_tiled<T, 64, 16, 1, true, EPI_D2>(a, inj, nzc, st, e, rev);
       else launch_tiled<T, 64, 16, 1, false, EPI_D2>(a, inj, nzc, st, e, rev);
