@@ -594,6 +594,11 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
   const T *inj_vals = static_cast<const T *>(io.inj_vals);
   T *smp_out = static_cast<T *>(io.smp_out);
   int s0 = nb;
+  // 2D: several steps per launch, up to the end of the probe block, when the
+  // step kernels take the injection (FP64: up to 2 M cells, see
+  // k_stencil2d_steps)
+  const bool multi = ndim == 2 && variant < 0 && (sizeof(T) == 4 || P->N < 2000000) &&
+                     (inj.ncell == 0 || !inj_vals || inj.inj.map);
   for (int s = nb; s < ne; ++s) {
     const int n = io.adjoint ? d.nt - 1 - s : s;
     a.cur = level(s);
@@ -601,10 +606,18 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
     a.next = level(s + 1);
     TimedLaunch tl;
     prof_begin(KT_STENCIL, s, st, &tl);
-    HIP_TRY(launch_stencil<T>(ndim, a, step_inj(inj, inj_vals, n), variant, g_stencil_blocks, st,
-                              g_stencil_alternate ? (s & 1) : 0));
+    if (multi) {
+      const int steps = std::min({kMaxSteps2D, s0 + d.k_block - s, ne - s});
+      HIP_TRY(launch_stencil2d<T>(a, step_inj(inj, inj_vals, n),
+                                  (io.adjoint ? -1 : 1) * (int64_t)inj.npts, ring, P->ld, P->R, s,
+                                  steps, st));
+      s += steps - 1;
+    } else {
+      HIP_TRY(launch_stencil<T>(ndim, a, step_inj(inj, inj_vals, n), variant, g_stencil_blocks, st,
+                                g_stencil_alternate ? (s & 1) : 0));
+    }
     prof_end(st, &tl);
-    if (inj.ncell > 0 && inj_vals && !inj.inj.map)
+    if (inj.ncell > 0 && inj_vals && !inj.inj.map)  // (never after several steps)
       HIP_TRY(launch_inject<T>(a, inj, inj_vals + (int64_t)n * inj.npts, a.next, st));
     const bool block_end = s + 1 - s0 == d.k_block || s == d.nt - 1 || s == ne - 1;
     if (block_end && smp_out)

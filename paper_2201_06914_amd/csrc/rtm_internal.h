@@ -141,6 +141,13 @@ int min_planes(int64_t bytes);
 template <typename T>
 hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, int variant,
                           int target_blocks, hipStream_t st, int rev = 0);
+// 2D: up to kMaxSteps2D steps s .. s + nsteps - 1 in one launch, from levels s
+// and s - 1 of the ring into the next nsteps; inj: the folded injection of
+// step s, its values advancing by vstride per step (no map: none)
+constexpr int kMaxSteps2D = 4;
+template <typename T>
+hipError_t launch_stencil2d(const StepArgs<T> &a, const InjMap<T> &inj, int64_t vstride, T *ring,
+                            int64_t ld, int R, int s, int nsteps, hipStream_t st);
 // exact comparator: stencil step with a fused epilogue (hipErrorInvalidValue
 // when no tiled kernel serves the grid), and the matching injection
 template <typename T>

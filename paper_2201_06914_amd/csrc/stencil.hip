@@ -117,6 +117,126 @@ __global__ __launch_bounds__(256) void k_stencil_simple(StepArgs<T> a, InjMap<T>
 }
 
 // ---------------------------------------------------------------------------
+// 2D: several steps per launch
+// ---------------------------------------------------------------------------
+// A workgroup (NW waves) advances a tile of TX x TZ cells by up to kSteps2D
+// steps: the tile with a halo of four cells per step (64 x EZ cells) is loaded
+// once, each step computes the cells that the remaining ones still need (the
+// region shrinks by four on each side), and every level's tile goes to the
+// ring.  A lane owns one x column of rows w, w + NW, ... (wave w): its cells'
+// two levels, model and damping stay in registers, the current level sits in
+// LDS for the neighbours, double buffered, one barrier per step.  Cells
+// outside the grid stay zero.  The arithmetic per cell is k_stencil_simple's,
+// and the halo's cells get the same injection as their owners give them, so
+// levels are the same bit for bit.
+// Bound: a 2D step's levels stay in the caches; a launch per step is bound by
+// the launch and one chain of loads, this kernel by the chains of its steps
+// (16 waves per workgroup: the more rows in flight, the better) and, on large
+// grids, by the halo's arithmetic (2.6 times the tile's).  us per step, one
+// launch per step -> four steps per launch: 221 x 221 3.4 -> 1.9 (FP64 3.5 ->
+// 2.3), 301 x 901 4.8 -> 3.6 (6.1 -> 5.4), 600 x 1000 7.3 -> 5.4 (8.7 -> 7.9),
+// 1200 x 2000 20.5 -> 17.4 (24.3 -> 24.9: FP64 keeps the launch per step there).
+constexpr int kSteps2D = kMaxSteps2D;
+template <typename T, int TZ, int NW>
+__global__ __launch_bounds__(64 * NW) void k_stencil2d_steps(StepArgs<T> a, InjMap<T> inj,
+                                                         int64_t vstride, T *ring, int64_t ld,
+                                                         int R, int s, int nsteps, int ntx) {
+  constexpr int H = 4 * kSteps2D;
+  constexpr int TX = 64 - 2 * H;
+  constexpr int EZ = TZ + 2 * H;
+  constexpr int NR = EZ / NW;
+  static_assert(EZ % NW == 0, "whole rows per wave");
+  __shared__ T lds[2][EZ * 64 + 8];  // 4 cells of slack at both ends
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  const int x = (b % ntx) * TX - H + lane;
+  const int zt = (b / ntx) * TZ - H;
+  auto level = [&](int j) { return ring + (int64_t)((j + 1) % R) * ld; };
+  const T *c0 = level(s), *p0 = level(s - 1);
+  T cu[NR], pv[NR], mm[NR], damp[NR];
+  int iv[NR];  // the folded injection's map entry
+  bool in[NR], any[NR];
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    const int r = w + NW * k, z = zt + r;
+    in[k] = x >= 0 && x < a.nx && z >= 0 && z < a.nz;
+    const int64_t i = in[k] ? (int64_t)z * a.nx + x : 0;
+    cu[k] = in[k] ? c0[i] : T(0);
+    pv[k] = in[k] ? p0[i] : T(0);
+    mm[k] = in[k] ? a.m[i] : T(1);
+    damp[k] = sponge_a(a, z, 0, x);
+    iv[k] = -1;
+    if (inj.map && in[k] && z >= inj.z0 && z < inj.z1 && x >= inj.x0 && x < inj.x1)
+      iv[k] = inj.map[(int64_t)(z - inj.z0) * (inj.x1 - inj.x0) + x - inj.x0];
+    any[k] = __any(iv[k] != -1);
+    lds[0][4 + r * 64 + lane] = cu[k];
+  }
+  __syncthreads();
+  const T *vals = inj.vals;
+  for (int j = 0; j < nsteps; ++j) {
+    const int e = 4 * (j + 1);  // cells the region has shrunk to on each side
+    const T *L = &lds[j & 1][4];
+    T *Ln = &lds[(j + 1) & 1][4];
+    T *out = level(s + 1 + j);
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const int r = w + NW * k, z = zt + r;
+      if (r < e || r >= EZ - e) continue;  // wave-uniform
+      T acc = T(0);
+      const int v = iv[k];
+      if (any[k]) {  // wave-uniform
+        if (v >= 0) {
+          acc += vals[v];
+        } else if (v < -1) {
+          for (int q = inj.ioff[-2 - v]; q < inj.ioff[-1 - v]; ++q)
+            acc = fma_t(inj.iw[q], vals[inj.ipt[q]], acc);
+        }
+      }
+      const T *row = L + r * 64 + lane;
+      const T c = cu[k];
+      const T lz = axis_sum(a, row[64], row[-64], row[128], row[-128], row[192], row[-192],
+                            row[256], row[-256]);
+      const T lx = axis_sum(a, row[1], row[-1], row[2], row[-2], row[3], row[-3], row[4], row[-4]);
+      const T lap = fma_t(a.cc, c, lz) + lx;
+      T nv = cell_update(a, c, pv[k], mm[k], lap, damp[k]);
+      if (any[k] && v != -1) nv += inj_term(a, acc, mm[k] + damp[k]);
+      nv = in[k] ? nv : T(0);
+      pv[k] = c;
+      cu[k] = nv;
+      Ln[r * 64 + lane] = nv;
+      if (in[k] && r >= H && r < H + TZ && lane >= H && lane < H + TX)
+        out[(int64_t)z * a.nx + x] = nv;
+    }
+    vals += vstride;
+    __syncthreads();
+  }
+}
+
+// steps s .. s + nsteps - 1 of a 2D sweep (nsteps <= kSteps2D <= R - 2); inj:
+// the folded injection of step s, whose values advance by vstride per step
+template <typename T>
+hipError_t launch_stencil2d(const StepArgs<T> &a, const InjMap<T> &inj, int64_t vstride, T *ring,
+                            int64_t ld, int R, int s, int nsteps, hipStream_t st) {
+  constexpr int TX = 64 - 8 * kSteps2D;
+  const int ntx = (a.nx + TX - 1) / TX;
+  auto go = [&](auto kern, int tz, int nw) {
+    hipLaunchKernelGGL(kern, dim3(ntx * ((a.nz + tz - 1) / tz)), dim3(64 * nw), 0, st, a, inj,
+                       vstride, ring, ld, R, s, nsteps, ntx);
+  };
+  // tiles of 16 rows: 8 need more halo, 32 leave CUs idle; FP64, whose halo
+  // arithmetic weighs more, 32 once those fill the chip (301 x 901: 5.4
+  // against 5.9)
+  if (sizeof(T) == 8 && ntx * ((a.nz + 31) / 32) >= 256) go(k_stencil2d_steps<T, 32, 16>, 32, 16);
+  else go(k_stencil2d_steps<T, 16, 16>, 16, 16);
+  return hipGetLastError();
+}
+template hipError_t launch_stencil2d<float>(const StepArgs<float> &, const InjMap<float> &, int64_t,
+                                            float *, int64_t, int, int, int, hipStream_t);
+template hipError_t launch_stencil2d<double>(const StepArgs<double> &, const InjMap<double> &,
+                                             int64_t, double *, int64_t, int, int, int,
+                                             hipStream_t);
+
+// ---------------------------------------------------------------------------
 // 3D LDS plane ring + z-marching register queue
 // ---------------------------------------------------------------------------
 // A thread owns VX = 16 / sizeof(T) consecutive x cells of RY rows, so every

@@ -68,3 +68,35 @@ def test_automatic_choice_equals_simple(shape, field):
         P.set_stencil_variant(-1)
     assert float(ref.abs().max()) > 0
     assert torch.equal(got, ref)
+
+
+# 2D, several steps per launch: fewer cells than a tile, one column more than a
+# tile, both tile heights; blocks that end on and off a launch's four steps
+@pytest.mark.parametrize("shape,field,k", [((9, 1, 11), "f32", 3), ((16, 1, 33), "f64", 4),
+                                           ((50, 1, 97), "f32", 7), ((17, 1, 32), "f64", 1),
+                                           ((1060, 1, 260), "f64", 6), ((70, 1, 64), "f32", 2)])
+def test_2d_steps_equal_single_steps(shape, field, k):
+    nt = 11
+    plan = P.Plan(P.PlanSpec(2, shape, 10.0, 1e-3, nt, 2, 4500.0, 1e-3, 4500.0, field,
+                             "f32" if field == "f32" else "f64", 3, k, 2, 3))
+    m = _m(plan, 3)
+    q = torch.tensor([[1e-3, -2e-3]], device="cuda", dtype=plan.dtype).repeat(nt, 1)
+    src = np.array([[shape[0] / 2, 0, shape[2] / 2], [shape[0] / 2 + 0.5, 0, shape[2] / 2 + 0.25]])
+    rec = np.array([[3.0, 0, 4.5], [shape[0] / 2, 0, shape[2] / 2], [shape[0] - 1, 0, 0]])
+    Z = torch.ones((nt, 3), device="cuda", dtype=torch.int8)
+    say(f"case: 2D steps {shape} {field} k={k}")
+
+    def run():
+        f = P.rtm_forward_probe(plan, m, src, q, rec, Z, final=True)
+        res = f["d"] + 1e-6
+        b = P.rtm_adjoint_probe(plan, m, rec, res, Z, src_pos=src, want_qadj=True)
+        return f["final"], f["d"], f["Ubar"], b["Vbar"], b["qadj"]
+    got = run()
+    P.set_stencil_variant(0)
+    try:
+        ref = run()
+    finally:
+        P.set_stencil_variant(-1)
+    assert float(ref[0].abs().max()) > 0
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)
