@@ -21,6 +21,8 @@
 //   k_probe_vec   FMA path (any real Z): FP64, and FP32 blocks whose probe
 //                 operand exceeds the MFMA path's LDS.  Thread per cell, 32
 //                 probe rows per pass, in the per-step order bar += z_n s^n.
+#include <type_traits>
+
 #include "ring.h"
 
 namespace rtm {
@@ -47,6 +49,8 @@ __device__ __forceinline__ int64_t bar_index(int64_t x, int i, int r) {
 // ---------------------------------------------------------------------------
 // vector path
 // ---------------------------------------------------------------------------
+// The block's values are formed eight steps at a time from ten loads in
+// flight.
 template <typename T, typename ZT>
 __global__ __launch_bounds__(256) void k_probe_vec(ProbeArgs<T> p, const ZT *__restrict__ Z) {
   constexpr int RC = 32;  // probe rows per pass
@@ -68,10 +72,26 @@ __global__ __launch_bounds__(256) void k_probe_vec(ProbeArgs<T> p, const ZT *__r
     T acc[RC];
 #pragma unroll
     for (int i = 0; i < RC; ++i) acc[i] = i < rc && !p.first ? p.bar[bar_index(c, r0 + i, p.r)] : T(0);
-    for (int t = 0; t < p.kb; ++t) {
-      const T s = probed(p, t, c);
+    for (int t0 = 0; t0 < p.kb; t0 += 8) {
+      T s[8];
+      if (p.mode == PROBE_UTT) {
+        T lv[10];
 #pragma unroll
-      for (int i = 0; i < RC; ++i) acc[i] += zs[t * RC + i] * s;
+        for (int q = 0; q < 10; ++q) lv[q] = ring_level(p, p.s0 + min(t0 + q - 1, p.kb))[c];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s[q] = (lv[q + 2] - T(2) * lv[q + 1] + lv[q]) * p.inv_dt2;
+      } else {
+        const int shift = p.mode == PROBE_NEW ? 1 : 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          s[q] = ring_level(p, p.s0 + min(t0 + q, p.kb - 1) + shift)[c];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (t0 + q >= p.kb) break;
+#pragma unroll
+        for (int i = 0; i < RC; ++i) acc[i] += zs[(t0 + q) * RC + i] * s[q];
+      }
     }
 #pragma unroll
     for (int i = 0; i < RC; ++i)
@@ -82,15 +102,148 @@ __global__ __launch_bounds__(256) void k_probe_vec(ProbeArgs<T> p, const ZT *__r
 template <typename T>
 hipError_t launch_probe_vec(const ProbeArgs<T> &p, const void *Z, bool z_is_i8, hipStream_t st) {
   const unsigned nblk = (unsigned)((p.N + 255) / 256);
-  const size_t shm = sizeof(T) * (size_t)p.kb * 32;
-  if (z_is_i8)
-    hipLaunchKernelGGL((k_probe_vec<T, int8_t>), dim3(nblk), dim3(256), shm, st, p,
-                       static_cast<const int8_t *>(Z));
-  else
-    hipLaunchKernelGGL((k_probe_vec<T, T>), dim3(nblk), dim3(256), shm, st, p,
-                       static_cast<const T *>(Z));
+  auto go = [&](auto kern, auto z) {
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3(256), sizeof(T) * (size_t)p.kb * 32, st, p,
+                       static_cast<decltype(z)>(Z));
+  };
+  if (z_is_i8) go(k_probe_vec<T, int8_t>, (const int8_t *)nullptr);
+  else go(k_probe_vec<T, T>, (const T *)nullptr);
   return hipGetLastError();
 }
+// ---------------------------------------------------------------------------
+// FP64 on the matrix cores
+// ---------------------------------------------------------------------------
+// v_mfma_f64_16x16x4_f64 operand layout (64 lanes, l = lane, g = l / 16):
+//   A (16 x 4): lane l holds A[l % 16][g];  B (4 x 16): B[g][l % 16]
+//   C (16 x 16): lane l, register v holds C[4 v + g][l % 16]
+// One wave owns a 32-cell tile, 16 cells at a time; MFMA q of a 16-step chunk
+// takes the steps 4 g + q, so a lane's four values of a chunk are consecutive
+// steps (six loads in the u_tt mode).  Z sits in LDS in A-operand order.  Rows
+// at or past r take an offset past the tile's buffer (read as zero, stores
+// dropped).
+// Bound: HBM on large grids (8 (k + 2 + 2 r) bytes per cell).  us a block,
+// vector kernel -> this one: 221 x 221, r = 32, k = 32 33 -> 12.5; 96 x 90 x 110,
+// r = 32, k = 16 139 -> 82; 200^3, r = 32, k = 32 1528 -> 1008 (4.1 -> 6.2 TB/s).
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+template <int KS, typename ZT, int MODE, bool FIRST>
+__global__ __launch_bounds__(256) void k_probe_mfma_f64(ProbeArgs<double> p,
+                                                        const ZT *__restrict__ Z, int MT) {
+  extern __shared__ double ldsD[];  // [MT][KS][4][64]
+  for (int e = threadIdx.x; e < MT * KS * 256; e += 256) {
+    const int l = e & 63, q = (e >> 6) & 3, ks = (e >> 8) % KS, mt = (e >> 8) / KS;
+    const int t = ks * 16 + 4 * (l >> 4) + q, i = mt * 16 + (l & 15);
+    ldsD[e] = t < p.kb && i < p.r ? (double)Z[(int64_t)(p.zrow0 + p.zdir * t) * p.r + i] : 0.0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = lane & 15, g = lane >> 4;
+  const int64_t ntiles = (p.N + 31) / 32;
+  const int shift = p.mode == PROBE_NEW ? 1 : 0;
+  for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles;
+       tile += (int64_t)gridDim.x * 4) {
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+        p.bar + tile * (int64_t)p.r * 32, (short)0, p.r * 256, 0x00020000);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t c = tile * 32 + h * 16 + col;
+      double b[KS][4];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int tb = ks * 16 + 4 * g;
+        if (MODE == PROBE_UTT) {
+          double lv[6];
+#pragma unroll
+          for (int q = 0; q < 6; ++q)
+            lv[q] = c < p.N ? ring_level(p, p.s0 + min(tb + q - 1, p.kb))[c] : 0.0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double d2 = (__builtin_fma(-2.0, lv[q + 1], lv[q + 2]) + lv[q]) * p.inv_dt2;
+            b[ks][q] = tb + q < p.kb ? d2 : 0.0;
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double v =
+                c < p.N ? ring_level(p, p.s0 + min(tb + q, p.kb - 1) + shift)[c] : 0.0;
+            b[ks][q] = tb + q < p.kb ? v : 0.0;
+          }
+        }
+      }
+      for (int mt0 = 0; mt0 < MT; mt0 += 2) {
+        f64x4 acc[2];
+        int off[2][4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int row = (mt0 + j) * 16 + 4 * v + g;
+            off[j][v] = row < p.r ? (row * 32 + h * 16 + col) * 8 : (int)0x80000000;
+            acc[j][v] = FIRST ? 0.0
+                              : __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                                               rb, off[j][v], 0, 0));
+          }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if (mt0 + j >= MT) break;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                  ldsD[(((mt0 + j) * KS + ks) * 4 + q) * 64 + lane], b[ks][q], acc[j], 0, 0, 0);
+        }
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const double x = acc[j][v];  // (a bit cast of the element itself takes element 0)
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), rb, off[j][v], 0, 0);
+          }
+      }
+    }
+  }
+}
+
+template <int KS, typename ZT>
+static void launch_f64_ks(const ProbeArgs<double> &p, const void *Z, hipStream_t st) {
+  const int MT = (p.r + 15) / 16;
+  const int64_t want = ((p.N + 31) / 32 + 3) / 4;  // one workgroup per four tiles
+  const size_t shm = (size_t)MT * KS * 256 * 8;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)want), dim3(256), shm, st, p,
+                       static_cast<const ZT *>(Z), MT);
+  };
+  if (p.mode == PROBE_UTT) {
+    if (p.first) go(k_probe_mfma_f64<KS, ZT, PROBE_UTT, true>);
+    else go(k_probe_mfma_f64<KS, ZT, PROBE_UTT, false>);
+  } else {
+    if (p.first) go(k_probe_mfma_f64<KS, ZT, PROBE_NEW, true>);
+    else go(k_probe_mfma_f64<KS, ZT, PROBE_NEW, false>);
+  }
+}
+
+// FP64 blocks: the matrix cores, or the vector kernel where the probe operand
+// exceeds 64 KB of LDS
+hipError_t launch_probe_f64(const ProbeArgs<double> &p, const void *Z, bool z_is_i8,
+                            hipStream_t st) {
+  int KS = (p.kb + 15) / 16;
+  KS = KS <= 1 ? 1 : KS <= 2 ? 2 : KS <= 4 ? 4 : 8;
+  if (p.kb > 128 || (p.r + 15) / 16 * KS > 32) return launch_probe_vec<double>(p, Z, z_is_i8, st);
+  auto go = [&](auto ks) {
+    constexpr int K = decltype(ks)::value;
+    if (z_is_i8) launch_f64_ks<K, int8_t>(p, Z, st);
+    else launch_f64_ks<K, double>(p, Z, st);
+  };
+  switch (KS) {
+    case 1: go(std::integral_constant<int, 1>()); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    default: go(std::integral_constant<int, 8>()); break;
+  }
+  return hipGetLastError();
+}
+
 template hipError_t launch_probe_vec<float>(const ProbeArgs<float> &, const void *, bool,
                                             hipStream_t);
 template hipError_t launch_probe_vec<double>(const ProbeArgs<double> &, const void *, bool,

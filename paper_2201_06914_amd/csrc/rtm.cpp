@@ -659,7 +659,7 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
                                   static_cast<const float *>(io.fuse_U),
                                   static_cast<float *>(io.fuse_img), (float)io.fuse_scale, st));
       } else {
-        HIP_TRY(launch_probe_vec<T>(p, io.Z, io.zt == RTM_I8, st));
+        HIP_TRY(launch_probe_f64(p, io.Z, io.zt == RTM_I8, st));
       }
       prof_end(st, &tp);
       s0 = s + 1;
@@ -1994,7 +1994,7 @@ static rtm_status run_tti_sweep(const rtm_plan *P, const TtiIO &io, const PointT
           HIP_TRY(launch_probe_mfma(p, io.Z, io.zt == RTM_F32, probe_op(d.probe_dtype), Uf,
                                     static_cast<float *>(io.fuse_img), (float)io.fuse_scale, st));
         } else {
-          HIP_TRY(launch_probe_vec<T>(p, io.Z, io.zt == RTM_I8, st));
+          HIP_TRY(launch_probe_f64(p, io.Z, io.zt == RTM_I8, st));
         }
       }
       s0 = s + 1;

@@ -227,6 +227,8 @@ hipError_t launch_sample_block(const PointTables<T> &pt, const T *ring, const T 
 template <typename T>
 hipError_t launch_probe_vec(const ProbeArgs<T> &p, const void *Z, bool z_is_i8,
                             hipStream_t st);
+hipError_t launch_probe_f64(const ProbeArgs<double> &p, const void *Z, bool z_is_i8,
+                            hipStream_t st);
 // Uf / img / scale: non-NULL img selects the fused adjoint imaging variant
 // (img[c] += scale * sum_i Uf[i][c] (Z_b^T S_b)[i][c]; p.bar unused).
 // Z is int8 +-1, or with zf32 real FP32 probes split into bf16 hi + lo (needs
