@@ -401,8 +401,8 @@ void rtm_set_exact_fused(int32_t on);
  * instead.  Results agree to rounding. */
 void rtm_set_tti_shape(int32_t shape);
 /* Tuning hook, process wide: the tiled TTI kernels split z into the fewest
- * chunks (of at least 16 planes) that give a launch this many workgroups,
- * for the forward step and for the transpose step (<= 0: the defaults, 2800
+ * chunks (of at least 16 planes; fewer on grids that do not fill the chip)
+ * that give a launch this many workgroups, for the forward step and for the transpose step (<= 0: the defaults, 2800
  * and 1750). */
 void rtm_set_tti_blocks(int32_t forward, int32_t transpose);
 rtm_status fwi_gradient_exact(const rtm_plan *plan, const void *m, const double *src_pos,

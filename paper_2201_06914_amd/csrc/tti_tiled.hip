@@ -22,6 +22,8 @@
 // (double buffered, one barrier per plane) and the next plane's loads are in
 // flight while the current one is computed.  Intermediates live in the
 // plan's scratch slots g[k] (stride N).
+#include <algorithm>
+
 #include "tti_common.h"
 
 namespace rtm {
@@ -1330,11 +1332,16 @@ __global__ __launch_bounds__(TX *TY, MINW) void k_tti_afused_dq(TtiArgs<T> t, in
 }
 
 // grid of one tiled launch: (64 x ty) column tiles, z split into the fewest
-// chunks (of at least 16 planes) that give target_blocks workgroups
+// chunks (of at least 16 planes) that give target_blocks workgroups.  Where
+// those leave some of the chip's `slots` (workgroups resident at once, at most
+// target_blocks) empty, into as many chunks as still run in one round, down to
+// two planes: a step then takes the time of one chunk's planes and its eight
+// warm-up planes (us forward / transpose: 64^3 30 / 38 ->
+// 15 / 17, 100^3 38 / 42 -> 26 / 34).
 struct TtiGrid {
   int ntx, nty, nzc, zchunk;
 };
-static TtiGrid tti_grid(int nz, int ny, int nx, int ty, int target_blocks) {
+static TtiGrid tti_grid(int nz, int ny, int nx, int ty, int target_blocks, int slots) {
   TtiGrid g;
   g.ntx = (nx + TX - 1) / TX;
   g.nty = (ny + ty - 1) / ty;
@@ -1343,6 +1350,8 @@ static TtiGrid tti_grid(int nz, int ny, int nx, int ty, int target_blocks) {
   const int most = nz / 16 > 1 ? nz / 16 : 1;
   if (nzc > most) nzc = most;
   if (nzc < 1) nzc = 1;
+  if (slots > target_blocks) slots = target_blocks;
+  if (tiles * nzc < slots) nzc = std::max(nzc, std::min(slots / tiles, std::max(1, nz / 2)));
   g.zchunk = (nz + nzc - 1) / nzc;
   g.nzc = (nz + g.zchunk - 1) / g.zchunk;
   return g;
@@ -1366,8 +1375,10 @@ template <typename T, int TYP, int TYM, int FUSED = 0, int AFUSED = 0, int UA = 
 static hipError_t tti_step_tiled(const TtiArgs<T> &t, bool adjoint, int target_blocks,
                                  hipStream_t st) {
   const StepArgs<T> &a = t.a;
-  const TtiGrid gp = tti_grid(a.nz, a.ny, a.nx, TYP, target_blocks);
-  const TtiGrid gm = tti_grid(a.nz, a.ny, a.nx, TYM, target_blocks);
+  // resident at once: one transpose workgroup per CU, three forward ones
+  const int slots = adjoint ? 256 : 768;
+  const TtiGrid gp = tti_grid(a.nz, a.ny, a.nx, TYP, target_blocks, slots);
+  const TtiGrid gm = tti_grid(a.nz, a.ny, a.nx, TYM, target_blocks, slots);
   const dim3 bp(TX * TYP), bm(TX * TYM);
   const dim3 np(gp.ntx * gp.nty * gp.nzc), nm(gm.ntx * gm.nty * gm.nzc);
   if constexpr (FUSED == 1) {
