@@ -163,43 +163,51 @@ __device__ __forceinline__ void gather_finish(const GatherThread<T, GX> &th, con
 // v_mfma_f32_16x16x4f32 (4 probe rows per instruction, FP32 products and
 // sums).  A workgroup of 4 waves owns a segment of 32 NT cells (2 NT
 // wave-tiles, NT / 2 per wave); a wider segment stages less of the V halo
-// (the 4 nh cells around the segment) per cell.  Chunks of GR probe rows
-// stream straight from global memory into three LDS buffers by buffer loads,
-// two chunks in flight; the buffers are distinct arrays alternated
-// statically, so the compiler can tell the loads in flight from the reads
-// and does not wait for the former before the latter.  Staged rows keep the
-// even cells of each 64-cell group in its first 32 slots and the odd cells in
-// the last 32, so a lane group's 16 same-parity cells are 16 consecutive
-// words; the row stride is 16 mod 64 words so the 4 probe rows of one
-// instruction fall in distinct banks.  The products go out through LDS in
-// rounds of TR 32-cell tiles, an array [h + nh][a - a_round] whose rows are
-// written as consecutive x for each offset.
+// (the 4 nh cells around the segment) per cell.
+// Staging: eight probe rows of a 32-cell tile are 1 KB of consecutive memory,
+// which one wave moves to LDS with one load of 16 bytes per lane (WIDE) and in
+// the order of memory; the segment's and the halo's tiles are loaded whole and
+// a lane's cell is found by its place in the tile (the row may start inside
+// one).  A 16 x 4 operand then reads its same-parity cells 2 words apart and
+// its probe rows 32 words apart: 32 lanes on distinct banks.  Cells of the
+// neighbouring x rows come along with the first and last tile; they only meet
+// products that are not written (a) or written as zero (b).
+// Chunks of 8 probe rows stream into two LDS buffers, one chunk in flight; the
+// buffers are distinct arrays alternated statically, so the compiler can tell
+// the loads in flight from the reads and does not wait for the former before
+// the latter.  The products leave through LDS.
+// Bound: HBM at few offsets (r = 64 on two fields of 160 x 300 x 400, nh = 0:
+// 3.3 ms, 5.8 TB/s; 5.9 ms when 4-byte loads sorted the cells by parity on
+// their way to LDS, four times the load instructions).  At nh = 40 6.6 ms
+// (10.7) against 4.4 of HBM and 3.2 of matrix cores, which the two or four
+// workgroups of a CU overlap in part; r = 4 on one field, mostly the way out,
+// 2.5 (3.5: an [offset][a] array cost an address, a range check and a choice
+// of three buffers per product; without any store it took as long).  Three
+// buffers with two chunks in flight leave room for three workgroups instead
+// of four or five: 7.4 ms.  nh = 64, r = 32, 120 x 200 x 301: 2.1 (5.2).
 typedef float gv4f __attribute__((ext_vector_type(4)));
 
-__host__ __device__ constexpr int gm_ug(int nt) { return (nt + 1) / 2; }         // U groups of 64
-__host__ __device__ constexpr int gm_vg(int nt, int nbt) { return (nt + nbt + 1) / 2; }  // V groups
-__host__ __device__ constexpr int gm_lsu(int nt) { return 64 * gm_ug(nt) + 16; }
-__host__ __device__ constexpr int gm_lsv(int nt, int nbt) { return 64 * gm_vg(nt, nbt) + 16; }
-__host__ __device__ constexpr int gm_buf(int nt, int nbt, int gr) {
-  return gr * (gm_lsu(nt) + gm_lsv(nt, nbt));
+constexpr int GR = 8;      // probe rows per chunk: a tile's chunk is 1 KB
+constexpr int GTW = 32 * GR;  // its words
+constexpr int GOS = 37;    // product rows on their way out: no bank conflicts either way
+__host__ __device__ constexpr int gm_ut(int nt) { return nt + 1; }              // U tiles
+__host__ __device__ constexpr int gm_vt(int nt, int nbt) { return nt + nbt; }   // V tiles
+__host__ __device__ constexpr int gm_buf(int nt, int nbt) {
+  const int stage = GTW * (gm_ut(nt) + gm_vt(nt, nbt)), out = 16 * nbt * GOS;
+  return stage > out ? stage : out;
 }
-// staged slot of column c
-__device__ __forceinline__ int gm_slot(int c) { return (c & ~63) + 32 * (c & 1) + ((c & 63) >> 1); }
 
-template <int NBT, int NT, int GR>
+template <int NBT, int NT, bool WIDE>
 __global__ __launch_bounds__(256) void k_offset_gathers_mfma(const float *__restrict__ U,
                                                              const float *__restrict__ V,
                                                              GatherArgs a, float scale,
                                                              float *__restrict__ G) {
-  constexpr int UG = gm_ug(NT), VG = gm_vg(NT, NBT), LSU = gm_lsu(NT), LSV = gm_lsv(NT, NBT);
-  constexpr int BUFN = gm_buf(NT, NBT, GR), NGRP = UG + VG, QG = (NGRP + 3) / 4, NQ = NT / 2;
-  constexpr int W = 32 * NT, VL = 32 * (NT + NBT);  // segment cells; V columns read
-  constexpr int PER = QG * GR;  // loads per wave per chunk
-  constexpr int VMW = 0x0F70 | (PER & 15) | ((PER >> 4) << 14);  // s_waitcnt vmcnt(PER)
-  static_assert(NT % 2 == 0 && GR % 4 == 0 && PER < 64, "tile shape");
-  __shared__ __align__(16) float SA[BUFN + 64];  // + a spare row for loads past the groups
-  __shared__ __align__(16) float SB[BUFN + 64];
-  __shared__ __align__(16) float SC[BUFN + 64];
+  constexpr int UT = gm_ut(NT), NTL = UT + gm_vt(NT, NBT), BUFN = gm_buf(NT, NBT), NQ = NT / 2;
+  constexpr int W = 32 * NT;  // segment cells
+  constexpr int QG = (NTL + 3) / 4, LPT = WIDE ? 1 : 4;  // tiles per wave, loads each
+  static_assert(NT % 2 == 0, "wave-tiles come in pairs");
+  __shared__ __align__(16) float SA[BUFN];
+  __shared__ __align__(16) float SB[BUFN];
   int blk = blockIdx.x;
   blk = xcd_block(blk, a.nblk);  // XCD-aware
   const int seg = blk % a.nseg;
@@ -207,28 +215,27 @@ __global__ __launch_bounds__(256) void k_offset_gathers_mfma(const float *__rest
   const int a0 = seg * W;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
-  // staging: wave w loads groups w + 4 j (U groups first, then V; groups past
-  // the last go to a spare row); lane l of a group holds column
-  // 2 (l % 32) + l / 32 of it, which lands in slot l.  Buffer loads address
-  // this x row's tiles; an offset past them (a cell outside the row, a probe
-  // row past r) reads zero, so every wave issues the same loads per chunk.
+  // staging: wave w loads the tiles w + 4 j (U's first, then V's).  Buffer
+  // loads address this x row's tiles (numbered from its first); a tile past
+  // them and a probe row past r read zero.
   const int64_t t0row = rb >> 5;
-  const uint32_t nrec = (uint32_t)((((rb + a.nx - 1) >> 5) - t0row + 1) * a.r * 128);
+  const int s0 = (int)(rb & 31);  // the row's first cell in its first tile
+  const int ntile = (s0 + a.nx + 31) >> 5;
+  const uint32_t nrec = (uint32_t)ntile * (uint32_t)a.r * 128u;
   constexpr uint32_t OOR = 0x80000000u;  // >= nrec
-  const int cg = 2 * (lane & 31) + (lane >> 5);
+  const int ub = (s0 + a0) >> 5, vc = s0 + a0 - 2 * a.nh, vb = vc >> 5;  // first tiles
+  const int lrow = WIDE ? lane >> 3 : lane >> 5;                         // probe row of a load
   uint32_t goff[QG];
 #pragma unroll
   for (int j = 0; j < QG; ++j) {
     const int g = w + 4 * j;
-    const int c = g < UG ? 64 * g + cg : 64 * (g - UG) + cg;
-    const int x = g < UG ? a0 + c : a0 - 2 * a.nh + c;
-    const bool ok = g < NGRP && x >= 0 && x < a.nx && (g < UG || c < VL);
-    const int64_t cell = rb + x;
-    goff[j] = ok ? (uint32_t)((((cell >> 5) - t0row) * a.r * 32 + (cell & 31)) * 4) : OOR;
+    const int t = g < UT ? ub + g : vb + g - UT;
+    goff[j] = t >= 0 && t < ntile ? (uint32_t)t * (uint32_t)a.r * 128u + lane * (WIDE ? 16u : 4u)
+                                  : OOR;
   }
   const int cpf = (a.r + GR - 1) / GR, nch = a.nfield * cpf;
   auto issue = [&](int c, float *S) {
-    const int f = c / cpf, i0 = (c % cpf) * GR;
+    const int f = c / cpf, i0 = (c - f * cpf) * GR;
     const int64_t fb = f * a.fstride + t0row * a.r * 32;
     const __amdgpu_buffer_rsrc_t ru =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(U + fb), (short)0, (int)nrec, 0x00020000);
@@ -237,13 +244,16 @@ __global__ __launch_bounds__(256) void k_offset_gathers_mfma(const float *__rest
 #pragma unroll
     for (int j = 0; j < QG; ++j) {
       const int g = w + 4 * j;
-      float *dst = g < UG ? S + 64 * g : g < NGRP ? S + GR * LSU + 64 * (g - UG) : S + BUFN;
-      const int ls = g < UG ? LSU : g < NGRP ? LSV : 0;
+      if ((j + 1) * 4 > NTL && g >= NTL) continue;
 #pragma unroll
-      for (int ii = 0; ii < GR; ++ii) {
-        const uint32_t off = i0 + ii < a.r ? goff[j] + (uint32_t)(i0 + ii) * 128u : OOR;
-        if (g < UG) __builtin_amdgcn_raw_ptr_buffer_load_lds(ru, dst + ii * ls, 4, off, 0, 0, 0);
-        else __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, dst + ii * ls, 4, off, 0, 0, 0);
+      for (int k = 0; k < LPT; ++k) {
+        const int row = i0 + 2 * k + lrow;
+        const uint32_t off = row < a.r ? goff[j] + (uint32_t)(i0 + 2 * k) * 128u : OOR;
+        float *dst = S + GTW * g + 64 * k;
+        if constexpr (WIDE)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(g < UT ? ru : rv, dst, 16, off, 0, 0, 0);
+        else
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(g < UT ? ru : rv, dst, 4, off, 0, 0, 0);
       }
     }
   };
@@ -251,11 +261,9 @@ __global__ __launch_bounds__(256) void k_offset_gathers_mfma(const float *__rest
   // lane l holds operand row / column l % 16 and probe row 4 s + l / 16 of
   // each 4-row step
   const int p = w & 1, kq = lane >> 4, ln = lane & 15;
-  const int posu = kq * LSU + gm_slot(32 * (w >> 1) + p + 2 * ln);
-  int posv[NBT];
-#pragma unroll
-  for (int bt = 0; bt < NBT; ++bt)
-    posv[bt] = GR * LSU + kq * LSV + gm_slot(32 * ((w >> 1) + bt) + p + 2 * ln);
+  auto place = [&](int c) { return (c >> 5) * GTW + (c & 31) + kq * 32 + (w >> 1) * GTW; };
+  const int posu = place(((s0 + a0) & 31) + p + 2 * ln);
+  const int posv = place((vc & 31) + p + 2 * ln) + UT * GTW;
   bool act[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) act[q] = a0 + 32 * ((w >> 1) + 2 * q) + p < a.nx;
@@ -265,113 +273,89 @@ __global__ __launch_bounds__(256) void k_offset_gathers_mfma(const float *__rest
 #pragma unroll
     for (int bt = 0; bt < NBT; ++bt) acc[q][bt] = gv4f{0.f, 0.f, 0.f, 0.f};
   auto mult = [&](const float *S, int c) {
-    const int nst = (min(GR, a.r - (c % cpf) * GR) + 3) >> 2;
-    for (int s = 0; s < nst; ++s) {
+    const int f = c / cpf, i0 = (c - f * cpf) * GR;
+    auto four = [&](int s) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         if (act[q]) {
-          const float av = S[posu + 64 * q + 4 * s * LSU];
+          const float av = S[posu + 2 * GTW * q + 128 * s];
 #pragma unroll
           for (int bt = 0; bt < NBT; ++bt)
-            acc[q][bt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, S[posv[bt] + 64 * q + 4 * s * LSV],
-                                                              acc[q][bt], 0, 0, 0);
+            acc[q][bt] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                av, S[posv + GTW * (bt + 2 * q) + 128 * s], acc[q][bt], 0, 0, 0);
         }
       }
-    }
+    };
+    four(0);
+    if (i0 + 4 < a.r) four(1);
   };
-  // three buffers, two chunks in flight: waiting for chunk k leaves the PER
-  // loads of chunk k + 1 outstanding.  The barrier is a bare s_barrier: a
-  // workgroup fence would wait for every load in flight.  The loop writes LDS
-  // only through those loads, and the reads before it are consumed before it;
-  // the empty asm statements keep the compiler from moving memory accesses
-  // across it.
-  auto wait_chunk = [&](int k) {
-    if (k + 1 < nch) __builtin_amdgcn_s_waitcnt(VMW);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
+  // two buffers, one chunk in flight.  The barrier is a bare s_barrier after a
+  // wait for this wave's loads; the loop writes LDS only through those loads,
+  // and the reads before the barrier are consumed before it; the empty asm
+  // statements keep the compiler from moving memory accesses across it.
+  auto next_chunk = [&]() {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();  // everyone's loads of chunk k; chunk k - 1 is multiplied out
+    __builtin_amdgcn_s_barrier();  // everyone's loads; the chunk before is multiplied out
     asm volatile("" ::: "memory");
   };
   issue(0, SA);
-  if (1 < nch) issue(1, SB);
-  for (int c = 0; c < nch; c += 3) {
-    wait_chunk(c);
-    if (c + 2 < nch) issue(c + 2, SC);
+  for (int c = 0; c < nch; c += 2) {
+    next_chunk();
+    if (c + 1 < nch) issue(c + 1, SB);
     mult(SA, c);
     if (c + 1 >= nch) break;
-    wait_chunk(c + 1);
-    if (c + 3 < nch) issue(c + 3, SA);
+    next_chunk();
+    if (c + 2 < nch) issue(c + 2, SA);
     mult(SB, c + 1);
-    if (c + 2 >= nch) break;
-    wait_chunk(c + 2);
-    if (c + 4 < nch) issue(c + 4, SB);
-    mult(SC, c + 2);
   }
-  // products -> O[H][j] (H = h + nh, j = a - a0 - 32 t0) in rounds of TR tiles,
-  // row stride 32 TR + 1, spread over the three buffers
-  const int nout = 2 * a.nh + 1, TR = a.hgs, OS = 32 * TR + 1;
-  auto oref = [&](int e) -> float & { return e < BUFN ? SA[e] : e < 2 * BUFN ? SB[e - BUFN] : SC[e - 2 * BUFN]; };
-  for (int t0 = 0; t0 < NT; t0 += TR) {
+  // products -> rows of one offset, two 32-cell tiles (one q) per round.  A
+  // tile's 16 NBT x 32 products lie in LDS as [16 bt + n][a - a_t] (row stride
+  // GOS), where lane and register are an address and an immediate offset; the
+  // product for offset H = h + nh of cell a = a_t + 2 m + p is the one in row
+  // m + 2 nh - H.  A wave then takes 64 consecutive cells of one offset.
+  const int nout = 2 * a.nh + 1, lt = lane >> 5, lm = (lane & 31) >> 1;
+  float *const ow = (w >> 1 ? SB : SA) + ln * GOS + 8 * kq + p;
+  const float *const orow = (lt ? SB : SA) + (lm + 2 * a.nh - w) * GOS + (lane & 31);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    if (a0 + 64 * q >= a.nx) break;
     __syncthreads();
+    if (act[q]) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int tq = (w >> 1) + 2 * q;
-      if (act[q] && tq >= t0 && tq < t0 + TR) {
+      for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
-        for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int m = 4 * kq + v, H = m - 16 * bt - ln + 2 * a.nh;
-            if (H >= 0 && H <= 2 * a.nh) oref(H * OS + 32 * (tq - t0) + p + 2 * m) = acc[q][bt][v];
-          }
-      }
+        for (int v = 0; v < 4; ++v) ow[16 * bt * GOS + 2 * v] = scale * acc[q][bt][v];
     }
     __syncthreads();
-    const int ar = a0 + 32 * t0, mt = min(TR, NT - t0), wr = 32 * mt;
-    if ((mt & (mt - 1)) == 0) {
-      // a thread keeps column j and steps over offsets; G[H][x] with
-      // x = ar + j + nh - H moves by N - 1 words per offset
-      const int lw = 5 + __builtin_ctz(mt), j = tid & (wr - 1), hs = 256 >> lw;
-      const bool okj = ar + j < a.nx;
-      const int64_t step = (int64_t)hs * (a.N - 1);
-      int H = tid >> lw;
-      float *gp = G + rb + ar + j + a.nh + (int64_t)H * (a.N - 1);
-      for (; H < nout; H += hs, gp += step) {
-        const int x = ar + j + a.nh - H;
-        if (okj && x >= 0 && x < a.nx) *gp = scale * oref(H * OS + j);
-      }
-    } else {
-      for (int e = tid; e < nout * wr; e += 256) {
-        const int H = e / wr, j = e - H * wr, x = ar + j + a.nh - H;
-        if (ar + j < a.nx && x >= 0 && x < a.nx) G[(int64_t)H * a.N + rb + x] = scale * oref(H * OS + j);
+    const int al = a0 + 64 * q + lane;
+    const int xa = al < a.nx ? al + a.nh : -(1 << 30);  // x = xa - H, b = xa + nh - 2 H
+    float *gp = G + rb + (int64_t)w * (a.N - 1) + a0 + 64 * q + a.nh;
+    for (int H0 = w; H0 < nout; H0 += 16) {
+      float o[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        o[k] = H0 + 4 * k < nout ? orow[(w - H0 - 4 * k) * GOS] : 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k, gp += 4 * (a.N - 1)) {
+        const int H = H0 + 4 * k, x = xa - H, b = x + a.nh - H;
+        if (H < nout && (uint32_t)x < (uint32_t)a.nx)
+          gp[lane] = (uint32_t)b < (uint32_t)a.nx ? o[k] : 0.f;
       }
     }
   }
   // cells with a outside the row are zero: the first segment writes them for
-  // h < 0 (x < -h), the last for h > 0 (x >= nx - h)
-  const bool first = seg == 0, last = seg == a.nseg - 1;
-  if (first || last) {
-    for (int e = tid; e < nout * 64; e += 256) {
-      const int H = e >> 6, j = e & 63, h = H - a.nh;
-      float *Gh = G + (int64_t)H * a.N + rb;
-      if (first && h < 0 && j < -h && j < a.nx) Gh[j] = 0.f;
-      const int xl = a.nx - 1 - j;
-      if (last && h > 0 && j < h && xl >= 0) Gh[xl] = 0.f;
-    }
-  }
+  // h < 0 (x < -h), the last for h > 0 (x >= nx - h); nh <= 64 lanes
+  if (seg == 0 && lane < a.nx)
+    for (int H = w; H < a.nh; H += 4)
+      if (lane < a.nh - H) G[(int64_t)H * a.N + rb + lane] = 0.f;
+  const int xl = a.nx - 1 - lane;
+  if (seg == a.nseg - 1 && xl >= 0)
+    for (int H = a.nh + 1 + w; H < nout; H += 4)
+      if (lane < H - a.nh) G[(int64_t)H * a.N + rb + xl] = 0.f;
 }
 
-// rounds of 32-cell tiles whose products fit the three staging buffers (the
-// output rows leave through the same LDS)
-template <int NBT, int NT, int GR>
-static int gm_rounds(int nh) {
-  const int nout = 2 * nh + 1, room = 3 * gm_buf(NT, NBT, GR);
-  int tr = NT;
-  while (tr > 1 && nout * (32 * tr + 1) > room) --tr;
-  return nout * (32 * tr + 1) <= room ? tr : 0;
-}
-
-template <int NBT, int NT, int GR>
+template <int NBT, int NT>
 static hipError_t gm_launch(const float *U, const float *V, GatherArgs a, int64_t rows, double scale,
                             float *G, hipStream_t st) {
   a.nseg = (a.nx + 32 * NT - 1) / (32 * NT);
@@ -380,26 +364,31 @@ static hipError_t gm_launch(const float *U, const float *V, GatherArgs a, int64_
   const int64_t nb = rows * a.nseg;
   if (nb > 0x7fffffff) return hipErrorInvalidValue;
   a.nblk = (int)nb;
-  a.hgs = gm_rounds<NBT, NT, GR>(a.nh);
-  if (a.hgs < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_offset_gathers_mfma<NBT, NT, GR>), dim3(a.nblk), dim3(256), 0, st, U, V, a,
-                     (float)scale, G);
+  // 16-byte loads want the fields' tiles on 16-byte boundaries (fstride is a
+  // multiple of 32); else four times the loads, 4 bytes per lane
+  const bool wide = ((reinterpret_cast<uintptr_t>(U) | reinterpret_cast<uintptr_t>(V)) & 15) == 0;
+  if (wide)
+    hipLaunchKernelGGL((k_offset_gathers_mfma<NBT, NT, true>), dim3(a.nblk), dim3(256), 0, st, U, V,
+                       a, (float)scale, G);
+  else
+    hipLaunchKernelGGL((k_offset_gathers_mfma<NBT, NT, false>), dim3(a.nblk), dim3(256), 0, st, U, V,
+                       a, (float)scale, G);
   return hipGetLastError();
 }
 
-template <int NT, int GR>
+template <int NT>
 static hipError_t gm_dispatch(const float *U, const float *V, GatherArgs a, int64_t rows,
                               double scale, float *G, hipStream_t st) {
   switch ((16 + 2 * a.nh + 15) / 16) {
-    case 1: return gm_launch<1, NT, GR>(U, V, a, rows, scale, G, st);
-    case 2: return gm_launch<2, NT, GR>(U, V, a, rows, scale, G, st);
-    case 3: return gm_launch<3, NT, GR>(U, V, a, rows, scale, G, st);
-    case 4: return gm_launch<4, NT, GR>(U, V, a, rows, scale, G, st);
-    case 5: return gm_launch<5, NT, GR>(U, V, a, rows, scale, G, st);
-    case 6: return gm_launch<6, NT, GR>(U, V, a, rows, scale, G, st);
-    case 7: return gm_launch<7, NT, GR>(U, V, a, rows, scale, G, st);
-    case 8: return gm_launch<8, NT, GR>(U, V, a, rows, scale, G, st);
-    case 9: return gm_launch<9, NT, GR>(U, V, a, rows, scale, G, st);
+    case 1: return gm_launch<1, NT>(U, V, a, rows, scale, G, st);
+    case 2: return gm_launch<2, NT>(U, V, a, rows, scale, G, st);
+    case 3: return gm_launch<3, NT>(U, V, a, rows, scale, G, st);
+    case 4: return gm_launch<4, NT>(U, V, a, rows, scale, G, st);
+    case 5: return gm_launch<5, NT>(U, V, a, rows, scale, G, st);
+    case 6: return gm_launch<6, NT>(U, V, a, rows, scale, G, st);
+    case 7: return gm_launch<7, NT>(U, V, a, rows, scale, G, st);
+    case 8: return gm_launch<8, NT>(U, V, a, rows, scale, G, st);
+    case 9: return gm_launch<9, NT>(U, V, a, rows, scale, G, st);
   }
   return hipErrorInvalidValue;
 }
@@ -463,7 +452,7 @@ hipError_t launch_offset_gathers(const T *U, const T *V, int nfield, int64_t fst
   if (rows <= 0) return hipSuccess;
   if constexpr (sizeof(T) == 4) {
     // 128-cell segments, chunks of 8 probe rows
-    return gm_dispatch<4, 8>(U, V, a, rows, scale, G, st);
+    return gm_dispatch<4>(U, V, a, rows, scale, G, st);
   } else {
     constexpr int GCX = gather_cx<T>(), gx = 64, CB = gx / GCX;
     a.hgs = (2 * nh + 1 + GBH - 1) / GBH;          // offset blocks
