@@ -1519,6 +1519,7 @@ struct rtm_batch {
   int32_t nsrc_total = 0, nrec_total = 0;
   bool ragged = false;  // a row length that is no multiple of four
   bool stream = false;  // the levels of one step exceed the memory-side cache
+  bool wide = false;    // tiles of 128 x 8 cells instead of 64 x 16
   // cached graph of the last fwi_gradient_batched launch sequence
   hipGraphExec_t gexec = nullptr;
   uint64_t gkey = 0;
@@ -1558,17 +1559,17 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
     b->nsrc_total += shots[i].nsrc;
     b->nrec_total += shots[i].nrec;
   }
-  // tile table: 64 x 16 column tiles of every shot, z split until the launch
+  // tile table: column tiles (64 x 16 cells, or 128 x 8) of every shot, z split until the launch
   // has >= 2 x rtm_set_stencil_blocks workgroups (default 4096): the windows
   // are shallow (128-256 planes) and the extra waves in flight outweigh the
   // chunks' warm-up planes.  Chunks of at least 16 planes where the shots'
   // levels stream from HBM, shorter where they stay in the memory-side cache
   // (the warm-up planes then cost less than idle CUs and a long chain of
   // planes).  Fixed when the batch is created.
-  int nzc = 1;
+  int nzc = 1, tx = 64, ty = 16;
   auto count = [&](int z) {
     int64_t t = 0;
-    for (auto *p : b->P) t += ((p->d.nx + 63) / 64) * ((p->d.ny + 15) / 16) * (int64_t)z;
+    for (auto *p : b->P) t += ((p->d.nx + tx - 1) / tx) * ((p->d.ny + ty - 1) / ty) * (int64_t)z;
     return t;
   };
   int minz = INT32_MAX;
@@ -1579,11 +1580,27 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
     b->ragged |= p->d.nx % 4 != 0;
   }
   b->stream = 16 * cells > (int64_t)640000000;
+  // Rows that are no multiple of four cut a cache line at every tile's edge;
+  // where they stream from HBM, half as many edges are worth up to a quarter
+  // of idle lanes (8 windows of 128^3 .. 256 x 320 x 320, 92.6 M cells: 178 ms
+  // a gradient against 184).
+  if (b->ragged && b->stream) {
+    int64_t c64 = 0, c128 = 0;
+    bool fits = true;
+    for (auto *p : b->P) {
+      const int64_t rows = p->d.ny * p->d.nz;
+      c64 += (p->d.nx + 63) / 64 * 64 * rows;
+      c128 += (p->d.nx + 127) / 128 * 128 * rows;
+      fits = fits && p->d.ny <= 8 * 0x7fff;
+    }
+    b->wide = fits && 4 * c128 <= 5 * c64;
+  }
+  if (b->wide) tx = 128, ty = 8;
   const int minp = b->stream ? 16 : min_planes(4 * cells);
   while (count(nzc) < 2 * (int64_t)g_stencil_blocks && minz / (nzc * 2) >= minp) nzc *= 2;
   for (int i = 0; i < nshots; ++i) {
     const rtm_desc &d = b->P[i]->d;
-    const int ntx = (int)((d.nx + 63) / 64), nty = (int)((d.ny + 15) / 16);
+    const int ntx = (int)((d.nx + tx - 1) / tx), nty = (int)((d.ny + ty - 1) / ty);
     const int zc = (int)((d.nz + nzc - 1) / nzc);
     if (ntx > 0xffff || nty > 0x7fff) {
       rtm_batch_destroy(b);
@@ -1731,7 +1748,7 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   int s0 = 0;
   for (int s = 0; s < nt; ++s) {
     HIP_TRY(launch_stencil_batched<float>(shots, iof, src_t.mapped, tiles, ntiles, s, s, variant,
-                                          b->ragged, st, g_stencil_alternate ? (s & 1) : 0));
+                                          b->ragged, b->wide, st, g_stencil_alternate ? (s & 1) : 0));
     if (!src_t.mapped) HIP_TRY(launch_inject_batched<float>(shots, iof, src_t, s, s, st));
     if (s + 1 - s0 == k || s == nt - 1) {
       HIP_TRY(launch_sample_batched<float>(shots, iof, rec_t, s0, s + 1 - s0, st));
@@ -1755,7 +1772,7 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   s0 = 0;
   for (int s = 0; s < nt; ++s) {
     HIP_TRY(launch_stencil_batched<float>(shots, ioa, rec_t.mapped, tiles, ntiles, s, nt - 1 - s,
-                                          variant, b->ragged, st,
+                                          variant, b->ragged, b->wide, st,
                                           g_stencil_alternate ? (s & 1) : 0));
     if (!rec_t.mapped) HIP_TRY(launch_inject_batched<float>(shots, ioa, rec_t, s, nt - 1 - s, st));
     if (s + 1 - s0 == k || s == nt - 1) {

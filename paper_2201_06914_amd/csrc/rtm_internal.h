@@ -179,7 +179,7 @@ hipError_t launch_offset_gathers(const T *U, const T *V, int nfield, int64_t fst
 template <typename T>
 hipError_t launch_stencil_batched(const ShotStep<T> *shots, const ShotIO<T> *io, bool mapped,
                                   const int4 *tiles, int ntiles, int s, int n, int variant,
-                                  bool ragged, hipStream_t st, int rev = 0);
+                                  bool ragged, bool wide, hipStream_t st, int rev = 0);
 template <typename T>
 hipError_t launch_inject_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
                                  const BatchPoints<T> &pt, int s, int n, hipStream_t st);

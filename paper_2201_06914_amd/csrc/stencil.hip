@@ -691,10 +691,14 @@ static TileShape tile_shape(int variant) {
 //   one or more whole chunks per column fill nearly all 256 CUs with one
 //   workgroup each, that is fastest (384 x 512 x 512: 2 chunks, 256
 //   workgroups, 261; 16-plane chunks 288), else chunks of 16 planes (320 x 448
-//   x 448: 173; 196 workgroups of 160 planes 181; v1 220).  Rows that are no
-//   multiple of the vector cut cache lines at every tile's edge, which the
-//   hint would send to HBM twice: ordinary accesses (400 x 400 x 401: 250
-//   against 275 non-temporal; 320 x 448 x 447: 257 against 274).
+//   x 448: 173; 196 workgroups of 160 planes 181; v1 220).
+//   F32 rows that are no multiple of the vector cut a cache line at every
+//   tile's edge.  128-cell tiles have half as many edges and stream (320 x 448
+//   x 447: 236; 64 x 32 ordinary 261, non-temporal 274; 260 x 320 x 501 152,
+//   157), as long as they cover no more columns than 64-cell tiles; else two
+//   rows per thread and twice the workgroups (400 x 400 x 401: 246, 64 x 32
+//   265; 320 x 600 x 257: 189, 204, 128-cell tiles 207; 500 x 800 x 131: 215,
+//   224, 253).  FP64 rows: 64 x 16 tiles, ordinary.
 constexpr int64_t kSimpleCells = 150000;
 constexpr int64_t kStreamBytes = 640000000;
 template <typename T>
@@ -702,11 +706,15 @@ static int auto_variant(const StepArgs<T> &a, int *nzc) {
   if (a.N < kSimpleCells) return kStencilSimple;
   const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
   const bool ragged = a.nx % V16<T>::n != 0;
-  const int v = !stream ? 1 : ragged ? 2 : 8;
+  const bool edges = stream && ragged && sizeof(T) == 4;
+  const bool wide = edges && (a.nx + 127) / 128 * 2 == (a.nx + 63) / 64;
+  const int v = !stream ? 1 : edges ? (wide ? 12 : 3) : ragged ? 2 : 8;
   const TileShape t = tile_shape<T>(v);
   const int64_t tiles = (int64_t)((a.nx + t.tx - 1) / t.tx) * ((a.ny + t.ty - 1) / t.ty);
   if (!stream) {
     *nzc = z_split(a.nz, tiles, t.threads, kAutoBlocks, min_planes(a.N * (int)sizeof(T)));
+  } else if (edges) {
+    *nzc = z_split(a.nz, tiles, t.threads, wide ? kAutoBlocks : 2 * kAutoBlocks, 16);
   } else {
     const int c = (int)std::min<int64_t>(256 / tiles, a.nz / 16);
     *nzc = c >= 1 && c * tiles >= 230 && !ragged ? c : std::max(1, a.nz / 16);
@@ -944,14 +952,17 @@ hipError_t launch_sample_block(const PointTables<T> &pt, const T *ring, const T 
 template <typename T>
 hipError_t launch_stencil_batched(const ShotStep<T> *shots, const ShotIO<T> *io, bool mapped,
                                   const int4 *tiles, int ntiles, int s, int n, int variant,
-                                  bool ragged, hipStream_t st, int rev) {
+                                  bool ragged, bool wide, hipStream_t st, int rev) {
   if (ntiles <= 0) return hipSuccess;
   const bool nt = variant >= 7 && variant <= 12;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(ntiles), dim3(256), 0, st, shots, io, (int)mapped, tiles,
                        ntiles, s, n, rev);
   };
-  if (ragged) {
+  if (wide) {
+    if (nt) go(k_stencil3d_batched<T, 128, 8, 1, true, true>);
+    else go(k_stencil3d_batched<T, 128, 8, 1, false, true>);
+  } else if (ragged) {
     if (nt) go(k_stencil3d_batched<T, 64, 16, 1, true, true>);
     else go(k_stencil3d_batched<T, 64, 16, 1, false, true>);
   } else {
@@ -1020,7 +1031,7 @@ hipError_t launch_sample_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
 }
 template hipError_t launch_stencil_batched<float>(const ShotStep<float> *, const ShotIO<float> *,
                                                   bool, const int4 *, int, int, int, int, bool,
-                                                  hipStream_t, int);
+                                                  bool, hipStream_t, int);
 template hipError_t launch_inject_batched<float>(const ShotStep<float> *, const ShotIO<float> *,
                                                  const BatchPoints<float> &, int, int,
                                                  hipStream_t);
