@@ -695,10 +695,10 @@ static TileShape tile_shape(int variant) {
 //   F32 rows that are no multiple of the vector cut a cache line at every
 //   tile's edge.  128-cell tiles have half as many edges and stream (320 x 448
 //   x 447: 236; 64 x 32 ordinary 261, non-temporal 274; 260 x 320 x 501 152,
-//   157), as long as they cover no more columns than 64-cell tiles; else two
-//   rows per thread and twice the workgroups (400 x 400 x 401: 246, 64 x 32
-//   265; 320 x 600 x 257: 189, 204, 128-cell tiles 207; 500 x 800 x 131: 215,
-//   224, 253).  FP64 rows: 64 x 16 tiles, ordinary.
+//   157), as long as they cover at most a seventh more columns than 64-cell
+//   tiles; else two rows per thread and twice the workgroups (320 x 600 x 257:
+//   189, 204, 128-cell tiles 207; 500 x 800 x 131: 215, 224, 253).  FP64 rows:
+//   64 x 16 tiles, ordinary.
 constexpr int64_t kSimpleCells = 150000;
 constexpr int64_t kStreamBytes = 640000000;
 template <typename T>
@@ -707,14 +707,14 @@ static int auto_variant(const StepArgs<T> &a, int *nzc) {
   const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
   const bool ragged = a.nx % V16<T>::n != 0;
   const bool edges = stream && ragged && sizeof(T) == 4;
-  const bool wide = edges && (a.nx + 127) / 128 * 2 == (a.nx + 63) / 64;
+  const bool wide = edges && (a.nx + 127) / 128 * 14 <= (a.nx + 63) / 64 * 8;
   const int v = !stream ? 1 : edges ? (wide ? 12 : 3) : ragged ? 2 : 8;
   const TileShape t = tile_shape<T>(v);
   const int64_t tiles = (int64_t)((a.nx + t.tx - 1) / t.tx) * ((a.ny + t.ty - 1) / t.ty);
   if (!stream) {
     *nzc = z_split(a.nz, tiles, t.threads, kAutoBlocks, min_planes(a.N * (int)sizeof(T)));
   } else if (edges) {
-    *nzc = z_split(a.nz, tiles, t.threads, wide ? kAutoBlocks : 2 * kAutoBlocks, 16);
+    *nzc = z_split(a.nz, tiles, t.threads, wide ? kAutoBlocks : 2 * kAutoBlocks, 6);
   } else {
     const int c = (int)std::min<int64_t>(256 / tiles, a.nz / 16);
     *nzc = c >= 1 && c * tiles >= 230 && !ragged ? c : std::max(1, a.nz / 16);
