@@ -279,7 +279,9 @@ def autotune_stencil(plan: Plan, m, work=None, steps: int = 20, apply: bool = Tr
     if cache:
         props = torch.cuda.get_device_properties(m.device)
         arch = getattr(props, "gcnArchName", props.name)
-        key = f"{arch}|{plan.spec.ndim}|{'x'.join(map(str, plan.spec.shape))}|{plan.spec.field}"
+        # "tiles2": what the variant ids stand for; entries of other sets don't count
+        key = (f"tiles2|{arch}|{plan.spec.ndim}|{'x'.join(map(str, plan.spec.shape))}"
+               f"|{plan.spec.field}")
         if os.path.exists(cache):
             with open(cache) as f:
                 table = json.load(f)

@@ -124,7 +124,7 @@ def autotune_batch(specs, shots, variants=(1, 3, 7, 11, 12), blocks=(2048, 4096,
     if cache is None:
         cache = os.environ.get("RTM_TUNE_CACHE") or None
     dev = shots[0]["m"].device
-    key = ("batch|" + _arch(dev) + "|" + ";".join("x".join(map(str, s.shape)) for s in specs)
+    key = ("batch|tiles2|" + _arch(dev) + "|" + ";".join("x".join(map(str, s.shape)) for s in specs)
            + f"|{specs[0].field}|{specs[0].probe}|r{specs[0].r}|k{','.join(map(str, k_blocks))}")
     hit = _cache_get(cache, key)
     if hit:
