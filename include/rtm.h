@@ -131,8 +131,8 @@ const char *rtm_status_str(rtm_status s);
  * z-marching variants (3D; x-width x y-rows, rows halved for F64): 1: 64x16,
  * 2: 64x32, 3: 64x32 with two rows per thread, 4: 64x8, 5: 32x32, 6: 128x8,
  * 7..12: as 1..6 with non-temporal streaming loads and stores, 13: 32x16.
- * Every choice gives bitwise-identical levels.  Batched shots run 64x16 tiles,
- * non-temporal for 7..12.
+ * Every choice gives bitwise-identical levels.  Batched shots run 64x16 tiles
+ * (128x8 where cut rows stream from HBM), non-temporal for 7..12.
  * rtm_set_stencil_blocks: the tiled acoustic kernels split z into the fewest
  * chunks (of at least 4 planes) that give a launch this many workgroups of
  * 256 threads' worth (default 2048, which leaves the split of the automatic
@@ -402,8 +402,8 @@ void rtm_set_exact_fused(int32_t on);
 void rtm_set_tti_shape(int32_t shape);
 /* Tuning hook, process wide: the tiled TTI kernels split z into the fewest
  * chunks (of at least 16 planes; fewer on grids that do not fill the chip)
- * that give a launch this many workgroups, for the forward step and for the transpose step (<= 0: the defaults, 2800
- * and 1750). */
+ * that give a launch this many workgroups, for the forward step and for the
+ * transpose step (<= 0: the defaults, 2800 and 1750). */
 void rtm_set_tti_blocks(int32_t forward, int32_t transpose);
 rtm_status fwi_gradient_exact(const rtm_plan *plan, const void *m, const double *src_pos,
                               const void *q, const double *rec_pos, const void *d_obs,
