@@ -668,7 +668,8 @@ def main():
     src, rec = wl.src_pos, wl.rec_pos
     del wl
     if a.stencil_variant is None:
-        tune = P.autotune_stencil(plan, m, work=work, steps=20)
+        tune = P.autotune_stencil(plan, m, work=work, steps=20,
+                                   blocks=(512, 768, 1024, 1536, 2048, 4096))
     else:
         P.set_stencil_variant(a.stencil_variant)
         P.set_stencil_blocks(a.stencil_blocks or 2048)
