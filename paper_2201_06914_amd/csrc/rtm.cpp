@@ -1520,6 +1520,7 @@ struct rtm_batch {
   bool ragged = false;  // a row length that is no multiple of four
   bool stream = false;  // the levels of one step exceed the memory-side cache
   bool wide = false;    // tiles of 128 x 8 cells instead of 64 x 16
+  bool tiled = true;    // every window's planes fit the tiles' 32-bit offsets
   // cached graph of the last fwi_gradient_batched launch sequence
   hipGraphExec_t gexec = nullptr;
   uint64_t gkey = 0;
@@ -1578,6 +1579,7 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
   for (auto *p : b->P) {
     cells += p->N;
     b->ragged |= p->d.nx % 4 != 0;
+    b->tiled = b->tiled && plane_fits(p->d.ny, p->d.nx, sizeof(float));
   }
   b->stream = 16 * cells > (int64_t)640000000;
   // Rows that are no multiple of four cut a cache line at every tile's edge;
@@ -1606,7 +1608,7 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
       rtm_batch_destroy(b);
       return fail(RTM_E_SHAPE, "shot %d: too many tiles", i);
     }
-    if (b->P[i]->N * 4 >= (int64_t(1) << 32)) {  // tiled kernels use 32-bit offsets
+    if (b->P[i]->N * 4 >= (int64_t(1) << 32)) {
       rtm_batch_destroy(b);
       return fail(RTM_E_SHAPE, "shot %d: a window of 4 GiB or more per level", i);
     }
@@ -1660,7 +1662,7 @@ static rtm_status pack_batch_points(const rtm_batch *b, const rtm_shot_io *io, b
                                     std::vector<ShotIO<float>> &sio, BatchPoints<float> *t) {
   HostPoints<float> hp;
   std::vector<int32_t> sshot, slocal, ishot, map;
-  t->mapped = true;
+  t->mapped = b->tiled;
   for (int i = 0; i < b->ns; ++i) {
     const rtm_plan *P = b->P[i];
     const int32_t n = rec ? P->d.nrec : P->d.nsrc;
@@ -1745,10 +1747,26 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
     HIP_TRY(launch_fill<float>(lvl(i, -1), b->P[i]->N, 0.f, st));
     HIP_TRY(launch_fill<float>(lvl(i, 0), b->P[i]->N, 0.f, st));
   }
+  // step s at time index n: one launch for all shots, or a launch per shot
+  // where a window's plane exceeds the tiles' offsets
+  auto step = [&](const ShotIO<float> *io_, bool mapped, int s, int n) -> hipError_t {
+    const int rev = g_stencil_alternate ? (s & 1) : 0;
+    if (b->tiled)
+      return launch_stencil_batched<float>(shots, io_, mapped, tiles, ntiles, s, n, variant,
+                                           b->ragged, b->wide, st, rev);
+    for (int i = 0; i < b->ns; ++i) {
+      StepArgs<float> a = step_args<float>(b->P[i], static_cast<const float *>(io[i].m));
+      a.cur = lvl(i, s);
+      a.prev = lvl(i, s - 1);
+      a.next = lvl(i, s + 1);
+      const hipError_t e = launch_stencil<float>(3, a, InjMap<float>(), -1, kAutoBlocks, st, rev);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
   int s0 = 0;
   for (int s = 0; s < nt; ++s) {
-    HIP_TRY(launch_stencil_batched<float>(shots, iof, src_t.mapped, tiles, ntiles, s, s, variant,
-                                          b->ragged, b->wide, st, g_stencil_alternate ? (s & 1) : 0));
+    HIP_TRY(step(iof, src_t.mapped, s, s));
     if (!src_t.mapped) HIP_TRY(launch_inject_batched<float>(shots, iof, src_t, s, s, st));
     if (s + 1 - s0 == k || s == nt - 1) {
       HIP_TRY(launch_sample_batched<float>(shots, iof, rec_t, s0, s + 1 - s0, st));
@@ -1771,9 +1789,7 @@ static rtm_status batch_enqueue(const rtm_batch *b, const rtm_shot_io *io, doubl
   }
   s0 = 0;
   for (int s = 0; s < nt; ++s) {
-    HIP_TRY(launch_stencil_batched<float>(shots, ioa, rec_t.mapped, tiles, ntiles, s, nt - 1 - s,
-                                          variant, b->ragged, b->wide, st,
-                                          g_stencil_alternate ? (s & 1) : 0));
+    HIP_TRY(step(ioa, rec_t.mapped, s, nt - 1 - s));
     if (!rec_t.mapped) HIP_TRY(launch_inject_batched<float>(shots, ioa, rec_t, s, nt - 1 - s, st));
     if (s + 1 - s0 == k || s == nt - 1) {
       if ((s_ = probe(true, s0, s + 1 - s0))) return s_;

@@ -129,6 +129,13 @@ struct ProbeArgs {
   int *queue = nullptr;
 };
 
+// the tiled stencil addresses a plane with 32-bit byte offsets below 2 GiB (an
+// offset of 2 GiB is its mark of a cell outside the grid)
+constexpr uint32_t kPlaneBytes = 0x80000000u;
+inline bool plane_fits(int64_t ny, int64_t nx, size_t esz) {
+  return ny * nx * (int64_t)esz < (int64_t)kPlaneBytes;
+}
+
 // the shortest z chunks of the tiled stencil for a step over levels of this
 // many bytes that stay in the caches (stencil.hip)
 int min_planes(int64_t bytes);

@@ -252,7 +252,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // end return zero and stores there are dropped, so a cell outside the grid
 // takes the offset kOff (a per-thread constant) and a plane outside the grid
 // an empty buffer; neither needs a branch or per-load arithmetic.
-constexpr uint32_t kOff = 0x80000000u;  // past the end of any plane (planes are below 2 GiB)
+constexpr uint32_t kOff = kPlaneBytes;  // past the end of any plane (see plane_fits)
 template <typename T>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const T *p, uint32_t bytes) {
   // gfx9 buffer descriptor word 3: 32-bit data format, no swizzle
@@ -727,11 +727,9 @@ hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, 
                           int target_blocks, hipStream_t st, int rev) {
   constexpr int F = sizeof(T) / 4;
   const EpiArgs<T> e{};
-  // a plane is addressed with 32-bit byte offsets below kOff
-  const bool fits = (int64_t)a.ny * a.nx * (int64_t)sizeof(T) < (int64_t)kOff;
   int nzc = 1;
   const bool rule = variant < 0;
-  if (ndim != 3 || !fits) {
+  if (ndim != 3 || !plane_fits(a.ny, a.nx, sizeof(T))) {
     variant = kStencilSimple;
   } else if (rule) {
     variant = auto_variant(a, &nzc);
@@ -781,7 +779,7 @@ hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, const InjMap<T> &i
                               int target_blocks, int epi, const EpiArgs<T> &e, hipStream_t st,
                               int rev) {
   if (ndim != 3 || sizeof(T) != 4 || variant == kStencilSimple ||
-      (int64_t)a.ny * a.nx * (int64_t)sizeof(T) >= (int64_t)kOff)
+      !plane_fits(a.ny, a.nx, sizeof(T)))
     return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 4) {
     const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
