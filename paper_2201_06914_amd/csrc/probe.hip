@@ -110,6 +110,14 @@ hipError_t launch_probe_vec(const ProbeArgs<T> &p, const void *Z, bool z_is_i8, 
   else go(k_probe_vec<T, T>, (const T *)nullptr);
   return hipGetLastError();
 }
+
+// workgroups of a probe launch that wants one per four tiles: a dispatch holds
+// fewer than 2^32 work items (the kernels stride over what is left)
+static constexpr int64_t groups_for(int64_t want) {
+  return want < 1 ? 1 : want < (1 << 24) ? want : (1 << 24) - 1;
+}
+static_assert(256 * groups_for((int64_t)1 << 24) < (int64_t)1 << 32, "grids of 2^31 - 1 cells");
+
 // ---------------------------------------------------------------------------
 // FP64 on the matrix cores
 // ---------------------------------------------------------------------------
@@ -208,7 +216,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_f64(ProbeArgs<double> p,
 template <int KS, typename ZT>
 static void launch_f64_ks(const ProbeArgs<double> &p, const void *Z, hipStream_t st) {
   const int MT = (p.r + 15) / 16;
-  const int64_t want = ((p.N + 31) / 32 + 3) / 4;  // one workgroup per four tiles
+  const int64_t want = groups_for(((p.N + 31) / 32 + 3) / 4);  // one workgroup per four tiles
   const size_t shm = (size_t)MT * KS * 256 * 8;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)want), dim3(256), shm, st, p,
@@ -752,7 +760,7 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
       if (cap < 2048) cap = 2048;  // small grids: fill the chip
     }
     if (cap > want) cap = want;
-    return (unsigned)(cap > 0 ? cap : 1);
+    return (unsigned)groups_for(cap);
   };
   // work queue (fast kernel only): reset the counter, then launch
   ProbeArgs<float> pq = p;
