@@ -17,6 +17,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -342,6 +343,25 @@ struct HostPoints {
   int64_t lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
 };
 
+// The entries' numbers in the low halves of `order`, by cell and then in the
+// order given: a radix sort on the cells' span, 11 bits a pass (the
+// 524 k entries of an off-grid 256 x 256 spread on a 384 x 512 x 512 grid take
+// 4 ms, std::sort of the same keys 13).
+static void by_cell(const int32_t *cell, size_t n, std::vector<uint64_t> &order) {
+  const auto mm = std::minmax_element(cell, cell + n);
+  const uint32_t lo = (uint32_t)*mm.first, span = (uint32_t)*mm.second - lo;
+  order.resize(n);
+  for (size_t e = 0; e < n; ++e) order[e] = (uint64_t)((uint32_t)cell[e] - lo) << 32 | e;
+  std::vector<uint64_t> to(n);
+  for (int bit = 0; bit < 32 && span >> bit; bit += 11) {
+    size_t at[2049] = {0};
+    for (uint64_t k : order) ++at[(k >> 32 >> bit & 2047) + 1];
+    for (int i = 0; i < 2048; ++i) at[i + 1] += at[i];
+    for (uint64_t k : order) to[at[k >> 32 >> bit & 2047]++] = k;
+    order.swap(to);
+  }
+}
+
 // Adds a point set: multilinear weights of each point; injection entries
 // grouped by cell (points in increasing order within a cell) so that the
 // injection sums a cell's contributions in a fixed order without atomics.
@@ -352,10 +372,7 @@ static rtm_status add_points(const rtm_plan *P, int32_t n, const double *pos, Ho
   hp.c0 = hp.icell.size();
   const size_t e0 = hp.sidx.size();
   hp.soff.reserve(hp.soff.size() + n);
-  hp.sidx.reserve(e0 + n);
-  hp.sw.reserve(e0 + n);
   std::vector<int32_t> pt;  // the point of each entry
-  pt.reserve(n);
   bool sorted = true;
   for (int32_t p = 0; p < n; ++p) {
     int64_t base[3];
@@ -372,6 +389,12 @@ static rtm_status add_points(const rtm_plan *P, int32_t n, const double *pos, Ho
       hp.lo[a] = p ? std::min(hp.lo[a], base[a]) : base[a];
       hp.hi[a] = p ? std::max(hp.hi[a], base[a] + ncor[a]) : base[a] + ncor[a];
     }
+    if (p == 0) {  // the points of a set mostly have as many corners as its first
+      const size_t room = (size_t)n * ncor[0] * ncor[1] * ncor[2];
+      hp.sidx.reserve(e0 + room);
+      hp.sw.reserve(e0 + room);
+      pt.reserve(room);
+    }
     for (int iz = 0; iz < ncor[0]; ++iz)
       for (int iy = 0; iy < ncor[1]; ++iy)
         for (int ix = 0; ix < ncor[2]; ++ix) {
@@ -385,15 +408,11 @@ static rtm_status add_points(const rtm_plan *P, int32_t n, const double *pos, Ho
         }
     hp.soff.push_back((int32_t)hp.sidx.size());
   }
-  // entries by cell, then by point: (cell, entry) keys, in order already for
-  // points along the grid's rows
+  // entries by cell, then by point; in order already for points along the
+  // grid's rows
   const size_t ne = pt.size();
-  std::vector<uint64_t> order(sorted ? 0 : ne);
-  if (!sorted) {
-    for (size_t e = 0; e < ne; ++e)
-      order[e] = (uint64_t)(uint32_t)hp.sidx[e0 + e] << 32 | (uint64_t)e;
-    std::sort(order.begin(), order.end());
-  }
+  std::vector<uint64_t> order;
+  if (!sorted) by_cell(hp.sidx.data() + e0, ne, order);
   hp.icell.reserve(hp.icell.size() + ne);
   hp.ioff.reserve(hp.ioff.size() + ne);
   hp.ipt.reserve(hp.ipt.size() + ne);
@@ -441,16 +460,19 @@ static bool make_map(const rtm_plan *P, const HostPoints<T> &hp, size_t cap,
 }
 
 // Packs tables for one upload: only what a call uses travels (the layout is
-// the call's own, within the bytes that the plan set aside).
+// the call's own, within the bytes that the plan set aside: `room`).
 struct Pack {
-  std::vector<unsigned char> host;
-  char *dev;  // where the packed bytes go
-  explicit Pack(char *d) : dev(d) {}
+  char *dev;          // where the packed bytes go
+  size_t room, size = 0;
+  std::unique_ptr<unsigned char[]> host;
+  bool fits = true;   // everything put so far is there
+  Pack(char *d, size_t r) : dev(d), room(r), host(new unsigned char[r]) {}
   template <typename T>
   const T *put(const std::vector<T> &v) {
-    const size_t at = host.size();
-    host.resize(align256(at + sizeof(T) * v.size()));
-    if (!v.empty()) std::memcpy(host.data() + at, v.data(), sizeof(T) * v.size());
+    const size_t at = size, bytes = sizeof(T) * v.size();
+    size = align256(at + bytes);
+    fits = fits && size <= room;
+    if (fits && bytes) std::memcpy(host.get() + at, v.data(), bytes);
     return reinterpret_cast<const T *>(dev + at);
   }
 };
@@ -493,15 +515,14 @@ template <typename T>
 static rtm_status upload_points(const rtm_plan *P, char *work, hipStream_t st,
                                 const double *src_pos, PointTables<T> *src_t,
                                 const double *rec_pos, PointTables<T> *rec_t) {
-  Pack pk(work + P->tab_off);
+  Pack pk(work + P->tab_off, P->tab_bytes);
   rtm_status s;
   if (src_pos && src_t && (s = pack_points<T>(P, P->d.nsrc, src_pos, P->smap, pk, src_t))) return s;
   if (rec_pos && rec_t && (s = pack_points<T>(P, P->d.nrec, rec_pos, P->rmap, pk, rec_t))) return s;
-  if (pk.host.size() > P->tab_bytes) return fail(RTM_E_WORKSPACE, "point tables do not fit");
+  if (!pk.fits) return fail(RTM_E_WORKSPACE, "point tables do not fit");
   HIP_TRY(launch_status_clear(status_word(P, work), st));
-  if (!pk.host.empty()) {
-    HIP_TRY(hipMemcpyAsync(work + P->tab_off, pk.host.data(), pk.host.size(), hipMemcpyHostToDevice,
-                           st));
+  if (pk.size) {
+    HIP_TRY(hipMemcpyAsync(work + P->tab_off, pk.host.get(), pk.size, hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
   }
   return RTM_OK;
@@ -1870,19 +1891,20 @@ extern "C" rtm_status fwi_gradient_batched(rtm_batch *b, const rtm_shot_io *io, 
                           (const void *)io[i].resid, (const void *)io[i].grad})
       mix(p);
   }
-  Pack pk(w + b->tab_off);
+  Pack pk(w + b->tab_off, b->tab_bytes);
   BatchTables bt;
   bt.shots = pk.put(shots);
   bt.tiles = pk.put(b->tile_host);
-  const size_t at_f = pk.host.size();
+  const size_t at_f = pk.size;
   bt.iof = pk.put(iof);  // rewritten below, with the maps
-  const size_t at_a = pk.host.size();
+  const size_t at_a = pk.size;
   bt.ioa = pk.put(ioa);
   rtm_status s = pack_batch_points(b, io, false, pk, iof, &bt.src);
   if (s) return s;
   if ((s = pack_batch_points(b, io, true, pk, ioa, &bt.rec))) return s;
-  std::memcpy(pk.host.data() + at_f, iof.data(), sizeof(ShotIO<float>) * b->ns);
-  std::memcpy(pk.host.data() + at_a, ioa.data(), sizeof(ShotIO<float>) * b->ns);
+  if (!pk.fits) return fail(RTM_E_WORKSPACE, "point tables do not fit");
+  std::memcpy(pk.host.get() + at_f, iof.data(), sizeof(ShotIO<float>) * b->ns);
+  std::memcpy(pk.host.get() + at_a, ioa.data(), sizeof(ShotIO<float>) * b->ns);
   if (use_graph)  // a captured sequence holds pointers into the packed tables
     for (int i = 0; i < b->ns; ++i)
       for (int rec = 0; rec < 2; ++rec) {
@@ -1898,8 +1920,7 @@ extern "C" rtm_status fwi_gradient_batched(rtm_batch *b, const rtm_shot_io *io, 
                                                    : b->stream && !b->ragged ? 7 : 1;
   key = (key ^ (uint64_t)variant) * 1099511628211ull;
   key = (key ^ (uint64_t)(g_stencil_alternate + 64)) * 1099511628211ull;
-  if (pk.host.size() > b->tab_bytes) return fail(RTM_E_WORKSPACE, "point tables do not fit");
-  HIP_TRY(hipMemcpyAsync(w + b->tab_off, pk.host.data(), pk.host.size(), hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(w + b->tab_off, pk.host.get(), pk.size, hipMemcpyHostToDevice, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (!use_graph) return batch_enqueue(b, io, misfit, w, bt, variant, st);
   if (!b->gexec || b->gkey != key) {
