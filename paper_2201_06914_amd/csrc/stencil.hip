@@ -681,6 +681,11 @@ static TileShape tile_shape(int variant) {
 //   kernel (40 x 36 x 70: 4.3 against 4.2), and a folded injection waits for
 //   one cell's entries per thread, not four's (gradient there 1.40 against
 //   1.55 ms).  64^3: 5.8 against 4.0.
+//   So do grids that would leave four fifths of the tiles' lanes idle (FP64,
+//   and F32 in brackets, thread per cell against tiled): 300 x 300 x 20, 31 %
+//   of the lanes, 27 against 25 (23, 16); 1000 x 16 x 16, 25 %, 8.3 against
+//   9.6 (6.7, 7.3); 64 x 2000 x 8, 12 %, 18 against 29 (15, 19); 400 x 400 x 4
+//   13 against 33 (11, 21); 3000 x 300 x 1 16 against 181 (13, 93).
 //   While the four arrays of a step (16 N bytes) stay near the 256 MB
 //   memory-side cache, ordinary loads and short chunks on 64 x 16 tiles: a
 //   chunk re-reads eight planes, but they hit the caches, and a step is a chain
@@ -703,7 +708,9 @@ constexpr int64_t kSimpleCells = 150000;
 constexpr int64_t kStreamBytes = 640000000;
 template <typename T>
 static int auto_variant(const StepArgs<T> &a, int *nzc) {
-  if (a.N < kSimpleCells) return kStencilSimple;
+  constexpr int F = sizeof(T) / 4;
+  const int64_t lanes = (int64_t)((a.nx + 63) / 64 * 64) * ((a.ny + 16 / F - 1) / (16 / F) * (16 / F));
+  if (a.N < kSimpleCells || lanes > 5 * (int64_t)a.ny * a.nx) return kStencilSimple;
   const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
   const bool ragged = a.nx % V16<T>::n != 0;
   const bool edges = stream && ragged && sizeof(T) == 4;
