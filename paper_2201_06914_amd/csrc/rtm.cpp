@@ -616,10 +616,8 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
   T *smp_out = static_cast<T *>(io.smp_out);
   int s0 = nb;
   // 2D: several steps per launch, up to the end of the probe block, when the
-  // step kernels take the injection (FP64: up to 2 M cells, see
-  // k_stencil2d_steps)
-  const bool multi = ndim == 2 && variant < 0 && (sizeof(T) == 4 || P->N < 2000000) &&
-                     (inj.ncell == 0 || !inj_vals || inj.inj.map);
+  // step kernels take the injection
+  const bool multi = ndim == 2 && variant < 0 && (inj.ncell == 0 || !inj_vals || inj.inj.map);
   for (int s = nb; s < ne; ++s) {
     const int n = io.adjoint ? d.nt - 1 - s : s;
     a.cur = level(s);
@@ -627,8 +625,8 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
     a.next = level(s + 1);
     TimedLaunch tl;
     prof_begin(KT_STENCIL, s, st, &tl);
-    if (multi) {
-      const int steps = std::min({kMaxSteps2D, s0 + d.k_block - s, ne - s});
+    const int steps = std::min({kMaxSteps2D, s0 + d.k_block - s, ne - s});
+    if (multi && stencil2d_multi<T>(P->N, steps)) {
       HIP_TRY(launch_stencil2d<T>(a, step_inj(inj, inj_vals, n),
                                   (io.adjoint ? -1 : 1) * (int64_t)inj.npts, ring, P->ld, P->R, s,
                                   steps, st));

@@ -153,6 +153,8 @@ hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, 
 // step s, its values advancing by vstride per step (no map: none)
 constexpr int kMaxSteps2D = 4;
 template <typename T>
+bool stencil2d_multi(int64_t N, int nsteps);  // whether that beats nsteps launches
+template <typename T>
 hipError_t launch_stencil2d(const StepArgs<T> &a, const InjMap<T> &inj, int64_t vstride, T *ring,
                             int64_t ld, int R, int s, int nsteps, hipStream_t st);
 // exact comparator: stencil step with a fused epilogue (hipErrorInvalidValue

@@ -137,6 +137,25 @@ __global__ __launch_bounds__(256) void k_stencil_simple(StepArgs<T> a, InjMap<T>
 // 2.3), 301 x 901 4.8 -> 3.6 (6.1 -> 5.4), 600 x 1000 7.3 -> 5.4 (8.7 -> 7.9),
 // 1200 x 2000 20.5 -> 17.4 (24.3 -> 24.9: FP64 keeps the launch per step there).
 constexpr int kSteps2D = kMaxSteps2D;
+
+// The halo is loaded and mostly computed whether one step follows or four, so
+// the fewer steps a launch has (short probe blocks, the end of one), the
+// smaller the grid up to which it is worth it.  us per step, a thread per cell
+// against this kernel:
+//   1 step   221 x 221 7.0 / 5.9 (FP64 7.0 / 6.5), 300 x 500 7.0 / 7.6
+//            (7.9 / 10.2), 1200 x 2000 23 / 44
+//   2 steps  600 x 1000 11.1 / 9.1 (11.5 / 12.1; 400 x 600 8.4 / 7.2),
+//            1500 x 1300 20 / 23 (27 / 29)
+//   3 steps  1200 x 2000 23 / 22 (1500 x 1300 27 / 24), 2400 x 4000 73 / 79
+//   4 steps  2400 x 4000 73 / 69, 4000 x 8000 232 / 231, 8000 x 16000 921 / 937
+template <typename T>
+bool stencil2d_multi(int64_t N, int nsteps) {
+  static const int64_t below[2][kSteps2D] = {{64000, 1000000, 4000000, 16000000},
+                                             {64000, 250000, 2000000, 2000000}};
+  return nsteps >= 1 && nsteps <= kSteps2D && N < below[sizeof(T) == 8][nsteps - 1];
+}
+template bool stencil2d_multi<float>(int64_t, int);
+template bool stencil2d_multi<double>(int64_t, int);
 template <typename T, int TZ, int NW>
 __global__ __launch_bounds__(64 * NW) void k_stencil2d_steps(StepArgs<T> a, InjMap<T> inj,
                                                          int64_t vstride, T *ring, int64_t ld,

@@ -43,3 +43,28 @@ def test_thin_grids_run_a_thread_per_cell(shape, tiled, field):
         P.set_stencil_variant(-1)
     assert (named(names, "k_stencil3d_tiled") == 5) == tiled, names
     assert (named(names, "k_stencil_simple") == 5) != tiled, names
+
+
+# (grid, steps per block, launches of four, three, two and one steps by k_stencil2d_steps,
+# launches of one step by a thread per cell); 9 steps
+@pytest.mark.parametrize("field,shape,k,multi,simple", [
+    ("f32", (120, 1, 130), 1, 9, 0), ("f64", (120, 1, 130), 1, 9, 0),
+    ("f32", (300, 1, 310), 1, 0, 9), ("f64", (300, 1, 310), 2, 4, 1),
+    ("f32", (300, 1, 310), 5, 2, 1),                    # 4 + 1, 4
+    ("f32", (1010, 1, 1000), 2, 0, 9), ("f64", (520, 1, 500), 2, 0, 9),
+    ("f32", (1010, 1, 1000), 3, 3, 0), ("f32", (2010, 1, 2000), 3, 0, 9),
+    ("f32", (2010, 1, 2000), 4, 2, 1), ("f32", (4010, 1, 4000), 4, 0, 9),
+    ("f64", (1250, 1, 1500), 3, 3, 0), ("f64", (1450, 1, 1400), 4, 0, 9)])
+def test_2d_steps_per_launch(field, shape, k, multi, simple):
+    """2D launches of several steps only where they beat a launch per step."""
+    say(f"case: {shape} {field} k {k}")
+    run = _levels(shape, field, nt=9, k=k)
+    names = kernels(run)
+    got = run()
+    P.set_stencil_variant(0)
+    try:
+        assert torch.equal(got, run())
+    finally:
+        P.set_stencil_variant(-1)
+    assert named(names, "k_stencil2d_steps") == multi, names
+    assert named(names, "k_stencil_simple") == simple, names
