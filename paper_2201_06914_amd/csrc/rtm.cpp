@@ -431,15 +431,65 @@ static rtm_status add_points(const rtm_plan *P, int32_t n, const double *pos, Ho
   return RTM_OK;
 }
 
-// The map of the folded injection (InjMap) of the set added last, if its
-// cells' bounding box has at most `cap` cells.
+// what the steps that would take a folded injection run
+enum FoldInto {
+  FOLD_NONE,     // nothing (the set is sampled only, or the steps take none)
+  FOLD_CELLS,    // a thread per cell, 2D kernels
+  FOLD_CACHED,   // tiles, levels in the caches
+  FOLD_STREAM,   // tiles, levels from HBM
+};
 template <typename T>
-static bool make_map(const rtm_plan *P, const HostPoints<T> &hp, size_t cap,
+static FoldInto fold_into(const rtm_plan *P, bool epilogue = false) {
+  const rtm_desc &d = P->d;
+  const int variant = g_stencil_variant;
+  // (an epilogue's steps are tiled wherever a tiled kernel serves the grid)
+  const bool tiled =
+      stencil_tiled<T>(d.ndim, (int)d.nz, (int)d.ny, (int)d.nx, variant) ||
+      (epilogue && g_exact_fused && d.ndim == 3 && sizeof(T) == 4 && variant != kStencilSimple &&
+       plane_fits(d.ny, d.nx, sizeof(T)));
+  return !tiled ? FOLD_CELLS
+         : 4 * P->N * (int64_t)sizeof(T) > kStreamBytes ? FOLD_STREAM : FOLD_CACHED;
+}
+
+// The map of the folded injection (InjMap) of the set added last, if its
+// cells' bounding box has at most `cap` cells and the steps take it at less
+// than a launch of its own costs (about 3.5 us a step).
+// Threads that own one cell wait for its entries side by side, and any set is
+// cheaper in the step, but for FP64 2D grids whose steps are short of waves
+// (600 x 1000, 2395 points down a column, eight entries a cell: 15.0 us
+// against 13.5).
+// A tile marches z, and each plane of it that holds entries costs a chain of
+// loads that every wave waits for: 0.3 us a plane where a cell has one point of
+// weight one, 1.2 us and more off the grid, with its four cells per thread in
+// turn.  So a set on one plane (off the grid: two) is taken, a spread in depth is
+// not.  us per step, folded / launched: a 200 x 200 surface in 200^3 28 / 31 (off
+// the grid 31 / 31), in 384 x 512 x 512 257 / 261 (264 / 262; every seventh
+// point in 320 x 448 x 448 192 / 177: beyond the caches off-grid sets are
+// launched); wall of all y and z in 384 x 512 x 512 368 / 276 (off the grid 819 /
+// 280), of all x and z 490 / 261 (1067 / 267), in 128^3 14.5 / 12.4 (26.5 /
+// 13.3); a vertical column in 128^3 10.1 / 11.9 (13.4 / 12.3), in 384 x 512 x 512
+// 317 / 261 (503 / 260); 500 points in one cell of 128^3 256 / 90.
+template <typename T>
+static bool make_map(const rtm_plan *P, const HostPoints<T> &hp, size_t cap, FoldInto into,
                      std::vector<int32_t> &map, InjMap<T> *j) {
-  if (hp.icell.size() == hp.c0) return false;
-  const int64_t by = hp.hi[1] - hp.lo[1], bx = hp.hi[2] - hp.lo[2];
-  const int64_t vol = (hp.hi[0] - hp.lo[0]) * by * bx;
+  if (into == FOLD_NONE || hp.icell.size() == hp.c0) return false;
+  const int64_t by = hp.hi[1] - hp.lo[1], bx = hp.hi[2] - hp.lo[2], bz = hp.hi[0] - hp.lo[0];
+  const int64_t vol = bz * by * bx;
   if (vol > (int64_t)cap) return false;
+  int most = 1;         // entries of a cell
+  bool whole = true;    // single points of weight one
+  for (size_t c = hp.c0; c < hp.icell.size(); ++c) {
+    most = std::max(most, hp.ioff[c + 1] - hp.ioff[c]);
+    whole = whole && hp.iw[hp.ioff[c]] == T(1);
+  }
+  whole = whole && most == 1;
+  if (into == FOLD_CELLS) {
+    if (P->d.ndim == 2 && sizeof(T) == 8 && P->N >= 250000 && most > 2) return false;
+  } else if (whole) {
+    if (bz > 2 && !(by * bx == 1 && into == FOLD_CACHED)) return false;
+  } else if (bz > 2 || most > 4 || into == FOLD_STREAM) {
+    return false;
+  }
   map.assign((size_t)vol, -1);
   const uint32_t nx = (uint32_t)P->d.nx, ny = (uint32_t)P->d.ny;
   for (size_t c = hp.c0; c < hp.icell.size(); ++c) {
@@ -479,12 +529,12 @@ struct Pack {
 
 template <typename T>
 static rtm_status pack_points(const rtm_plan *P, int32_t n, const double *pos, size_t map_cap_,
-                              Pack &pk, PointTables<T> *t) {
+                              FoldInto into, Pack &pk, PointTables<T> *t) {
   HostPoints<T> hp;
   rtm_status s = add_points(P, n, pos, hp);
   if (s) return s;
   std::vector<int32_t> map;
-  const bool fold = make_map(P, hp, map_cap_, map, &t->inj);
+  const bool fold = make_map(P, hp, map_cap_, into, map, &t->inj);
   t->soff = pk.put(hp.soff);
   t->sidx = pk.put(hp.sidx);
   t->sw = pk.put(hp.sw);
@@ -507,18 +557,22 @@ static uint32_t *status_word(const rtm_plan *P, char *work) {
   return reinterpret_cast<uint32_t *>(work + P->status.off);
 }
 
-// Builds the tables of the given point sets and copies them into the
-// workspace (stream ordered; waits for the copy so host memory can go).  Once
+// Builds the tables of the given point sets (`src_in`, `rec_in`: the steps
+// that inject them) and copies them into the workspace (stream ordered; waits for the copy so host memory can go).  Once
 // the points are valid, the call's non-finite watch word is cleared: every
 // sweeping call passes through here first.
 template <typename T>
 static rtm_status upload_points(const rtm_plan *P, char *work, hipStream_t st,
-                                const double *src_pos, PointTables<T> *src_t,
-                                const double *rec_pos, PointTables<T> *rec_t) {
+                                const double *src_pos, PointTables<T> *src_t, FoldInto src_in,
+                                const double *rec_pos, PointTables<T> *rec_t, FoldInto rec_in) {
   Pack pk(work + P->tab_off, P->tab_bytes);
   rtm_status s;
-  if (src_pos && src_t && (s = pack_points<T>(P, P->d.nsrc, src_pos, P->smap, pk, src_t))) return s;
-  if (rec_pos && rec_t && (s = pack_points<T>(P, P->d.nrec, rec_pos, P->rmap, pk, rec_t))) return s;
+  if (src_pos && src_t &&
+      (s = pack_points<T>(P, P->d.nsrc, src_pos, P->smap, src_in, pk, src_t)))
+    return s;
+  if (rec_pos && rec_t &&
+      (s = pack_points<T>(P, P->d.nrec, rec_pos, P->rmap, rec_in, pk, rec_t)))
+    return s;
   if (!pk.fits) return fail(RTM_E_WORKSPACE, "point tables do not fit");
   HIP_TRY(launch_status_clear(status_word(P, work), st));
   if (pk.size) {
@@ -733,7 +787,7 @@ static rtm_status forward_impl(const rtm_plan *P, const void *m, const double *s
                                const void *state_in = nullptr) {
   PointTables<T> src_t, rec_t;
   rtm_status s = upload_points<T>(P, static_cast<char *>(work), st, src_pos, &src_t,
-                                  d_pred ? rec_pos : nullptr, &rec_t);
+                                  fold_into<T>(P), d_pred ? rec_pos : nullptr, &rec_t, FOLD_NONE);
   if (s) return s;
   SweepIO io;
   io.adjoint = false;
@@ -804,7 +858,7 @@ static rtm_status adjoint_impl(const rtm_plan *P, const void *m, const double *r
                                rtm_dtype zt, void *Vbar, void *work, hipStream_t st) {
   PointTables<T> src_t, rec_t;
   rtm_status s = upload_points<T>(P, static_cast<char *>(work), st, qadj ? src_pos : nullptr,
-                                  &src_t, rec_pos, &rec_t);
+                                  &src_t, FOLD_NONE, rec_pos, &rec_t, fold_into<T>(P));
   if (s) return s;
   SweepIO io;
   io.adjoint = true;
@@ -839,8 +893,8 @@ static rtm_status adjoint_image_impl(const rtm_plan *P, const void *m, const dou
                                      const void *Ubar, double scale, void *image, void *work,
                                      hipStream_t st) {
   PointTables<T> src_t, rec_t;
-  rtm_status s = upload_points<T>(P, static_cast<char *>(work), st, nullptr, &src_t, rec_pos,
-                                  &rec_t);
+  rtm_status s = upload_points<T>(P, static_cast<char *>(work), st, nullptr, &src_t, FOLD_NONE,
+                                  rec_pos, &rec_t, fold_into<T>(P));
   if (s) return s;
   HIP_TRY(launch_fill<T>(static_cast<T *>(image), P->N, T(0), st));
   SweepIO io;
@@ -1071,7 +1125,8 @@ static rtm_status gradient_impl(const rtm_plan *P, const void *m, const double *
                                 double scale) {
   PointTables<T> src_t, rec_t;
   char *w = static_cast<char *>(work);
-  rtm_status s0 = upload_points<T>(P, w, st, src_pos, &src_t, rec_pos, &rec_t);
+  const FoldInto in = fold_into<T>(P);
+  rtm_status s0 = upload_points<T>(P, w, st, src_pos, &src_t, in, rec_pos, &rec_t, in);
   if (s0) return s0;
   uint64_t key = 1469598103934665603ull;
   {  // the plan's parameters (a new plan may reuse an old one's address)
@@ -1202,7 +1257,8 @@ template <typename T>
 static rtm_status sketch_impl(const rtm_plan *P, const void *m, const double *src_pos,
                               const void *q, uint64_t seed, double *Y, char *w, hipStream_t st) {
   PointTables<T> src_t, none;
-  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, nullptr, &none);
+  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, fold_into<T>(P), nullptr, &none,
+                                  FOLD_NONE);
   if (s) return s;
   SweepIO f;
   f.adjoint = false;
@@ -1309,7 +1365,8 @@ static rtm_status exact_impl(const rtm_plan *P, const void *mv, const double *sr
   const rtm_desc &d = P->d;
   char *w = static_cast<char *>(work);
   PointTables<T> src_t, rec_t;
-  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, rec_pos, &rec_t);
+  const FoldInto in = fold_into<T>(P, true);
+  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, in, rec_pos, &rec_t, in);
   if (s) return s;
   const int nt = d.nt, ndim = d.ndim;
   const int64_t N = P->N, ld = P->ld;
@@ -1600,7 +1657,7 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
     b->ragged |= p->d.nx % 4 != 0;
     b->tiled = b->tiled && plane_fits(p->d.ny, p->d.nx, sizeof(float));
   }
-  b->stream = 16 * cells > (int64_t)640000000;
+  b->stream = 16 * cells > kStreamBytes;
   // Rows that are no multiple of four cut a cache line at every tile's edge;
   // where they stream from HBM, half as many edges are worth up to a quarter
   // of idle lanes (8 windows of 128^3 .. 256 x 320 x 320, 92.6 M cells: 178 ms
@@ -1690,8 +1747,9 @@ static rtm_status pack_batch_points(const rtm_batch *b, const rtm_shot_io *io, b
     rtm_status st = add_points(P, n, pos, hp);
     if (st) return st;
     InjMap<float> &m = sio[i].map;
-    if (make_map(P, hp, map_cap(n, P->N), map, &m)) m.map = pk.put(map);
-    else if (n > 0) t->mapped = false;
+    const FoldInto into = !b->tiled ? FOLD_NONE : b->stream ? FOLD_STREAM : FOLD_CACHED;
+    if (make_map(P, hp, map_cap(n, P->N), into, map, &m)) m.map = pk.put(map);
+    else if (n > 0) t->mapped = false;  // (a set without a map injects with a launch for all)
     sshot.insert(sshot.end(), n, i);
     for (int32_t p = 0; p < n; ++p) slocal.push_back(p);
     ishot.resize(hp.icell.size(), i);
@@ -2104,7 +2162,8 @@ static rtm_status tti_fwd_impl(const rtm_plan *P, const void *m, const void *ani
                                hipStream_t st) {
   PointTables<T> src_t, rec_t;
   char *w = static_cast<char *>(work);
-  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, d_pred ? rec_pos : nullptr, &rec_t);
+  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, FOLD_NONE, d_pred ? rec_pos : nullptr,
+                                  &rec_t, FOLD_NONE);
   if (s) return s;
   TtiIO io;
   io.m = m;
@@ -2141,7 +2200,8 @@ static rtm_status tti_adj_impl(const rtm_plan *P, const void *m, const void *ani
                                hipStream_t st) {
   PointTables<T> src_t, rec_t;
   char *w = static_cast<char *>(work);
-  rtm_status s = upload_points<T>(P, w, st, qadj ? src_pos : nullptr, &src_t, rec_pos, &rec_t);
+  rtm_status s = upload_points<T>(P, w, st, qadj ? src_pos : nullptr, &src_t, FOLD_NONE, rec_pos,
+                                  &rec_t, FOLD_NONE);
   if (s) return s;
   TtiIO io;
   io.adjoint = true;
@@ -2180,7 +2240,8 @@ static rtm_status tti_grad_impl(const rtm_plan *P, const void *m, const void *an
                                 hipStream_t st) {
   PointTables<T> src_t, rec_t;
   char *w = static_cast<char *>(work);
-  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, rec_pos, &rec_t);
+  rtm_status s = upload_points<T>(P, w, st, src_pos, &src_t, FOLD_NONE, rec_pos, &rec_t,
+                                  FOLD_NONE);
   if (s) return s;
   TtiIO f;
   f.m = m;

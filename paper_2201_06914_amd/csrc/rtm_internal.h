@@ -136,6 +136,14 @@ inline bool plane_fits(int64_t ny, int64_t nx, size_t esz) {
   return ny * nx * (int64_t)esz < (int64_t)kPlaneBytes;
 }
 
+// a step's arrays beyond this many bytes (16 N in FP32: the memory-side cache
+// and a half) stream from HBM
+constexpr int64_t kStreamBytes = 640000000;
+
+// whether the steps of a sweep run the tiled kernel (variant -1: automatic)
+template <typename T>
+bool stencil_tiled(int ndim, int nz, int ny, int nx, int variant);
+
 // the shortest z chunks of the tiled stencil for a step over levels of this
 // many bytes that stay in the caches (stencil.hip)
 int min_planes(int64_t bytes);

@@ -724,7 +724,6 @@ static TileShape tile_shape(int variant) {
 //   189, 204, 128-cell tiles 207; 500 x 800 x 131: 215, 224, 253).  FP64 rows:
 //   64 x 16 tiles, ordinary.
 constexpr int64_t kSimpleCells = 150000;
-constexpr int64_t kStreamBytes = 640000000;
 template <typename T>
 static int auto_variant(const StepArgs<T> &a, int *nzc) {
   constexpr int F = sizeof(T) / 4;
@@ -747,6 +746,20 @@ static int auto_variant(const StepArgs<T> &a, int *nzc) {
   }
   return v;
 }
+
+template <typename T>
+bool stencil_tiled(int ndim, int nz, int ny, int nx, int variant) {
+  if (ndim != 3 || !plane_fits(ny, nx, sizeof(T))) return false;
+  StepArgs<T> a{};
+  a.nz = nz;
+  a.ny = ny;
+  a.nx = nx;
+  a.N = (int64_t)nz * ny * nx;
+  int nzc;
+  return (variant < 0 ? auto_variant(a, &nzc) : variant) != kStencilSimple;
+}
+template bool stencil_tiled<float>(int, int, int, int, int);
+template bool stencil_tiled<double>(int, int, int, int, int);
 
 template <typename T>
 hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, int variant,
