@@ -77,14 +77,15 @@ __global__ __launch_bounds__(256) void k_probe_vec(ProbeArgs<T> p, const ZT *__r
       if (p.mode == PROBE_UTT) {
         T lv[10];
 #pragma unroll
-        for (int q = 0; q < 10; ++q) lv[q] = ring_level(p, p.s0 + min(t0 + q - 1, p.kb))[c];
+        for (int q = 0; q < 10; ++q)
+          lv[q] = t0 + q - 1 <= p.kb ? ring_level(p, p.s0 + t0 + q - 1)[c] : T(0);
 #pragma unroll
         for (int q = 0; q < 8; ++q) s[q] = (lv[q + 2] - T(2) * lv[q + 1] + lv[q]) * p.inv_dt2;
       } else {
         const int shift = p.mode == PROBE_NEW ? 1 : 0;
 #pragma unroll
         for (int q = 0; q < 8; ++q)
-          s[q] = ring_level(p, p.s0 + min(t0 + q, p.kb - 1) + shift)[c];
+          s[q] = t0 + q < p.kb ? ring_level(p, p.s0 + t0 + q + shift)[c] : T(0);
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
@@ -232,12 +233,15 @@ static void launch_f64_ks(const ProbeArgs<double> &p, const void *Z, hipStream_t
 }
 
 // FP64 blocks: the matrix cores, or the vector kernel where the probe operand
-// exceeds 64 KB of LDS
+// exceeds 64 KB of LDS and for short blocks of few probes, which leave the 16 x
+// 16 x 4 products mostly empty (us a block on 100^3, this / vector: k = 4, r = 1
+// 42 / 24, r = 8 44 / 33, r = 16 47 / 49; k = 8, r = 4 43 / 37; k = 10, r = 1 42 / 44)
 hipError_t launch_probe_f64(const ProbeArgs<double> &p, const void *Z, bool z_is_i8,
                             hipStream_t st) {
   int KS = (p.kb + 15) / 16;
   KS = KS <= 1 ? 1 : KS <= 2 ? 2 : KS <= 4 ? 4 : 8;
-  if (p.kb > 128 || (p.r + 15) / 16 * KS > 32) return launch_probe_vec<double>(p, Z, z_is_i8, st);
+  if (p.kb > 128 || (p.r + 15) / 16 * KS > 32 || (p.kb <= 8 && p.kb * p.r < 64))
+    return launch_probe_vec<double>(p, Z, z_is_i8, st);
   auto go = [&](auto ks) {
     constexpr int K = decltype(ks)::value;
     if (z_is_i8) launch_f64_ks<K, int8_t>(p, Z, st);
@@ -381,8 +385,8 @@ __device__ __forceinline__ void probe_operand(const ProbeArgs<float> &p, int ks,
 #pragma unroll
     for (int q = 0; q < 10; ++q) {
       // level s0 + t, inside [-1, kb]
-      const int t = FULL ? tb + q - 1 : min(tb + q - 1, p.kb);
-      lv[q] = FAST || valid ? ring_level(p, p.s0 + t)[c] : 0.f;
+      const int t = FULL || !FAST ? tb + q - 1 : min(tb + q - 1, p.kb);
+      lv[q] = FAST || (valid && t <= p.kb) ? ring_level(p, p.s0 + t)[c] : 0.f;
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -394,8 +398,8 @@ __device__ __forceinline__ void probe_operand(const ProbeArgs<float> &p, int ks,
     const int shift = p.mode == PROBE_NEW ? 1 : 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int t = FULL ? tb + q : min(tb + q, p.kb - 1);
-      const float v = FAST || valid ? ring_level(p, p.s0 + t + shift)[c] : 0.f;
+      const int t = FULL || !FAST ? tb + q : min(tb + q, p.kb - 1);
+      const float v = FAST || (valid && t < p.kb) ? ring_level(p, p.s0 + t + shift)[c] : 0.f;
       sv[q] = dv[q] = FULL || tb + q < p.kb ? v : 0.f;
     }
   }
@@ -460,7 +464,8 @@ __device__ __forceinline__ f32x16 chunk_mfma(const typename Operand<OP>::type &a
 // adjoint's forward field) are read and written with the non-temporal hint
 // (each is touched once per block).  FIRST: the field starts from zero and is
 // not read (a template, not a branch: merging loaded and zero accumulators took
-// the k = 32 kernel from 90 to 138 VGPRs).
+// the k = 32 kernel from 90 to 138 VGPRs, and 16 more in the edge kernel made
+// k = 16, r = 4 on 100^3 34 us instead of 30).
 constexpr int kQueueChunk = 4;  // tiles per work-queue grab
 
 __global__ void k_queue_reset(int *q) {
@@ -608,7 +613,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
 
 // Edge kernel: tiles [tile_begin, ntiles) with any masking (ragged last tile,
 // r not a multiple of 8) and ordinary accesses.  One row tile at a time.
-template <int KS, int OP, int MODE, bool FUSED, bool QF>
+template <int KS, int OP, int MODE, bool FUSED, bool QF, bool FIRST = false>
 __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
                                                          const void *__restrict__ Z, int MT,
                                                          const float *__restrict__ Uf,
@@ -645,7 +650,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int rr = 8 * (v >> 2) + (v & 3);
-        const bool ok = valid && mt * 32 + rr + 4 * half < p.r && (FUSED || !p.first);
+        const bool ok = !FIRST && valid && mt * 32 + rr + 4 * half < p.r;
         const float val = ok ? Ut[rr * 32] : 0.f;
         acc[v] = (FUSED || F16) ? 0.f : val;
         uf[v] = val;
@@ -675,8 +680,8 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
         const int rr = 8 * (v >> 2) + (v & 3);
         if (FUSED)
           part += uf[v] * acc[v];
-        else if ((valid || p.first) && mt * 32 + rr + 4 * half < p.r)
-          Uo[rr * 32] = acc[v];  // padding cells: zeros, written once
+        else if ((FIRST || valid) && mt * 32 + rr + 4 * half < p.r)
+          Uo[rr * 32] = acc[v];  // (FIRST: padding cells too, zeros)
       }
     }
     if (FUSED) {
@@ -735,6 +740,26 @@ struct FuseArgs {
   float scale = 0.f;
 };
 
+// Whether blocks that the wide fast kernels do not divide (r = 8, 24, 96;
+// short blocks) take the fast kernel with one row tile at a time or the edge
+// kernel.  For KS <= 2 the fast kernel holds a tile's operands; the edge kernel
+// is ahead only for fused blocks of one or two row tiles on small grids.  For
+// longer blocks the fast kernel reads the levels again for every row tile and
+// the edge kernel keeps all chunks' operands; for F16S updates and fused BF16
+// the edge kernel is slow all the same.  us a block on 100^3, fast / edge:
+// update, k = 24, r = 32 55 / 57, r = 96 118 / 141; k = 50, r = 32 80 / 91, r = 96 177 / 178 (three
+// times the levels; 200 x 250 x 250 2.42 / 2.11 ms); k = 100, r = 32 118 / 203, r = 128 472 /
+// 418; F16S k = 50, r = 96 204 / 284; fused, k = 20, r = 32 38 / 36 (200 x 250 x
+// 250 463 / 495), r = 96 79 / 97; k = 50, r = 32 70 / 63, r = 128 188 / 141 (BF16 172
+// / 251); k = 100, r = 32 104 / 165, r = 128 342 / 303.  FP32 operands: k = 50 r = 8 97 / 83,
+// k = 100, r = 8 139 / 218, r = 96 500 / 469.
+template <int KS, int OP, bool FUSED>
+static bool one_row_tile(int MT, int64_t N) {
+  if (KS <= 2) return !FUSED || OP == OP_BF16 || MT >= 3 || N >= 4000000;
+  if (FUSED) return OP == OP_BF16 || (KS == 8 && MT == 1);
+  return OP == OP_F16S || (MT == 1 && (OP != OP_F32 || KS == 8));
+}
+
 template <int KS, int OP, int MODE, bool FUSED, bool QF>
 static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int MT,
                                  const FuseArgs &f, hipStream_t st) {
@@ -743,12 +768,21 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
   const int64_t ntiles = (p.N + 31) / 32;
   const int64_t nfull = p.N / 32;
   const int set = g_probe_grid[FUSED ? 1 : 0];
+  // which kernel takes the full tiles: several row tiles at a time where they
+  // divide whole blocks (four; the fused kernel, which also holds the forward
+  // field, two), or one, or none (the edge kernel takes all)
+  const bool fast = g_probe_nt && p.r % 8 == 0 && nfull > 0;
+  const bool whole = p.r % 32 == 0 && p.kb == 16 * KS && MT % 2 == 0;
+  const int rows = !fast ? 0 : whole ? (MT % 4 == 0 && !FUSED ? 4 : 2)
+                   : one_row_tile<KS, OP, FUSED>(MT, p.N) ? 1 : 0;
   // automatic: update kernels of +-1 probes and blocks of at most 32 steps
   // take one workgroup per four tiles (no stride), those of longer blocks a
-  // work queue (when the sweep provides a counter); the fused kernel, real
-  // probes (whose staging costs twice as much) and longer blocks without a
-  // counter a fixed number of tiles per wave, with at least 2048 workgroups
-  const bool queue = p.queue && (set == -2 || (set == -1 && !FUSED && !QF && KS > 2));
+  // work queue (when the sweep provides a counter and several row tiles share
+  // a tile's operands); the fused kernel, real probes (whose staging costs
+  // twice as much) and other long blocks a fixed number of tiles per wave,
+  // with at least 2048 workgroups
+  const bool queue =
+      p.queue && (set == -2 || (set == -1 && rows != 1 && !FUSED && !QF && KS > 2));
   auto grid_for = [set, queue](int64_t tiles) -> unsigned {
     const int64_t want = (tiles + 3) / 4;  // one workgroup per four tiles
     int64_t cap = set > 0 ? set : want;
@@ -764,39 +798,36 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
   };
   // work queue (fast kernel only): reset the counter, then launch
   ProbeArgs<float> pq = p;
-  if (queue) {
+  if (queue && rows) {
     hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, st, p.queue);
   } else {
     pq.queue = nullptr;
   }
-  // four row tiles at a time where they divide (the fused kernel, which also
-  // holds the forward field: two), else one (r = 32, 48, 96; short blocks).
-  // All are bound by HBM: r = 128, k = 32 on 320 x 448 x 448 12.8 ms (5.8
-  // TB/s), r = 32 on 100^3 59 us (6.6 TB/s; the edge kernel 61 us)
-  int64_t done = 0;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(grid_for(nfull)), dim3(256), shm, st, pq, Z, MT, f.Uf, f.img,
                        f.scale, nfull);
-    done = nfull;
   };
-  if (g_probe_nt && p.r % 8 == 0 && nfull > 0) {
-    const bool whole = p.r % 32 == 0 && p.kb == 16 * KS;
-    if (whole && MT % 4 == 0 && !FUSED) {
-      if constexpr (!FUSED) {
-        if (p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF, true>);
-        else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF>);
-      }
-    } else if (whole && MT % 2 == 0) {
-      if (!FUSED && p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF, !FUSED>);
-      else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF>);
-    } else {
-      if (!FUSED && p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 1, QF, !FUSED>);
-      else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 1, QF>);
+  if (rows == 4) {
+    if constexpr (!FUSED) {
+      if (p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF, true>);
+      else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF>);
     }
+  } else if (rows == 2) {
+    if (!FUSED && p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF, !FUSED>);
+    else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF>);
+  } else if (rows == 1) {
+    if (!FUSED && p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 1, QF, !FUSED>);
+    else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 1, QF>);
   }
-  if (done < ntiles)
-    hipLaunchKernelGGL((k_probe_mfma_edge<KS, OP, MODE, FUSED, QF>), dim3(grid_for(ntiles - done)),
-                       dim3(256), shm, st, p, Z, MT, f.Uf, f.img, f.scale, done);
+  const int64_t done = rows ? nfull : 0;
+  auto edge = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid_for(ntiles - done)), dim3(256), shm, st, p, Z, MT, f.Uf,
+                       f.img, f.scale, done);
+  };
+  if (done < ntiles) {
+    if (!FUSED && p.first) edge(k_probe_mfma_edge<KS, OP, MODE, FUSED, QF, !FUSED>);
+    else edge(k_probe_mfma_edge<KS, OP, MODE, FUSED, QF>);
+  }
 }
 
 template <int KS, int OP, bool QF>
@@ -836,15 +867,19 @@ static void launch_mfma_ks(const ProbeArgs<float> &p, const void *Z, bool zf32, 
 // real probes (zf32) need OP_BF16X2 or OP_F32.  FP32 products on the matrix
 // cores: r = 48, k = 32 on 150 x 200 x 226 0.65 ms (5.4 TB/s), where the vector
 // kernel, which reads the levels once per 32 rows, took 1.34.  OP_F32 blocks whose operand
-// takes more than 64 KB of LDS run the vector kernel: two workgroups per CU
-// (160 KB) keep its loads in flight.
+// takes more than 64 KB of LDS run the vector kernel (two workgroups per CU, 160
+// KB, keep the matrix kernels' loads in flight), and so do short blocks of few
+// probes, which leave the 32 x 32 products mostly empty (us a block on 100^3,
+// matrix cores / vector: k = 1, r = 1 31 / 15, r = 32 40 / 40; k = 4, r = 8 33 / 21; k = 8, r = 24 45 /
+// 40; k = 12, r = 16 40 / 39; k = 16, r = 8 36 / 38).
 hipError_t launch_probe_mfma(const ProbeArgs<float> &p, const void *Z, bool zf32, int op,
                              const float *Uf, float *img, float scale, hipStream_t st) {
   const FuseArgs f{Uf, img, scale};
   const int MT = (p.r + 31) / 32;
   int KS = (p.kb + 15) / 16;
   KS = KS <= 1 ? 1 : KS <= 2 ? 2 : KS <= 4 ? 4 : 8;
-  if (op == OP_F32 && (p.kb > 128 || MT * KS > 32)) return launch_probe_vec<float>(p, Z, !zf32, st);
+  if (op == OP_F32 && (p.kb > 128 || MT * KS > 32 || (p.kb < 16 && p.kb * p.r <= 192)))
+    return launch_probe_vec<float>(p, Z, !zf32, st);
   if (p.kb > 128 || (zf32 && op != OP_BF16X2 && op != OP_F32)) return hipErrorInvalidValue;
   switch (KS) {
     case 1: launch_mfma_ks<1>(p, Z, zf32, op, MT, f, st); break;
