@@ -148,8 +148,10 @@ void rtm_set_stencil_blocks(int32_t blocks);
 void rtm_set_stencil_alternate(int32_t on);
 /* Tuning hook, process wide: with on != 0 (default) the fast probe-GEMM
  * kernels read and write the compressed fields with the non-temporal hint
- * (each byte is touched once per block); 0 uses ordinary loads and stores.
- * Same results. */
+ * (each byte is touched once per block); 0 runs those of whole blocks (r a
+ * multiple of 64, a block of 16, 32, 64 or 128 steps) with ordinary loads and
+ * stores, and other blocks by the masked kernel, which has no hint.  FP32
+ * probe products keep it.  Same results. */
 void rtm_set_probe_nt(int32_t on);
 /* Tuning hook, process wide: the workgroups (4 waves, one 32-cell tile per
  * wave at a time) of one probe-GEMM launch, for the kernels that update a

@@ -230,7 +230,8 @@ N_STENCIL_VARIANTS = 14
 
 
 def set_probe_nt(on: bool) -> None:
-    """Non-temporal compressed-field traffic in the probe kernels (default on)."""
+    """Non-temporal compressed-field traffic in the probe kernels (default on;
+    off: the same wide kernels without the hint, the masked kernel elsewhere)."""
     _lib.load().rtm_set_probe_nt(1 if on else 0)
 
 

@@ -472,7 +472,20 @@ __global__ void k_queue_reset(int *q) {
   if (threadIdx.x == 0) *q = 0;
 }
 
-template <int KS, int OP, int MODE, bool FUSED, int MTC, bool QF, bool FIRST = false>
+// accesses to the compressed fields, with the non-temporal hint or without
+template <bool NT>
+__device__ __forceinline__ float ldb(const float *p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT>
+__device__ __forceinline__ void stb(float v, float *p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+template <int KS, int OP, int MODE, bool FUSED, int MTC, bool QF, bool FIRST = false,
+          bool NT = true>
 __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
                                                          const void *__restrict__ Z, int MT,
                                                          const float *__restrict__ Uf,
@@ -533,7 +546,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
             acc[j][v] = 0.f;
             uf[(FUSED || F16) ? j : 0][v] =
                 rows(mt0 + j, v) && !FIRST
-                    ? __builtin_nontemporal_load(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32)
+                    ? ldb<NT>(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32)
                     : 0.f;
           }
       } else {
@@ -543,7 +556,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
 #pragma unroll
           for (int v = 0; v < 16; ++v)
             acc[j][v] = rows(mt0 + j, v) && !FIRST
-                            ? __builtin_nontemporal_load(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32)
+                            ? ldb<NT>(Ut + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32)
                             : 0.f;
       }
       int ecur = 0;  // F16S: acc holds the block's partial product in units of 2^ecur
@@ -601,7 +614,7 @@ __global__ __launch_bounds__(256) void k_probe_mfma_fast(ProbeArgs<float> p,
 #pragma unroll
           for (int v = 0; v < 16; ++v)
             if (rows(mt0 + j, v))
-              __builtin_nontemporal_store(acc[j][v], Uo + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32);
+              stb<NT>(acc[j][v], Uo + (j * 32 + 8 * (v >> 2) + (v & 3)) * 32);
       }
     }
     if (FUSED) {
@@ -771,10 +784,13 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
   // which kernel takes the full tiles: several row tiles at a time where they
   // divide whole blocks (four; the fused kernel, which also holds the forward
   // field, two), or one, or none (the edge kernel takes all)
-  const bool fast = g_probe_nt && p.r % 8 == 0 && nfull > 0;
   const bool whole = p.r % 32 == 0 && p.kb == 16 * KS && MT % 2 == 0;
-  const int rows = !fast ? 0 : whole ? (MT % 4 == 0 && !FUSED ? 4 : 2)
-                   : one_row_tile<KS, OP, FUSED>(MT, p.N) ? 1 : 0;
+  // without the hint the wide kernels run without it and the rest of the
+  // blocks the edge kernel, which has none (FP32 operands keep it)
+  const bool nt = g_probe_nt || OP == OP_F32;
+  const int rows = p.r % 8 || nfull == 0 ? 0
+                   : whole               ? (MT % 4 == 0 && !FUSED ? 4 : 2)
+                   : nt && one_row_tile<KS, OP, FUSED>(MT, p.N) ? 1 : 0;
   // automatic: update kernels of +-1 probes and blocks of at most 32 steps
   // take one workgroup per four tiles (no stride), those of longer blocks a
   // work queue (when the sweep provides a counter and several row tiles share
@@ -807,7 +823,13 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
     hipLaunchKernelGGL(kern, dim3(grid_for(nfull)), dim3(256), shm, st, pq, Z, MT, f.Uf, f.img,
                        f.scale, nfull);
   };
-  if (rows == 4) {
+  if (rows > 1 && !nt) {
+    if constexpr (OP != OP_F32) {
+      if (!FUSED && p.first) (void)launch_fill<float>(p.bar, ntiles * 32 * p.r, 0.f, st);
+      if (rows == 2) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 2, QF, false, false>);
+      else if constexpr (!FUSED) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF, false, false>);
+    }
+  } else if (rows == 4) {
     if constexpr (!FUSED) {
       if (p.first) go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF, true>);
       else go(k_probe_mfma_fast<KS, OP, MODE, FUSED, 4, QF>);

@@ -108,3 +108,33 @@ def test_fused_block_route(probe, r, k, kernel):
     got = -r * run().double().reshape(-1)          # the call's scale is -1 / r
     assert float(want.abs().max()) > 0
     assert bool(((got - want).abs() <= 2.0**-23 * (nt + r + 4) * size).all())
+
+
+@pytest.mark.parametrize("probe,r,k,fused", [("bf16x2", 128, 16, False), ("bf16x2", 64, 32, False),
+                                             ("bf16", 128, 64, True), ("f16s", 64, 16, True)])
+def test_hint_off_keeps_the_kernel(probe, r, k, fused):
+    """rtm_set_probe_nt(0): the wide fast kernels with ordinary loads and
+    stores, not another kernel; the same bits."""
+    say(f"case: no hint, {probe} r {r} k {k}")
+    nt, rng = 2 * k, np.random.default_rng(4)
+    x = _inputs(torch.float32, nt, r, rng)
+    plan = _plan(probe, r, k, nt)
+    rec = np.array([[5., 9., 14.]])
+    d = torch.from_numpy(rng.standard_normal((nt, 1)).astype(np.float32)).cuda()
+    bars = (plan.empty_bar(), None if fused else plan.empty_bar())
+    run = lambda: P.fwi_gradient(plan, x["m"], x["src"], x["q"], rec, d, x["Z"], bars=bars,
+                                 fused=fused)
+    out = []
+    try:
+        for on in (True, False):
+            P.set_probe_nt(on)
+            names = kernels(run)
+            o = run()
+            out.append((o["Ubar"].clone(), o["grad"]))
+            assert named(names, "k_probe_mfma_fast") == 4, names
+            hint = {k_.rstrip(">").split(", ")[-1] for k_ in names if "mfma_fast" in k_}
+            assert hint == {"true" if on else "false"}, names
+    finally:
+        P.set_probe_nt(True)
+    assert float(out[0][1].abs().max()) > 0
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
