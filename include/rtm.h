@@ -187,13 +187,14 @@ rtm_status rtm_autotune_stencil(const rtm_plan *plan, const void *m, void *work,
                                 size_t work_bytes, int32_t steps, int32_t *best, float *us,
                                 int64_t *mismatch, rtm_stream stream);
 /* Kernel timing, process wide and off by default.  With stride > 0 the
- * sweeps record HIP events on their own stream around every stride-th
- * stencil launch (every stride-th TTI step, all of its kernels) and around
- * every probe-GEMM and image launch (0 turns it off).
+ * sweeps record HIP events on their own stream around the stencil launch of
+ * every stride-th step (every stride-th TTI step, all of its kernels) and
+ * around every probe-GEMM and image launch (0 turns it off).
  * rtm_profile_read(kind, ...) waits for the recorded events of one kind
  * (0 stencil, 1 forward probe GEMM, 2 image, 3 adjoint probe GEMM, 4 TTI
  * forward step, 5 TTI transpose step), returns their summed duration in ms
- * and their count, and forgets them. */
+ * and how many steps or launches that covers (a 2D stencil launch may cover
+ * several steps), and forgets them. */
 void rtm_profile_enable(int32_t stride);
 rtm_status rtm_profile_read(int32_t kind, double *total_ms, int64_t *count);
 /* Reference for the roofline figures: a streaming device-to-device copy of

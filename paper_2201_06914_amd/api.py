@@ -330,13 +330,14 @@ KERNEL_KINDS = {"stencil": 0, "probe": 1, "image": 2, "probe_adj": 3, "tti_step"
 
 
 def profile_enable(stride: int) -> None:
-    """Time every stride-th stencil launch and every probe / image launch with
-    HIP events on the sweep's stream (0 = off)."""
+    """Time the stencil launch of every stride-th step and every probe / image
+    launch with HIP events on the sweep's stream (0 = off)."""
     _lib.load().rtm_profile_enable(int(stride))
 
 
 def profile_read(kind: str):
-    """(total_ms, count) of the timed launches of one kernel kind."""
+    """(total_ms, count) of the timed launches of one kernel kind; count: the
+    steps they cover (2D launches may cover several), else the launches."""
     ms = ctypes.c_double()
     n = ctypes.c_int64()
     _check(_lib.load().rtm_profile_read(KERNEL_KINDS[kind], ctypes.byref(ms), ctypes.byref(n)),

@@ -45,23 +45,29 @@ static int g_tti_shape = 21;        // tiled TTI tile shape (1..21)
 static int g_stencil_alternate = 1; // sweeps: tiled stencil marches z up / down on alternate steps
 static int g_graph = 0;             // fwi_gradient: capture and replay HIP graphs
 
-// Opt-in kernel timing: HIP events recorded on the sweep's stream around every
-// `stride`-th launch of the stencil and every probe-GEMM / image launch.
+// Opt-in kernel timing: HIP events recorded on the sweep's stream around the
+// stencil launch of every `stride`-th step (a launch of several steps counts as
+// that many) and around every probe-GEMM / image launch.
 enum {
   KT_STENCIL = 0, KT_PROBE = 1, KT_IMAGE = 2, KT_PROBE_ADJ = 3, KT_TTI = 4, KT_TTI_ADJ = 5,
   KT_N = 6
 };
 struct TimedLaunch {
   int kind;
+  int steps;  // that the launch advances (1 where it advances none)
   hipEvent_t a, b;
 };
 static int g_prof_stride = 0;  // 0 = off
 static std::vector<TimedLaunch> g_prof;
 
-static void prof_begin(int kind, int step, hipStream_t st, TimedLaunch *t) {
+static void prof_begin(int kind, int step, hipStream_t st, TimedLaunch *t, int steps = 1) {
   t->kind = -1;
+  t->steps = steps;
   if (g_prof_stride <= 0) return;
-  if ((kind == KT_STENCIL || kind == KT_TTI || kind == KT_TTI_ADJ) && step % g_prof_stride) return;
+  // none of the launch's steps is a multiple of the stride
+  if ((kind == KT_STENCIL || kind == KT_TTI || kind == KT_TTI_ADJ) &&
+      (step + steps - 1) / g_prof_stride * g_prof_stride < step)
+    return;
   if (hipEventCreate(&t->a) != hipSuccess) return;
   if (hipEventCreate(&t->b) != hipSuccess) {
     (void)hipEventDestroy(t->a);
@@ -243,7 +249,7 @@ extern "C" rtm_status rtm_profile_read(int32_t kind, double *total_ms, int64_t *
     HIP_TRY(hipEventSynchronize(t.b));
     HIP_TRY(hipEventElapsedTime(&ms, t.a, t.b));
     tot += ms;
-    ++n;
+    n += t.steps;
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
   }
@@ -677,10 +683,11 @@ static rtm_status run_sweep(const rtm_plan *P, const SweepIO &io, const PointTab
     a.cur = level(s);
     a.prev = level(s - 1);
     a.next = level(s + 1);
+    const int left = std::min({kMaxSteps2D, s0 + d.k_block - s, ne - s});
+    const int steps = multi && stencil2d_multi<T>(P->N, left) ? left : 1;
     TimedLaunch tl;
-    prof_begin(KT_STENCIL, s, st, &tl);
-    const int steps = std::min({kMaxSteps2D, s0 + d.k_block - s, ne - s});
-    if (multi && stencil2d_multi<T>(P->N, steps)) {
+    prof_begin(KT_STENCIL, s, st, &tl, steps);
+    if (multi && stencil2d_multi<T>(P->N, left)) {
       HIP_TRY(launch_stencil2d<T>(a, step_inj(inj, inj_vals, n),
                                   (io.adjoint ? -1 : 1) * (int64_t)inj.npts, ring, P->ld, P->R, s,
                                   steps, st));
