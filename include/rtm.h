@@ -126,13 +126,15 @@ rtm_status rtm_plan_workspace_bytes(const rtm_plan *plan, size_t *bytes);
 double rtm_cfl_bound(int32_t ndim);
 const char *rtm_status_str(rtm_status s);
 /* Tuning hooks, process wide: stencil kernel of the sweeps.  -1 automatic
- * (3D grids: LDS-tiled, the shape chosen from the grid's size; small and 2D
- * grids: one thread per cell), 0 one thread per cell, 1..13 LDS-tiled
+ * (3D grids: LDS-tiled, the shape chosen from the grid's size, or one thread
+ * per cell where they are small or thin; 2D grids: up to four steps per launch,
+ * or one thread per cell), 0 one thread per cell, 1..13 LDS-tiled
  * z-marching variants (3D; x-width x y-rows, rows halved for F64): 1: 64x16,
  * 2: 64x32, 3: 64x32 with two rows per thread, 4: 64x8, 5: 32x32, 6: 128x8,
- * 7..12: as 1..6 with non-temporal streaming loads and stores, 13: 32x16.
- * Every choice gives bitwise-identical levels.  Batched shots run 64x16 tiles
- * (128x8 where cut rows stream from HBM), non-temporal for 7..12.
+ * 7..10 and 12: as 1..4 and 6 with non-temporal streaming loads and stores,
+ * 11 and 13: as 12.  Every choice gives bitwise-identical levels.  Batched
+ * shots run 64x16 tiles (128x8 where cut rows stream from HBM), non-temporal
+ * for 7..13.
  * rtm_set_stencil_blocks: the tiled acoustic kernels split z into the fewest
  * chunks (of at least 4 planes) that give a launch this many workgroups of
  * 256 threads' worth (default 2048, which leaves the split of the automatic

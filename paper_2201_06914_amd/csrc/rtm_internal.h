@@ -294,6 +294,9 @@ constexpr int kReduceBlocks = 1024;  // partial sums of the two-pass reductions
 constexpr int kStencilSimple = 0;
 constexpr int kStencilTiled = 1;     // first LDS-tiled variant
 constexpr int kStencilVariants = 13;  // last variant id
+inline int tiled_kernel(int variant) {  // the kernel an id stands for (11, 13: as 12)
+  return variant == 11 || variant == 13 ? 12 : variant;
+}
 constexpr int kAutoBlocks = 2048;     // the default z-split target
 
 // XCD-aware block order: hardware workgroup ids go round-robin over the 8

@@ -680,8 +680,13 @@ int min_planes(int64_t bytes) {
 // tiled variants: id -> tile (x cells x y rows), threads
 //   1: 64 x 16, 256     2: 64 x 32, 512     3: 64 x 32, 256 (two rows each)
 //   4: 64 x 8, 128      5: 32 x 32, 256     6: 128 x 8, 256
-//   7 .. 12: as 1 .. 6, non-temporal         13: 32 x 16, 128
-// (FP64: half as many rows)
+//   7 .. 10, 12: as 1 .. 4, 6, non-temporal    11, 13: as 12
+// (FP64: half as many rows).  11 and 13 once stood for 64 x 16 and 64 x 32
+// non-temporal tiles of other kernels, 13 the fastest at 384 x 512 x 512 (289);
+// 12 is at least as fast as either was on every grid measured (268-293 there;
+// 300^3 94-111 against 114-148, 320 x 448 x 447 222-250 against 236-308), tiles
+// of 32 x 32 and 32 x 16 were not (310-334 and 359-372, 137-151 and 111-115,
+// 377-389 and 307-315).
 struct TileShape {
   int tx, ty, threads;
 };
@@ -689,7 +694,7 @@ template <typename T>
 static TileShape tile_shape(int variant) {
   static const TileShape k[6] = {{64, 16, 256}, {64, 32, 512}, {64, 32, 256},
                                  {64, 8, 128},  {32, 32, 256}, {128, 8, 256}};
-  TileShape t = variant == 13 ? TileShape{32, 16, 128} : k[(variant - 1) % 6];
+  TileShape t = k[(tiled_kernel(variant) - 1) % 6];
   t.ty /= (int)sizeof(T) / 4;
   return t;
 }
@@ -778,7 +783,7 @@ hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, 
     nzc = z_split(a.nz, (int64_t)((a.nx + t.tx - 1) / t.tx) * ((a.ny + t.ty - 1) / t.ty),
                   t.threads, target_blocks, 4);
   }
-  switch (variant) {
+  switch (tiled_kernel(variant)) {
     case kStencilSimple: {
       const unsigned nblk = (unsigned)((a.N + 255) / 256);
       if (ndim == 3)
@@ -796,9 +801,7 @@ hipError_t launch_stencil(int ndim, const StepArgs<T> &a, const InjMap<T> &inj, 
     case 8: launch_tiled<T, 64, 32 / F, 1, true>(a, inj, nzc, st, e, rev); break;
     case 9: launch_tiled<T, 64, 16 / F, 2, true>(a, inj, nzc, st, e, rev); break;
     case 10: launch_tiled<T, 64, 8 / F, 1, true>(a, inj, nzc, st, e, rev); break;
-    case 11: launch_tiled<T, 32, 32 / F, 1, true>(a, inj, nzc, st, e, rev); break;
     case 12: launch_tiled<T, 128, 8 / F, 1, true>(a, inj, nzc, st, e, rev); break;
-    case 13: launch_tiled<T, 32, 16 / F, 1, false>(a, inj, nzc, st, e, rev); break;
     default: launch_tiled<T, 64, 16 / F, 1, false>(a, inj, nzc, st, e, rev); break;
   }
   return hipGetLastError();
@@ -822,7 +825,7 @@ hipError_t launch_stencil_epi(int ndim, const StepArgs<T> &a, const InjMap<T> &i
     return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 4) {
     const bool stream = 4 * a.N * (int64_t)sizeof(T) > kStreamBytes;
-    const bool nt = variant < 0 ? stream && a.nx % V16<T>::n == 0 : variant >= 7 && variant <= 12;
+    const bool nt = variant < 0 ? stream && a.nx % V16<T>::n == 0 : variant >= 7;
     const int64_t tiles = (int64_t)((a.nx + 63) / 64) * ((a.ny + 15) / 16);
     const int nzc = z_split(a.nz, tiles, 256, target_blocks,
                             stream ? 16 : min_planes(a.N * (int)sizeof(T)));
@@ -991,7 +994,7 @@ hipError_t launch_stencil_batched(const ShotStep<T> *shots, const ShotIO<T> *io,
                                   const int4 *tiles, int ntiles, int s, int n, int variant,
                                   bool ragged, bool wide, hipStream_t st, int rev) {
   if (ntiles <= 0) return hipSuccess;
-  const bool nt = variant >= 7 && variant <= 12;
+  const bool nt = variant >= 7;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(ntiles), dim3(256), 0, st, shots, io, (int)mapped, tiles,
                        ntiles, s, n, rev);

@@ -68,3 +68,21 @@ def test_2d_steps_per_launch(field, shape, k, multi, simple):
         P.set_stencil_variant(-1)
     assert named(names, "k_stencil2d_steps") == multi, names
     assert named(names, "k_stencil_simple") == simple, names
+
+
+@pytest.mark.parametrize("variant,kernel", [(9, "float, 64, 16, 2, true"), (10, "float, 64, 8, 1, true"),
+                                            (11, "float, 128, 8, 1, true"),
+                                            (12, "float, 128, 8, 1, true"),
+                                            (13, "float, 128, 8, 1, true")])
+def test_ids_of_the_streaming_tiles(variant, kernel):
+    """Ids 11 and 13 run the 128 x 8 non-temporal tiles."""
+    say(f"case: variant {variant}")
+    run = _levels((40, 37, 70), "f32")
+    want = run()
+    P.set_stencil_variant(variant)
+    try:
+        names = kernels(run)
+        assert named(names, f"k_stencil3d_tiled<{kernel},") == 5, names
+        assert torch.equal(run(), want)
+    finally:
+        P.set_stencil_variant(-1)
