@@ -183,8 +183,9 @@ void rtm_set_graph(int32_t on);
  * direction (mismatch[v]), times
  * `steps` launches of each (us[v], microseconds per launch; us and mismatch
  * may be NULL or hold 14 entries) and returns in *best the fastest variant
- * with no mismatch.  It does not change the current variant.  Needs
- * k_block >= 2; synchronises `stream`. */
+ * with no mismatch, or -1 where the automatic choice is at least as fast (it
+ * is timed too; in 2D only it takes several steps per launch).  It does not
+ * change the current variant.  Needs k_block >= 2; synchronises `stream`. */
 rtm_status rtm_autotune_stencil(const rtm_plan *plan, const void *m, void *work,
                                 size_t work_bytes, int32_t steps, int32_t *best, float *us,
                                 int64_t *mismatch, rtm_stream stream);

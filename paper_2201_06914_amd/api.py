@@ -222,11 +222,18 @@ def cfl_bound(ndim: int) -> float:
     return float(_lib.load().rtm_cfl_bound(ndim))
 
 
+N_STENCIL_VARIANTS = 14
+
+_STENCIL_VARIANT = [-1]     # the value last set in this process (-1: automatic)
+
+
 def set_stencil_variant(v: int) -> None:
     _lib.load().rtm_set_stencil_variant(int(v))
+    _STENCIL_VARIANT[0] = int(v) if -1 <= int(v) < N_STENCIL_VARIANTS else -1
 
 
-N_STENCIL_VARIANTS = 14
+def get_stencil_variant() -> int:
+    return _STENCIL_VARIANT[0]
 
 
 def set_probe_nt(on: bool) -> None:
@@ -264,14 +271,42 @@ def get_stencil_blocks() -> int:
     return _STENCIL_BLOCKS[0]
 
 
+def _automatic_us(plan: Plan, m, work, steps: int) -> float:
+    """us per step of sweeps with the automatic stencil (from two lengths, so
+    that what a call does once drops out)."""
+    n = max(1, -(-steps // plan.spec.k_block)) * plan.spec.k_block
+    variant, blocks = get_stencil_variant(), get_stencil_blocks()
+    set_stencil_variant(-1)
+    set_stencil_blocks(2048)
+    try:
+        ms = []
+        for nt in (n, 3 * n):
+            p = Plan(dataclasses.replace(plan.spec, nt=nt, nsrc=0, nrec=0))
+            best = float("inf")
+            for _ in range(3):
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record()
+                rtm_forward_probe(p, m, None, None, want_d=False, work=work)
+                e1.record()
+                e1.synchronize()
+                best = min(best, e0.elapsed_time(e1))
+            ms.append(best)
+    finally:
+        set_stencil_variant(variant)
+        set_stencil_blocks(blocks)
+    return 1e3 * (ms[1] - ms[0]) / (2 * n)
+
+
 def autotune_stencil(plan: Plan, m, work=None, steps: int = 20, apply: bool = True,
                      cache: str | None = None, blocks=(768, 1024, 1536, 2048, 4096)) -> dict:
     """Times every stencil variant on this plan's grid (after checking each
     against the one-thread-per-cell kernel bit for bit, in both z-marching
-    directions) for each z-split target in `blocks`, and with apply=True
-    selects the fastest (variant, target) pair.  `cache`: a JSON file keyed by
-    (arch, grid, dtype) that stores the choice across runs (default: the
-    RTM_TUNE_CACHE environment variable, if set)."""
+    directions) for each z-split target in `blocks`, and the automatic choice
+    (-1, target 2048) over steps of a sweep, and with apply=True selects the
+    fastest (variant, target) pair.  us[target]: one time per variant; the
+    automatic choice's is the last entry of us[2048].  `cache`: a JSON file
+    keyed by (arch, grid, dtype) that stores the choice across runs (default:
+    the RTM_TUNE_CACHE environment variable, if set)."""
     import json
     import os
     if cache is None:
@@ -280,8 +315,9 @@ def autotune_stencil(plan: Plan, m, work=None, steps: int = 20, apply: bool = Tr
     if cache:
         props = torch.cuda.get_device_properties(m.device)
         arch = getattr(props, "gcnArchName", props.name)
-        # "tiles2": what the variant ids stand for; entries of other sets don't count
-        key = (f"tiles2|{arch}|{plan.spec.ndim}|{'x'.join(map(str, plan.spec.shape))}"
+        # "tiles3": what the variant ids stand for and that the automatic choice
+        # was timed; entries of other sets don't count
+        key = (f"tiles3|{arch}|{plan.spec.ndim}|{'x'.join(map(str, plan.spec.shape))}"
                f"|{plan.spec.field}")
         if os.path.exists(cache):
             with open(cache) as f:
@@ -307,9 +343,14 @@ def autotune_stencil(plan: Plan, m, work=None, steps: int = 20, apply: bool = Tr
                                                 _stream(m.device)), "rtm_autotune_stencil")
         us_all[b] = [round(float(us[i]), 2) for i in range(last)]
         mism_all = [max(mism_all[i], int(mism[i])) for i in range(last)]
-        v = int(bv.value)
-        if us_all[b][v] < best[2]:
-            best = (v, b, us_all[b][v])
+        t, v = min((t, i) for i, t in enumerate(us_all[b]) if mism[i] == 0)
+        if t < best[2]:
+            best = (v, b, t)
+    set_stencil_blocks(blocks_before)
+    auto = round(_automatic_us(plan, m, work, int(steps)), 2)
+    us_all.setdefault(2048, []).append(auto)
+    if auto <= best[2]:
+        best = (-1, 2048, auto)
     res = {"best": best[0], "blocks": best[1], "us": us_all, "mismatch": mism_all, "cached": False}
     set_stencil_blocks(res["blocks"] if apply else blocks_before)
     if apply:

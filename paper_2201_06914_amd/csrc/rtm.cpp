@@ -1513,7 +1513,9 @@ extern "C" rtm_status fwi_gradient_exact(const rtm_plan *P, const void *m, const
 // Every candidate kernel runs one step from the same hash-pattern levels; its
 // output must equal the one-thread-per-cell kernel's bit for bit (the
 // per-cell arithmetic is shared, so any difference is a tiling or
-// synchronisation bug).  Passing candidates are timed over `steps` launches.
+// synchronisation bug).  Passing candidates are timed over `steps` launches,
+// and so is the automatic choice (variant -1): its z chunks and, in 2D, its
+// several steps per launch are out of reach of any fixed variant.
 template <typename T>
 static rtm_status autotune_impl(const rtm_plan *P, const void *mv, char *w, int steps,
                                 int32_t *best, float *us, int64_t *mismatch, hipStream_t st) {
@@ -1538,7 +1540,9 @@ static rtm_status autotune_impl(const rtm_plan *P, const void *mv, char *w, int 
   int best_v = kStencilSimple;
   const int last = P->d.ndim == 3 ? kStencilVariants : kStencilSimple;
   rtm_status status = RTM_OK;
+  bool clean = true;
   for (int v = kStencilSimple; v <= last && status == RTM_OK; ++v) {
+    if (tiled_kernel(v) != v) continue;  // (reported below)
     // both z-marching directions against the one-thread-per-cell step
     unsigned long long diff = 0;
     hipError_t e = launch_fill<double>(reinterpret_cast<double *>(cnt), 1, 0.0, st);
@@ -1563,11 +1567,36 @@ static rtm_status autotune_impl(const rtm_plan *P, const void *mv, char *w, int 
     const float t = steps > 0 ? 1e3f * ms / steps : 0.f;
     if (us) us[v] = t;
     if (mismatch) mismatch[v] = (int64_t)diff;
+    clean = clean && diff == 0;
     if (diff == 0 && (!have_best || t < best_t)) {  // fastest bitwise-correct candidate
       have_best = true;
       best_t = t;
       best_v = v;
     }
+  }
+  for (int v = kStencilSimple; v <= last && status == RTM_OK; ++v) {
+    if (us) us[v] = us[tiled_kernel(v)];
+    if (mismatch) mismatch[v] = mismatch[tiled_kernel(v)];
+  }
+  if (status == RTM_OK && clean) {  // the automatic choice
+    hipError_t e = hipEventRecord(e0, st);
+    for (int i = 0; i < steps && e == hipSuccess;) {
+      const int left = std::min({kMaxSteps2D, steps - i, P->R - 2});
+      if (P->d.ndim == 2 && stencil2d_multi<T>(N, left)) {
+        e = launch_stencil2d<T>(a, InjMap<T>(), 0, ring, ld, P->R, 0, left, st);
+        i += left;
+      } else {
+        e = launch_stencil<T>(P->d.ndim, a, InjMap<T>(), -1, g_stencil_blocks, st,
+                              g_stencil_alternate ? (i & 1) : 0);
+        ++i;
+      }
+    }
+    if (e == hipSuccess) e = hipEventRecord(e1, st);
+    if (e == hipSuccess) e = hipEventSynchronize(e1);
+    float ms = 0.f;
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+    if (e != hipSuccess) status = fail(RTM_E_HIP, "autotune: %s", hipGetErrorString(e));
+    else if (steps > 0 && 1e3f * ms / steps <= best_t) best_v = -1;
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

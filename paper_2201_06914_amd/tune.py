@@ -110,21 +110,22 @@ def autotune_k_block(spec: api.PlanSpec, m, src_pos, q, rec_pos, Z, candidates=(
     return dict(res, cached=False)
 
 
-def autotune_batch(specs, shots, variants=(1, 3, 7, 11, 12), blocks=(2048, 4096, 8192),
+def autotune_batch(specs, shots, variants=(1, 7), blocks=(2048, 4096, 8192),
                    steps: int = 128, cache: str | None = None, k_blocks=(32, 64, 128)) -> dict:
     """Times the batched gradient over the first `steps` time steps (a
-    multiple of every k) for every (stencil variant, z-split target) pair,
-    recreating the batch for each target (the tile table is fixed when a
+    multiple of every k) for every (stencil variant, z-split target) pair
+    (batches know two kernels: variants 1 and 7, without and with non-temporal
+    streaming), recreating the batch for each target (the tile table is fixed when a
     batch is created), then, with the best pair, every probe-block length in
     k_blocks whose memory fits.  shots: the per-shot input dicts of
-    Batch.fwi_gradient.  Applies nothing; returns {"best": (variant, blocks),
-    "k_block": k, ...}.  Apply with api.set_stencil_blocks(blocks) before
+    Batch.fwi_gradient.  Applies nothing (the variant and target set before
+    are set again); returns {"best": (variant, blocks), "k_block": k, ...}.  Apply with api.set_stencil_blocks(blocks) before
     creating the batch (with k_block = k in its descriptors) and
     api.set_stencil_variant(variant) before running it."""
     if cache is None:
         cache = os.environ.get("RTM_TUNE_CACHE") or None
     dev = shots[0]["m"].device
-    key = ("batch|tiles2|" + _arch(dev) + "|" + ";".join("x".join(map(str, s.shape)) for s in specs)
+    key = ("batch|tiles3|" + _arch(dev) + "|" + ";".join("x".join(map(str, s.shape)) for s in specs)
            + f"|{specs[0].field}|{specs[0].probe}|r{specs[0].r}|k{','.join(map(str, k_blocks))}")
     hit = _cache_get(cache, key)
     if hit:
@@ -136,7 +137,7 @@ def autotune_batch(specs, shots, variants=(1, 3, 7, 11, 12), blocks=(2048, 4096,
     tshots = [dict(sh, q=sh["q"][:nt].contiguous(), Z=sh["Z"][:nt].contiguous(),
                    d_obs=sh["d_obs"][:nt].contiguous()) for sh in shots]
     ms = {}
-    blocks_before = api.get_stencil_blocks()
+    blocks_before, variant_before = api.get_stencil_blocks(), api.get_stencil_variant()
     for b in blocks:
         api.set_stencil_blocks(b)
         B = api.Batch(tspecs)
@@ -174,6 +175,7 @@ def autotune_batch(specs, shots, variants=(1, 3, 7, 11, 12), blocks=(2048, 4096,
             del B, outs, work
             torch.cuda.empty_cache()
     api.set_stencil_blocks(blocks_before)
+    api.set_stencil_variant(variant_before)
     kbest = min(kms, key=kms.get) if kms else specs[0].k_block
     res = {"best": [v, b], "k_block": kbest, "ms_per_step": ms, "k_ms_per_step": kms,
            "steps_timed": nt}
