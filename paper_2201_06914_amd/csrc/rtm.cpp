@@ -1046,11 +1046,14 @@ extern "C" rtm_status rtm_dot(const rtm_plan *P, const void *a, const void *b, i
 
 // Graphs of single-shot launch sequences (rtm_set_graph): keyed by a hash of
 // everything baked into the launches (plan, pointers, point counts, kernel
-// choices); at most kGraphCache kept, the oldest dropped.  Shared by all
-// threads (a mutex guards the table; a replay itself is a stream launch).
+// choices); at most kGraphCache kept, the oldest dropped once its last replay
+// is done (shots of one plan in turn drop one each when their sources' cells
+// differ).  Shared by all threads (a mutex guards the table; a replay itself is
+// a stream launch).
 struct GraphEntry {
   uint64_t key;
   hipGraphExec_t exec;
+  hipEvent_t done;  // recorded behind its last replay
 };
 static std::mutex g_graph_mu;
 static std::vector<GraphEntry> g_graphs;
@@ -1094,8 +1097,12 @@ static rtm_status run_launches(uint64_t key, hipStream_t st, F body) {
   HIP_TRY(hipEventRecord(gs.in, st));
   HIP_TRY(hipStreamWaitEvent(gs.s, gs.in, 0));
   hipGraphExec_t exec = nullptr;
+  hipEvent_t done = nullptr;
   for (const GraphEntry &e : g_graphs)
-    if (e.key == key) exec = e.exec;
+    if (e.key == key) {
+      exec = e.exec;
+      done = e.done;
+    }
   if (!exec) {
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(gs.s, hipStreamCaptureModeThreadLocal));
@@ -1113,12 +1120,21 @@ static rtm_status run_launches(uint64_t key, hipStream_t st, F body) {
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return fail(RTM_E_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
     if (g_graphs.size() >= kGraphCache) {
-      (void)hipGraphExecDestroy(g_graphs.front().exec);
+      const GraphEntry old = g_graphs.front();
       g_graphs.erase(g_graphs.begin());
+      (void)hipEventSynchronize(old.done);
+      (void)hipEventDestroy(old.done);
+      (void)hipGraphExecDestroy(old.exec);
     }
-    g_graphs.push_back({key, exec});
+    e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+    if (e != hipSuccess) {
+      (void)hipGraphExecDestroy(exec);
+      return fail(RTM_E_HIP, "hipEventCreate: %s", hipGetErrorString(e));
+    }
+    g_graphs.push_back({key, exec, done});
   }
   HIP_TRY(hipGraphLaunch(exec, gs.s));
+  HIP_TRY(hipEventRecord(done, gs.s));
   HIP_TRY(hipEventRecord(gs.out, gs.s));
   HIP_TRY(hipStreamWaitEvent(st, gs.out, 0));
   return RTM_OK;
