@@ -915,7 +915,7 @@ def main():
         torch.cuda.empty_cache()
         try:
             rec_line["rsweep"] = bench_rsweep(a.rsweep_n, a.rsweep_nt,
-                                              tune["best"] if tune["best"] >= 1 else 7)
+                                              tune["best"] or 7)
         except Exception as e:
             rec_line["rsweep"] = {"error": f"{type(e).__name__}: {e}"}
         torch.cuda.empty_cache()
@@ -923,7 +923,7 @@ def main():
         torch.cuda.empty_cache()
         try:
             rec_line["fwi"] = bench_fwi(a.rsweep_n, a.rsweep_nt, a.fwi_iters, 64,
-                                        tune["best"] if tune["best"] >= 1 else 7)
+                                        tune["best"] or 7)
         except Exception as e:
             rec_line["fwi"] = {"error": f"{type(e).__name__}: {e}"}
         torch.cuda.empty_cache()
@@ -946,7 +946,7 @@ def main():
         rec_line["cpu_baseline"], slab = cpu_baseline(a.cpu_planes, a.cpu_nt, r)
         try:
             rec_line["precision"] = bench_precision(slab, (384, 512, 512), 256, r, k,
-                                                    tune["best"] if tune["best"] >= 1 else 7)
+                                                    tune["best"] or 7)
         except Exception as e:
             rec_line["precision"] = {"error": f"{type(e).__name__}: {e}"}
     print(json.dumps(rec_line), flush=True)
