@@ -756,20 +756,22 @@ struct FuseArgs {
 // Whether blocks that the wide fast kernels do not divide (r = 8, 24, 96;
 // short blocks) take the fast kernel with one row tile at a time or the edge
 // kernel.  For KS <= 2 the fast kernel holds a tile's operands; the edge kernel
-// is ahead only for fused blocks of one or two row tiles on small grids.  For
-// longer blocks the fast kernel reads the levels again for every row tile and
+// is ahead only for fused blocks of at most 16 steps and one or two row tiles on
+// small grids.  For longer blocks the fast kernel reads the levels again for every row tile and
 // the edge kernel keeps all chunks' operands; for F16S updates and fused BF16
 // the edge kernel is slow all the same.  us a block on 100^3, fast / edge:
 // update, k = 24, r = 32 55 / 57, r = 96 118 / 141; k = 50, r = 32 80 / 91, r = 96 177 / 178 (three
 // times the levels; 200 x 250 x 250 2.42 / 2.11 ms); k = 100, r = 32 118 / 203, r = 128 472 /
-// 418; F16S k = 50, r = 96 204 / 284; fused, k = 20, r = 32 38 / 36 (200 x 250 x
-// 250 463 / 495), r = 96 79 / 97; k = 50, r = 32 70 / 63, r = 128 188 / 141 (BF16 172
-// / 251); k = 100, r = 32 104 / 165, r = 128 342 / 303.  FP32 operands: k = 50 r = 8 97 / 83,
-// k = 100, r = 8 139 / 218, r = 96 500 / 469.
+// 418; F16S k = 50, r = 96 204 / 284; fused, k = 10, r = 32 35 / 32, r = 96 75 /
+// 94; k = 20, r = 32 38 / 36, but the gradient's steps find more of their levels
+// in the caches after the fast kernel's non-temporal loads (r = 32, k = 32, real
+// probes, 100^3: 24.3 ms a gradient / 24.8); k = 50, r = 32 70 / 63, r = 128 188 / 141 (BF16 172
+// / 251); k = 100, r = 32 104 / 165, r = 64 177 / 215, r = 128 342 / 303 (F16S r = 64 210 / 208).
+// FP32 operands: k = 50 r = 8 97 / 83, k = 100, r = 8 139 / 218, r = 96 500 / 469.
 template <int KS, int OP, bool FUSED>
 static bool one_row_tile(int MT, int64_t N) {
-  if (KS <= 2) return !FUSED || OP == OP_BF16 || MT >= 3 || N >= 4000000;
-  if (FUSED) return OP == OP_BF16 || (KS == 8 && MT == 1);
+  if (KS <= 2) return !FUSED || KS == 2 || OP == OP_BF16 || MT >= 3 || N >= 4000000;
+  if (FUSED) return OP == OP_BF16 || (KS == 8 && MT <= (OP == OP_BF16X2 ? 2 : 1));
   return OP == OP_F16S || (MT == 1 && (OP != OP_F32 || KS == 8));
 }
 

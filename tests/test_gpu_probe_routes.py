@@ -76,8 +76,9 @@ def test_update_block_route(probe, r, k, kernel):
     assert float(got[:, N:].abs().max()) == 0          # padding cells
 
 
-FUSED = [("bf16x2", 32, 20, "k_probe_mfma_edge<2"), ("bf16x2", 96, 20, "k_probe_mfma_fast<2"),
+FUSED = [("bf16x2", 32, 12, "k_probe_mfma_edge<1"), ("bf16x2", 32, 20, "k_probe_mfma_fast<2"), ("bf16x2", 96, 20, "k_probe_mfma_fast<2"),
          ("bf16x2", 32, 50, "k_probe_mfma_edge<4"), ("bf16x2", 32, 70, "k_probe_mfma_fast<8"),
+         ("bf16x2", 64, 70, "k_probe_mfma_fast<8"), ("f16s", 64, 70, "k_probe_mfma_edge<8"),
          ("bf16x2", 96, 70, "k_probe_mfma_edge<8"), ("f16s", 96, 50, "k_probe_mfma_edge<4"),
          ("bf16", 32, 20, "k_probe_mfma_fast<2"), ("bf16", 96, 50, "k_probe_mfma_fast<4")]
 
