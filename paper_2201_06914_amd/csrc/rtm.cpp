@@ -466,15 +466,21 @@ static FoldInto fold_into(const rtm_plan *P, bool epilogue = false) {
 // against 13.5).
 // A tile marches z, and each plane of it that holds entries costs a chain of
 // loads that every wave waits for: 0.3 us a plane where a cell has one point of
-// weight one, 1.2 us and more off the grid, with its four cells per thread in
-// turn.  So a set on one plane (off the grid: two) is taken, a spread in depth is
-// not.  us per step, folded / launched: a 200 x 200 surface in 200^3 28 / 31 (off
-// the grid 31 / 31), in 384 x 512 x 512 257 / 261 (264 / 262; every seventh
-// point in 320 x 448 x 448 192 / 177: beyond the caches off-grid sets are
-// launched); wall of all y and z in 384 x 512 x 512 368 / 276 (off the grid 819 /
-// 280), of all x and z 490 / 261 (1067 / 267), in 128^3 14.5 / 12.4 (26.5 /
-// 13.3); a vertical column in 128^3 10.1 / 11.9 (13.4 / 12.3), in 384 x 512 x 512
-// 317 / 261 (503 / 260); 500 points in one cell of 128^3 256 / 90.
+// weight one, 1.2 us and more off the grid, with the cells of a thread in turn.
+// So a set on one plane is taken (off the grid: two planes, with at most one
+// entry per cell of its box, or two in FP64, which has two cells to a thread),
+// a spread in depth is not, but for a column of points on the grid.  us per
+// step, folded / launched:
+//   surface on the grid    200^3 28 / 31, 384 x 512 x 512 257 / 261
+//   off it, 2 cells apart  200^3 31 / 31, 384 x 512 x 512 264 / 262; every
+//     seventh point of 320 x 448 x 448 192 / 177: beyond the caches launched
+//   off it, 128^3          at two entries a cell 17 / 13 (FP64 17.4 / 18.9), at
+//     four 23 / 13 (20.4 / 19.4)
+//   wall of y and z        384 x 512 x 512 368 / 276 (off the grid 819 / 280)
+//   wall of x and z        there 490 / 261 (1067 / 267), 128^3 14.5 / 12.4
+//   column of z            128^3 10.1 / 11.9 (13.4 / 12.3), 384 x 512 x 512
+//     317 / 261 (503 / 260)
+//   500 points in one cell 128^3 256 / 90
 template <typename T>
 static bool make_map(const rtm_plan *P, const HostPoints<T> &hp, size_t cap, FoldInto into,
                      std::vector<int32_t> &map, InjMap<T> *j) {
@@ -493,7 +499,8 @@ static bool make_map(const rtm_plan *P, const HostPoints<T> &hp, size_t cap, Fol
     if (P->d.ndim == 2 && sizeof(T) == 8 && P->N >= 250000 && most > 2) return false;
   } else if (whole) {
     if (bz > 2 && !(by * bx == 1 && into == FOLD_CACHED)) return false;
-  } else if (bz > 2 || most > 4 || into == FOLD_STREAM) {
+  } else if (bz > 2 || most > 4 || into == FOLD_STREAM ||
+             (int64_t)(hp.ipt.size() - (size_t)hp.ioff[hp.c0]) > vol * (sizeof(T) == 8 ? 2 : 1)) {
     return false;
   }
   map.assign((size_t)vol, -1);

@@ -17,6 +17,9 @@ def _set(kind, shape):
     z, y, x = np.arange(1.0, nz - 1), np.arange(0.0, ny - 1, 2), np.arange(0.0, nx - 1, 2)
     if kind.startswith("surface"):
         p = np.stack(np.meshgrid([3.0], y, x, indexing="ij"), -1).reshape(-1, 3)
+    elif kind.startswith("dense"):                        # between all cells of a row
+        y, x = np.arange(0.0, ny - 1), np.arange(0.0, nx - 1)
+        p = np.stack(np.meshgrid([3.0], y, x, indexing="ij"), -1).reshape(-1, 3) - [0, 0.25, 0]
     elif kind.startswith("wall"):
         p = np.stack(np.meshgrid(z, y, [5.0], indexing="ij"), -1).reshape(-1, 3)
     elif kind.startswith("column"):
@@ -31,10 +34,11 @@ def _set(kind, shape):
 SMALL, CACHED, STREAM = (30, 26, 44), (64, 50, 72), (200, 452, 452)
 FOLDED = [(SMALL, "f32", k) for k in ("surface", "surface off", "wall off", "column off", "pile off")]
 FOLDED += [(CACHED, f, k) for f in ("f32", "f64") for k in ("surface", "surface off", "column")]
-FOLDED += [(STREAM, "f32", "surface")]
+FOLDED += [(STREAM, "f32", "surface"), (CACHED, "f64", "dense off")]
 FOLDED += [((90, 1, 80), f, k) for f in ("f32", "f64") for k in ("column off", "pile off")]
 LAUNCHED = [(CACHED, f, k) for f in ("f32", "f64") for k in ("wall", "wall off", "column off",
                                                               "pile off")]
+LAUNCHED += [(CACHED, "f32", "dense off")]
 LAUNCHED += [(STREAM, "f32", k) for k in ("surface off", "column", "wall")]
 LAUNCHED += [((520, 1, 500), "f64", "pile off")]
 
