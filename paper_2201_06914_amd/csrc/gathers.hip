@@ -169,8 +169,8 @@ __device__ __forceinline__ void gather_finish(const GatherThread<T, GX> &th, con
 // the order of memory; the segment's and the halo's tiles are loaded whole and
 // a lane's cell is found by its place in the tile (the row may start inside
 // one).  A 16 x 4 operand then reads its same-parity cells 2 words apart and
-// its probe rows 32 words apart: 32 lanes on distinct banks.  Cells of the
-// neighbouring x rows come along with the first and last tile; they only meet
+// its probe rows 32 words apart: the words of half a wave lie on distinct banks.
+// Cells of the neighbouring x rows come along with the first and last tile; they only meet
 // products that are not written (a) or written as zero (b).
 // Chunks of 8 probe rows stream into two LDS buffers, one chunk in flight; the
 // buffers are distinct arrays alternated statically, so the compiler can tell
@@ -184,12 +184,14 @@ __device__ __forceinline__ void gather_finish(const GatherThread<T, GX> &th, con
 // 2.5 (3.5: an [offset][a] array cost an address, a range check and a choice
 // of three buffers per product; without any store it took as long).  Three
 // buffers with two chunks in flight leave room for three workgroups instead
-// of four or five: 7.4 ms.  nh = 64, r = 32, 120 x 200 x 301: 2.1 (5.2).
+// of four or five: 7.4 ms.  nh = 64, r = 32, 120 x 200 x 301: 2.1 (5.2).  At nh =
+// 40 the counters show 6.7e8 cycles of LDS bank conflicts, a sixth of the CUs'
+// cycles, over staging writes, operand reads and the way out together.
 typedef float gv4f __attribute__((ext_vector_type(4)));
 
 constexpr int GR = 8;      // probe rows per chunk: a tile's chunk is 1 KB
 constexpr int GTW = 32 * GR;  // its words
-constexpr int GOS = 37;    // product rows on their way out: no bank conflicts either way
+constexpr int GOS = 37;    // product rows on their way out (odd: rows start on different banks)
 __host__ __device__ constexpr int gm_ut(int nt) { return nt + 1; }              // U tiles
 __host__ __device__ constexpr int gm_vt(int nt, int nbt) { return nt + nbt; }   // V tiles
 __host__ __device__ constexpr int gm_buf(int nt, int nbt) {

@@ -705,8 +705,8 @@ __global__ __launch_bounds__(256) void k_probe_mfma_edge(ProbeArgs<float> p,
 }
 
 // process wide (rtm_set_probe_nt): non-temporal compressed-field traffic in the
-// fast kernels (default on: 11.3 -> 10.3 ms for the fused adjoint block and
-// 23.3 -> 22.8 ms for the forward block at 384 x 512 x 512, r = 128, k = 32)
+// fast kernels (default on: 11.2 -> 10.2 ms for the fused adjoint block and
+// 22.2 -> 20.8 ms for the forward block at 384 x 512 x 512, r = 128, k = 32)
 int g_probe_nt = 1;
 void set_probe_nt(int on) { g_probe_nt = on ? 1 : 0; }
 int get_probe_nt() { return g_probe_nt; }
@@ -756,18 +756,23 @@ struct FuseArgs {
 // Whether blocks that the wide fast kernels do not divide (r = 8, 24, 96;
 // short blocks) take the fast kernel with one row tile at a time or the edge
 // kernel.  For KS <= 2 the fast kernel holds a tile's operands; the edge kernel
-// is ahead only for fused blocks of at most 16 steps and one or two row tiles on
-// small grids.  For longer blocks the fast kernel reads the levels again for every row tile and
-// the edge kernel keeps all chunks' operands; for F16S updates and fused BF16
-// the edge kernel is slow all the same.  us a block on 100^3, fast / edge:
-// update, k = 24, r = 32 55 / 57, r = 96 118 / 141; k = 50, r = 32 80 / 91, r = 96 177 / 178 (three
-// times the levels; 200 x 250 x 250 2.42 / 2.11 ms); k = 100, r = 32 118 / 203, r = 128 472 /
-// 418; F16S k = 50, r = 96 204 / 284; fused, k = 10, r = 32 35 / 32, r = 96 75 /
-// 94; k = 20, r = 32 38 / 36, but the gradient's steps find more of their levels
-// in the caches after the fast kernel's non-temporal loads (r = 32, k = 32, real
-// probes, 100^3: 24.3 ms a gradient / 24.8); k = 50, r = 32 70 / 63, r = 128 188 / 141 (BF16 172
-// / 251); k = 100, r = 32 104 / 165, r = 64 177 / 215, r = 128 342 / 303 (F16S r = 64 210 / 208).
-// FP32 operands: k = 50 r = 8 97 / 83, k = 100, r = 8 139 / 218, r = 96 500 / 469.
+// is ahead only for fused blocks of at most 16 steps and one or two row tiles
+// on small grids.  For longer blocks the fast kernel reads the levels again for
+// every row tile and the edge kernel keeps all chunks' operands; for F16S
+// updates and fused BF16 the edge kernel is slow all the same.  us a block on
+// 100^3, fast / edge:
+//   update  k = 24: r = 32 55 / 57, r = 96 118 / 141
+//           k = 50: r = 32 80 / 91, r = 96 177 / 178 (200 x 250 x 250 2420 /
+//             2110), F16S r = 96 204 / 284, FP32 operands r = 8 97 / 83
+//           k = 100: r = 32 118 / 203, r = 128 472 / 418, FP32 operands r = 8
+//             139 / 218, r = 96 500 / 469
+//   fused   k = 10: r = 32 35 / 32, r = 96 75 / 94
+//           k = 20: r = 32 38 / 36, but the gradient's steps find more of
+//             their levels in the caches after the fast kernel's non-temporal
+//             loads (real probes, r = 32, k = 32: 24.3 ms a gradient / 24.8)
+//           k = 50: r = 32 70 / 63, r = 128 188 / 141 (BF16 172 / 251)
+//           k = 100: r = 32 104 / 165, r = 64 177 / 215 (F16S 210 / 208),
+//             r = 128 342 / 303
 template <int KS, int OP, bool FUSED>
 static bool one_row_tile(int MT, int64_t N) {
   if (KS <= 2) return !FUSED || KS == 2 || OP == OP_BF16 || MT >= 3 || N >= 4000000;
@@ -785,7 +790,8 @@ static void launch_probe_kernels(const ProbeArgs<float> &p, const void *Z, int M
   const int set = g_probe_grid[FUSED ? 1 : 0];
   // which kernel takes the full tiles: several row tiles at a time where they
   // divide whole blocks (four; the fused kernel, which also holds the forward
-  // field, two), or one, or none (the edge kernel takes all)
+  // field, two; bound by HBM: r = 128, k = 32 on 320 x 448 x 448 12.8 ms, 5.8
+  // TB/s), or one, or none (the edge kernel takes all)
   const bool whole = p.r % 32 == 0 && p.kb == 16 * KS && MT % 2 == 0;
   // without the hint the wide kernels run without it and the rest of the
   // blocks the edge kernel, which has none (FP32 operands keep it)

@@ -1719,8 +1719,13 @@ extern "C" rtm_status rtm_batch_create(const rtm_desc *shots, int32_t nshots, rt
   b->stream = 16 * cells > kStreamBytes;
   // Rows that are no multiple of four cut a cache line at every tile's edge;
   // where they stream from HBM, half as many edges are worth up to a quarter
-  // of idle lanes (8 windows of 128^3 .. 256 x 320 x 320, 92.6 M cells: 178 ms
-  // a gradient against 184).
+  // of idle lanes (the threshold of single grids, a seventh, is that of two
+  // rows per thread, which batches don't have).  ms a gradient, r = 64, k = 32,
+  // nt = 128, 64 x 16 / 128 x 8 tiles: 8 windows of 128^3 .. 256 x 320 x 320
+  // (17 % more columns) 181 / 174; 8 of 128 x 200 x 257 .. 256 x 320 x 321 (15 %)
+  // 250 / 247; 7 of 128 x 200 x 321 .. 256 x 320 x 383 (none) 265 / 254; but 8 of
+  // 160 x 200 x 129 .. 256 x 320 x 255 (10 %) 172 / 186.  Non-temporal they took
+  // 175, 241, 254 and 191 with 128 x 8 tiles, 186, 245, 280 and 206 with 64 x 16.
   if (b->ragged && b->stream) {
     int64_t c64 = 0, c128 = 0;
     bool fits = true;

@@ -3,10 +3,12 @@
 // L the 8th-order Laplacian with the field taken as zero outside the grid.
 // Forward and adjoint sweeps use the same step (the operator is symmetric).
 //
-// Two kernels share one per-cell arithmetic (cell_lap / cell_update), so their
+// Three kernels share one per-cell arithmetic (axis_sum / cell_update), so their
 // results are bitwise identical:
 //   k_stencil_simple  one thread per cell, neighbours from global memory
-//                     (2D and small grids, reference for the tiled kernel)
+//                     (small and thin grids, large 2D grids; the reference for
+//                     the others)
+//   k_stencil2d_steps 2D: up to four steps per launch
 //   k_stencil3d_tiled 3D: a TX x TY column tile per workgroup marches through
 //                     a z-chunk; the planes z .. z+4 (with a 4-cell x/y halo)
 //                     sit in a ring of LDS planes, and the z neighbours in a
@@ -341,7 +343,7 @@ __device__ __forceinline__ void vstore(__amdgpu_buffer_rsrc_t r, const VOff &o,
 
 // Bound: beyond the caches by HBM (16 bytes per cell-update; 384 x 512 x 512
 // 261 us, 6.2 TB/s, where the copy kernel reaches 5.9-6.4), before that by the
-// latency of a step.  42 VALU instructions per cell-update (81 with one cell
+// latency of a step.  43 VALU instructions per cell-update (81 with one cell
 // per thread and lane-wise LDS reads, where vector issue bound the step as
 // much as HBM did: 286-318 us at 384 x 512 x 512, 188-255 at 320 x 448 x 448
 // now 173, 27 at 128^3 now 8.8).
@@ -701,10 +703,12 @@ static TileShape tile_shape(int variant) {
 
 // Automatic choice of the kernel and its z chunks (us per step, F32 unless
 // said; v: the variant).
-//   Grids below kSimpleCells run one thread per cell: as fast as the tiled
-//   kernel (40 x 36 x 70: 4.3 against 4.2), and a folded injection waits for
-//   one cell's entries per thread, not four's (gradient there 1.40 against
-//   1.55 ms).  64^3: 5.8 against 4.0.
+//   Grids below kSimpleCells run one thread per cell.  Bare steps cross near
+//   100 K cells (tiled / thread per cell: 101 K cells 4.8 / 4.8, 124 K 4.2 / 5.0,
+//   150 K 4.5 / 5.2, 64^3 4.7 / 6.0; FP64 101 K 5.0 / 5.1, 201 K 5.0 / 6.2), adjoint
+//   steps near 200 K, as a folded injection waits for one cell's entries per
+//   thread, not four's (receivers on a plane: 148 K cells 5.4 / 4.9, 201 K 5.4 /
+//   5.5; every seventh off the grid: 6.1 / 5.2 and 6.5 / 5.4): the line between.
 //   So do grids that would leave four fifths of the tiles' lanes idle (FP64,
 //   and F32 in brackets, thread per cell against tiled): 300 x 300 x 20, 31 %
 //   of the lanes, 27 against 25 (23, 16); 1000 x 16 x 16, 25 %, 8.3 against
@@ -718,9 +722,11 @@ static TileShape tile_shape(int variant) {
 //   (one thread per cell 15.8 and 28); 300^3 166 non-temporal, 200 not.
 //   Beyond that the levels stream from HBM: non-temporal, 64 x 32 tiles.  If
 //   one or more whole chunks per column fill nearly all 256 CUs with one
-//   workgroup each, that is fastest (384 x 512 x 512: 2 chunks, 256
-//   workgroups, 261; 16-plane chunks 288), else chunks of 16 planes (320 x 448
-//   x 448: 173; 196 workgroups of 160 planes 181; v1 220).
+//   workgroup each, they are the chunks, else 16 planes.  Against that, 128 x 8
+//   tiles with their best split: 384 x 512 x 512 (2 chunks) 254 / 256 (16-plane
+//   chunks 288), 256 x 512 x 512 159 / 163, 320 x 448 x 448 170 / 183, 300 x 300 x
+//   512 116 / 125, 352 x 384 x 384 140 / 136, 512 x 400 x 400 270 / 272, 400^3 209 /
+//   206, 300 x 400 x 400 155 / 150, 384 x 448 x 512 261 / 251.
 //   F32 rows that are no multiple of the vector cut a cache line at every
 //   tile's edge.  128-cell tiles have half as many edges and stream (320 x 448
 //   x 447: 236; 64 x 32 ordinary 261, non-temporal 274; 260 x 320 x 501 152,
